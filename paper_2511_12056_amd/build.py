@@ -3,13 +3,15 @@ from __future__ import annotations
 
 import os
 import subprocess
+import tempfile
+from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libpipedit_attn.so")
-SOURCES = ["attn_fwd.hip", "attn_fwd_sp.hip", "merge.hip", "layout.hip", "probe.hip", "api.hip"]
+SOURCES = ["attn_fwd.hip", "attn_fwd_sp.hip", "attn_fwd_sp_d64.hip", "merge.hip", "layout.hip", "probe.hip", "api.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
-FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
+FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          "-Wno-unused-command-line-argument",
          "-Wno-inline-asm"]      # the DMA helpers declare m0, a register the compiler reserves, as clobbered
@@ -24,16 +26,25 @@ def build_library(verbose: bool = False, host_sanitizers: bool = False) -> str:
         flags = [f for f in flags if f != "-O3"] + ["-O1", "-g", "-Xarch_host", "-fsanitize=address",
                                                       "-Xarch_host", "-fsanitize=undefined",
                                                       "-Xarch_host", "-fno-omit-frame-pointer"]
-    cmd = [HIPCC, *flags, *[os.path.join(CSRC, s) for s in SOURCES], "-o", LIB]
-    if verbose:
-        print(" ".join(cmd), flush=True)
-    res = subprocess.run(cmd, capture_output=True, text=True)
     noise = "is not a recognized feature for this target"
-    err = "\n".join(l for l in res.stderr.splitlines() if noise not in l)
-    if res.returncode != 0:
-        raise RuntimeError("hipcc failed:\n" + err)
-    if verbose and err.strip():
-        print(err)
+
+    def run(cmd):
+        if verbose:
+            print(" ".join(cmd), flush=True)
+        res = subprocess.run(cmd, capture_output=True, text=True)
+        err = "\n".join(l for l in res.stderr.splitlines() if noise not in l)
+        if res.returncode != 0:
+            raise RuntimeError("hipcc failed:\n" + err)
+        if verbose and err.strip():
+            print(err)
+
+    # the sources compile side by side (the attention kernels take minutes), then one link
+    with tempfile.TemporaryDirectory() as tmp:
+        objs = [os.path.join(tmp, s + ".o") for s in SOURCES]
+        with ThreadPoolExecutor(max_workers=4) as pool:
+            list(pool.map(lambda so: run([HIPCC, *flags, "-c", os.path.join(CSRC, so[0]), "-o", so[1]]), zip(SOURCES, objs)))
+        link = [f for f in flags if not f.startswith("-O")]
+        run([HIPCC, *link, "-shared", *objs, "-o", LIB])
     return LIB
 
 

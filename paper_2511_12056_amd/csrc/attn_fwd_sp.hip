@@ -1,10 +1,8 @@
-// Flash-attention forward, software-pipelined schedule for gfx950, d = 128, 64-key tiles,
-// 256 query rows per workgroup.  Template parameter NQ = number of 32-row query sub-tiles a
-// wavefront owns.  Only NQ = 1 (8 wavefronts, two per SIMD) is instantiated.  NQ = 2 (one wavefront
-// per SIMD, each K/V operand fragment feeding two MFMAs, half the LDS operand reads) needs the O
-// accumulators and Q fragments in accumulation registers, which the compiler only does when the
-// MFMAs are written in assembly; built that way it was slower (a single wavefront per SIMD leaves
-// the latencies at the iteration boundary exposed).
+// Flash-attention forward, software-pipelined schedule for gfx950, d = 128 and 64, 64-key tiles.
+// A workgroup of NW wavefronts sweeps 32 NW query rows: eight wavefronts (256 rows, one workgroup per
+// CU) or four (128 rows, two per CU); either way two wavefronts share a SIMD.  A wavefront owns 32 rows
+// (NQ = 1 sub-tile).  Two sub-tiles in one wavefront per SIMD, each K/V fragment feeding two MFMAs,
+// were slower: a single wavefront leaves the latencies at the iteration boundary exposed.
 //
 // MFMA formulation and LDS tile layout are those of attn_fwd.hip (S^T = K Q^T, O^T = V^T P^T on
 // v_mfma_f32_32x32x16_bf16, one query per lane, XOR-swizzled 16-byte granules).  Schedule: on
@@ -31,18 +29,30 @@
 // adds on the unrounded probabilities; the dot-product instructions (v_dot2c_f32_bf16), which
 // would sum two rounded ones at a time, occupy the matrix pipe and stall the MFMA stream.
 //
-// K/V tiles go from global memory straight into LDS (global_load_lds_dwordx4), four buffers per
-// tensor; the loop is unrolled four times so that every buffer offset is an immediate.  At the
-// top of iteration t a wavefront issues its share of K tile t+4 (over K tile t) and V tile t+2
-// (over V tile t-2), both last read in iteration t-1; before the barrier that closes the
-// iteration it waits for all but its two newest batches, i.e. for K tile t+2 and V tile t, which
-// iteration t+1 reads.
+// K/V tiles go from global memory straight into LDS (global_load_lds_dwordx4), NBUF buffers per tensor
+// (four; two for d = 128 with four wavefronts, so that two workgroups fit the CU's LDS); the loop is
+// unrolled four times so that every buffer offset is an immediate.  At the top of iteration t a
+// wavefront issues its share of K tile t+NBUF (over K tile t) and V tile t+NBUF-2 (over V tile t-2),
+// both last read in iteration t-1; before the barrier that closes the iteration it waits for K tile
+// t+2 and V tile t, which iteration t+1 reads: with four buffers all but its two newest batches.
+//
+// Between items nothing but the claim of the next one is serial: its Q fragments and first tiles are
+// fetched while the results are stored.  The first iteration carries no PV and the last PV no softmax.
+// What an item costs besides its key tiles went from 14 to 10 us (24 x 16 384 queries on 600 keys,
+// ten tiles per item: 196 -> 187 us with eight wavefronts; about 3 us of the rest are the loads of Q
+// and the first tiles, 3 us the stores).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 #include "attn_internal.h"
 #include "attn_device.h"
 
 namespace pda {
+
+constexpr int kTileRows = 256;       // query rows of a tile of the launch plan
+
+// LDS tile buffers per tensor (see the top of the file): four, or two where two workgroups of d = 128
+// share a CU's 160 KB.
+constexpr int sp_buffers(int d, int n_waves) { return d == 128 && n_waves < 8 ? 2 : 4; }
 
 // 16 bytes per lane from global memory (scalar base + per-lane byte offset) straight into LDS:
 // lane l's data lands at lds_addr + 16*l (lds_addr wave-uniform, passed in M0).  Inline assembly
@@ -68,11 +78,7 @@ __device__ __forceinline__ void lds_dma16_at(const void* sbase, unsigned voff, u
 
 template <int N>
 __device__ __forceinline__ void wait_vmcnt() {
-    static_assert(N == 4 || N == 8 || N == 16 || N == 0, "add the literal below");
-    if constexpr (N == 0) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    if constexpr (N == 4) asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
-    if constexpr (N == 8) asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
-    if constexpr (N == 16) asm volatile("s_waitcnt vmcnt(16)" ::: "memory");
+    asm volatile("s_waitcnt vmcnt(%0)" :: "n"(N) : "memory");
 }
 
 // BASE2: the scores are already in units of log2 (the caller folded scale*log2(e) into Q), so the
@@ -89,18 +95,20 @@ __device__ __forceinline__ constexpr int swz_k(int row) { return D == 128 ? (row
 template <int D>
 __device__ __forceinline__ constexpr int swz_v(int row) { return D == 128 ? ((row & 3) << 2) : (((row >> 1) & 1) << 2); }
 
-template <int D, int NQ, bool BASE2>
-__global__ __launch_bounds__(512 / NQ, 1) void attn_fwd_sp_kernel(const AttnParams p) {
+template <int D, int NW, bool BASE2>
+__global__ __launch_bounds__(64 * NW, 2) void attn_fwd_sp_kernel(const AttnParams p) {
     static_assert(D == 128 || D == 64, "head dimension");
-    constexpr int NW = 8 / NQ;            // wavefronts
+    static_assert(NW == 8 || NW == 4, "wavefronts per workgroup");
+    constexpr int NQ = 1;
     constexpr int BN = 64;
-    constexpr int M = 256;
+    constexpr int M = 32 * NW;            // query rows of an item
+    constexpr int SUB = kTileRows / M;    // items per query tile (and key range)
     constexpr int G = D / 8;              // 16-byte granules per row: 16 (d = 128) or 8
     constexpr int NKB = BN / 32;          // 2
     constexpr int NKK = D / 16;           // 8 or 4
     constexpr int NDB = D / 32;           // 4 or 2
     constexpr int TILE = BN * D * 2;      // 16 KB or 8 KB
-    constexpr int NBUF = 4;
+    constexpr int NBUF = sp_buffers(D, NW);
     constexpr int K_BASE = 0, V_BASE = NBUF * TILE;       // LDS byte offsets
     constexpr int CHUNKS = TILE / 1024;   // DMA chunks of 1 KB per tile: 16 or 8
     constexpr int CPW = CHUNKS / NW;      // per wavefront: 2 (4 with NQ = 2), or 1 for d = 64
@@ -109,122 +117,122 @@ __global__ __launch_bounds__(512 / NQ, 1) void attn_fwd_sp_kernel(const AttnPara
 
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     __shared__ int next_item;
+    __shared__ int redo_flag[NW];
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int li = lane & 31, lh = lane >> 5;
+    // Values formed from the lane index outside the sweep's main path (tail rows, masks, Q rows, store
+    // addresses) start from a copy that the compiler cannot trace back: it would otherwise form them
+    // once, ahead of the item loop, and carry them in registers that the sweep has no room for.
+    auto opaque = [](int x) { asm volatile("" : "+v"(x)); return x; };
+    const int64_t Sq = p.Sq;
+    const unsigned lds0 = (unsigned)(uintptr_t)(LDS_PTR(const void))smem;
 
-    // Persistent workgroups (one per CU) take work items in index order from a device counter: the
-    // chip's XCDs run at persistently different speeds (several percent apart under the power
-    // limit) and the hardware deals the workgroups of a grid to them round robin, so a grid with
-    // one workgroup per item would end with the slowest XCD while the others idle.  A launch with no
-    // more items than workgroups needs no counter: workgroup i takes item i and leaves.
+    // Persistent workgroups (one per CU) take work items in index order: workgroup i starts with item
+    // i and fetches the following ones from a device counter.  The chip's XCDs run at persistently
+    // different speeds (several percent apart under the power limit) and the hardware deals the
+    // workgroups of a grid to them round robin, so a grid with one workgroup per item would end with
+    // the slowest XCD while the others idle.  A launch with no more items than workgroups does not
+    // touch the counter.
     const bool direct = p.n_items <= (int)gridDim.x;
-    for (int round = 0;; ++round) {
-    int item;
-    if (direct) {
-        item = round == 0 ? (int)blockIdx.x : p.n_items;
-    } else {
-        if (tid == 0) next_item = atomicAdd(p.counter, 1);
-        __syncthreads();
-        item = __builtin_amdgcn_readfirstlane(next_item);
-        __syncthreads();                               // everyone has read it before the next fetch overwrites it
-    }
-    if (item >= p.n_items) break;
+    int item = (int)blockIdx.x;
 
     // ---- work item -> (query tile, head, key range).  Items [0, n_full) are whole tiles; then the
     // cut tiles' key ranges, range-major, so that the items in flight at any time sweep the same keys.
-    int tile = item, part = 0;
-    if (item >= p.n_full) {
-        const int idx = item - p.n_full;
-        part = idx / p.n_cut;
-        tile = p.n_full + (idx - part * p.n_cut);
-    }
-    const int bh = tile / p.tiles_per_head;
-    const int q_tile = tile - bh * p.tiles_per_head;
-    const int b = bh / p.Hg, h = bh - b * p.Hg;
-    // this item's key range [kv0, kv1) (tile aligned): all keys, or range `part` of a cut tile
-    int64_t kv0 = 0, kv1 = p.n_v;
-    if (p.split > 1 && tile >= p.n_full) {
-        kv0 = p.part_off[part];
-        kv1 = p.part_off[part + 1];
-    }
-    const __bf16* __restrict__ qp = p.q + (int64_t)b * p.q_bs + (int64_t)h * p.q_hs;
-    const __bf16* __restrict__ kp = p.k + (int64_t)b * p.kv_bs + (int64_t)h * p.kv_hs + kv0 * D;
-    const __bf16* __restrict__ vp = p.v + (int64_t)b * p.kv_bs + (int64_t)h * p.kv_hs + kv0 * D;
-    // part 0 writes the tile's rows of out/lse; later parts write rows 0..255 of their partial slot
-    float* __restrict__ op;
-    float* __restrict__ lp;
-    int64_t row_sub;                                   // subtracted from the global row on store
-    // With a bf16 `out` the merge pass needs fp32 partials of ALL parts of a cut tile, part 0 included.
-    const bool cut = p.split > 1 && tile >= p.n_full;
-    const bool to_ws = part > 0 || (cut && p.out_bf16);
-    if (!to_ws) {
-        op = p.out + (p.out_bf16 ? 0 : (int64_t)b * p.o_bs + (int64_t)h * p.o_hs);
-        lp = p.lse + (int64_t)b * p.l_bs + (int64_t)h * p.l_hs;
-        row_sub = 0;
-    } else {
-        const int64_t slot = p.out_bf16 ? (int64_t)(tile - p.n_full) * p.split + part
-                                        : (int64_t)(tile - p.n_full) * (p.split - 1) + (part - 1);
-        op = p.part_out + slot * (M * D);
-        lp = p.part_lse + slot * M;
-        row_sub = (int64_t)q_tile * M;
-    }
-    __bf16* __restrict__ oph = reinterpret_cast<__bf16*>(p.out) + (int64_t)b * p.o_bs + (int64_t)h * p.o_hs;
-    const bool store_bf16 = p.out_bf16 && !to_ws;
-
-    const int64_t Sq = p.Sq;
-    const int n_v = (int)(kv1 - kv0);                 // keys of this item, >= 1
-    const int nt = (n_v + BN - 1) / BN;
-    const int64_t q_row0 = (int64_t)q_tile * M + wave * (32 * NQ);
-    const unsigned lds0 = (unsigned)(uintptr_t)(LDS_PTR(const void))smem;
+    int tile, part, b, h, q_tile, sub;
+    auto decode = [&](int it) __attribute__((always_inline)) {
+        sub = SUB == 1 ? 0 : it % SUB;
+        it /= SUB;
+        tile = it;
+        part = 0;
+        if (it >= p.n_full) {
+            const int idx = it - p.n_full;
+            part = idx / p.n_cut;
+            tile = p.n_full + (idx - part * p.n_cut);
+        }
+        const int bh = tile / p.tiles_per_head;
+        q_tile = tile - bh * p.tiles_per_head;
+        b = bh / p.Hg;
+        h = bh - b * p.Hg;
+    };
 
     // ---- tile DMA: wavefront w fetches the 1 KB chunks w, w+NW, ... of a tile (4 key rows each).
-    // Lane -> (row, granule to fetch); with this assignment row % 32 does not depend on the chunk
-    // number, so one per-lane offset serves all of a wavefront's chunks.
-    const int ld_row0 = wave * RPC + lane / G;        // row of chunk 0; chunk j adds j*NW*RPC
-    const int ld_gp = lane % G;                       // granule position the lane's data lands on
-    const unsigned ld_offk = (unsigned)(ld_row0 * D * 2 + (ld_gp ^ swz_k<D>(ld_row0)) * 16);
-    const unsigned ld_offv = (unsigned)(ld_row0 * D * 2 + (ld_gp ^ swz_v<D>(ld_row0)) * 16);
-    // chunk j (0..CPW-1) of this wavefront's share of a tile
-    auto issue_chunk = [&](const __bf16* base, unsigned off0, unsigned lds_tile, int tile, int j) {
-        const unsigned dst = lds0 + lds_tile + wave * 1024 + j * (NW * 1024);
-        if ((tile + 1) * BN <= n_v) {                 // whole tile valid: scalar tile base + fixed lane offsets
-            lds_dma16(base + (int64_t)tile * BN * D, off0 + j * (NW * 1024), dst);
-        } else {                                      // tail or beyond: rows clamped to the last valid key
-            const int last_tile = (n_v - 1) / BN;
-            const int tb = tile < last_tile ? tile : last_tile;
-            int row = tile * BN + ld_row0 + j * (NW * RPC);
-            row = row < n_v ? row : n_v - 1;          // hidden / out-of-range keys are never read
-            const unsigned off = (unsigned)(row - tb * BN) * (D * 2) + (off0 & (D * 2 - 1));
-            lds_dma16(base + (int64_t)tb * BN * D, off, dst);
-        }
+    // Lane -> (row, granule to fetch): row j * NW * RPC + wave * RPC + lane / G of chunk j, granule
+    // position lane % G.
+    auto granule_off = [&](int l, int j, bool is_k) __attribute__((always_inline)) {     // byte offset of the lane's granule inside its row
+        const int row = wave * RPC + l / G + j * (NW * RPC);
+        return (unsigned)(((l % G) ^ (is_k ? swz_k<D>(row) : swz_v<D>(row))) * 16);
     };
-    const unsigned dma_base = lds0 + wave * 1024;
-    unsigned ld_k[CPW], ld_v[CPW];
+    const __bf16* kp = nullptr;                       // the item's keys and values: n_v >= 1 of them in nt tiles
+    const __bf16* vp = nullptr;
+    int n_v = 1, nt = 1;
+    unsigned ld_k[CPW], ld_v[CPW];                    // per-lane offsets of the wavefront's chunks
 #pragma unroll
     for (int j = 0; j < CPW; ++j) {
-        ld_k[j] = ld_offk + j * (NW * 1024);
-        ld_v[j] = ld_offv + j * (NW * 1024);
+        const unsigned row_off = (unsigned)(wave * RPC + lane / G + j * (NW * RPC)) * (D * 2);
+        ld_k[j] = row_off + granule_off(lane, j, true);
+        ld_v[j] = row_off + granule_off(lane, j, false);
     }
-    const __bf16* k_dma = kp + 4 * BN * D;            // K tile t+4 and V tile t+2 of the coming iteration
-    const __bf16* v_dma = vp + 2 * BN * D;
-    auto issue_tile = [&](const __bf16* base, unsigned off0, unsigned lds_tile, int tile) {
+    const unsigned dma_base = lds0 + wave * 1024;
+    const __bf16* k_dma = nullptr;                    // K tile t+NBUF and V tile t+NBUF-2 of the coming iteration
+    const __bf16* v_dma = nullptr;
+    // this wavefront's share (chunks 0..CPW-1) of a tile of K or V
+    auto issue_tile = [&](const __bf16* base, bool is_k, unsigned lds_tile, int tile) __attribute__((always_inline)) {
 #pragma unroll
-        for (int j = 0; j < CPW; ++j) issue_chunk(base, off0, lds_tile, tile, j);
+        for (int j = 0; j < CPW; ++j) {
+            const unsigned dst = dma_base + lds_tile + j * (NW * 1024);
+            if ((tile + 1) * BN <= n_v) {             // whole tile valid
+                lds_dma16(base + (int64_t)tile * BN * D, is_k ? ld_k[j] : ld_v[j], dst);
+            } else {                                  // tail or beyond: rows clamped to the last valid key
+                const int l = opaque(lane);
+                const int tb = tile < nt ? tile : nt - 1;
+                int row = tile * BN + wave * RPC + l / G + j * (NW * RPC);
+                row = row < n_v ? row : n_v - 1;      // hidden / out-of-range keys are never read
+                lds_dma16(base + (int64_t)tb * BN * D, (unsigned)(row - tb * BN) * (D * 2) + granule_off(l, j, is_k), dst);
+            }
+        }
+    };
+    // the tiles an item starts with: K 0..NBUF-1 and V 0..NBUF-3 (every wavefront is done with the LDS tiles)
+    auto issue_first_tiles = [&]() __attribute__((always_inline)) {
+        issue_tile(kp, true, K_BASE + 0 * TILE, 0);
+        if constexpr (NBUF == 4) issue_tile(vp, false, V_BASE + 0 * TILE, 0);
+        if (nt > 1) issue_tile(kp, true, K_BASE + 1 * TILE, 1);
+        if constexpr (NBUF == 4) {
+            if (nt > 2) issue_tile(kp, true, K_BASE + 2 * TILE, 2);
+            if (nt > 3) issue_tile(kp, true, K_BASE + 3 * TILE, 3);
+            if (nt > 1) issue_tile(vp, false, V_BASE + 1 * TILE, 1);
+        }
     };
 
     // ---- Q operand fragments, resident for the whole sweep
     bf16x8 qf[NQ][NKK];
+    // Makes `it` the current item: its key range [kv0, kv1) (tile aligned; all keys, or range `part` of a
+    // cut tile), its Q fragments and first K/V tiles on their way.
+    auto begin_item = [&](int it) __attribute__((always_inline)) {
+        decode(it);
+        int64_t kv0 = 0, kv1 = p.n_v;
+        if (p.split > 1 && tile >= p.n_full) {
+            kv0 = p.part_off[part];
+            kv1 = p.part_off[part + 1];
+        }
+        const __bf16* __restrict__ qp = p.q + (int64_t)b * p.q_bs + (int64_t)h * p.q_hs;
+        kp = p.k + (int64_t)b * p.kv_bs + (int64_t)h * p.kv_hs + kv0 * D;
+        vp = p.v + (int64_t)b * p.kv_bs + (int64_t)h * p.kv_hs + kv0 * D;
+        n_v = (int)(kv1 - kv0);
+        nt = (n_v + BN - 1) / BN;
 #pragma unroll
-    for (int nq = 0; nq < NQ; ++nq) {
-        int64_t row = q_row0 + nq * 32 + li;
-        row = row < Sq ? row : Sq - 1;
+        for (int nq = 0; nq < NQ; ++nq) {
+            const int l = opaque(lane);
+            int64_t row = (int64_t)q_tile * kTileRows + sub * M + wave * (32 * NQ) + nq * 32 + (l & 31);
+            row = row < Sq ? row : Sq - 1;
 #pragma unroll
-        for (int kk = 0; kk < NKK; ++kk)
-            qf[nq][kk] = *reinterpret_cast<const bf16x8*>(qp + row * D + kk * 16 + 8 * lh);
-    }
+            for (int kk = 0; kk < NKK; ++kk)
+                qf[nq][kk] = *reinterpret_cast<const bf16x8*>(qp + row * D + kk * 16 + 8 * (l >> 5));
+        }
+        issue_first_tiles();
+    };
 
     // ---- per-lane LDS operand addresses (loop invariant; buffer and block offsets are immediates)
     // K operand: row kb*32+li, granule (2kk+lh) ^ swz_k(li)
@@ -251,19 +259,19 @@ __global__ __launch_bounds__(512 / NQ, 1) void attn_fwd_sp_kernel(const AttnPara
     unsigned p_io[NQ][NKB][2][4];
     const float c = BASE2 ? 1.0f : p.scale_log2e;   // > 0 (the host substitutes a tiny positive value for scale 0)
 
-    auto mask_tail = [&](f32x16 (&s)[NQ][NKB], int t) {
+    auto mask_tail = [&](f32x16 (&s)[NQ][NKB], int t) __attribute__((always_inline)) {
+        const int hidden = n_v - t * BN - 4 * (opaque(lane) >> 5);      // key 4 lh + x is hidden if x >= this
 #pragma unroll
         for (int kb = 0; kb < NKB; ++kb)
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
-                const int key = t * BN + kb * 32 + (r >> 2) * 8 + 4 * lh + (r & 3);
-                if (key >= n_v) {
+                if (kb * 32 + (r >> 2) * 8 + (r & 3) >= hidden) {
 #pragma unroll
                     for (int nq = 0; nq < NQ; ++nq) s[nq][kb][r] = -INFINITY;
                 }
             }
     };
-    auto barrier = [&]() {
+    auto barrier = [&]() __attribute__((always_inline)) {
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
         __builtin_amdgcn_s_barrier();
     };
@@ -272,8 +280,14 @@ __global__ __launch_bounds__(512 / NQ, 1) void attn_fwd_sp_kernel(const AttnPara
     // max of its scores in the first key tile and never moves, so the loop carries no max pass and
     // no rescaling; probabilities may exceed 1.  That is exact as long as nothing overflows, which
     // the caller of the sweep checks on the row sums.  SAFE = true: running max with lazy updates.
-    auto sweep = [&](auto safe_c) {
+    auto sweep = [&](auto safe_c) __attribute__((always_inline)) {
         constexpr bool SAFE = decltype(safe_c)::value;
+        // opaque operand bases: each buffer and block offset stays the immediate of its read instead of
+        // becoming a further address that is carried through the loop
+#pragma unroll
+        for (int kk = 0; kk < NKK; ++kk) asm volatile("" : "+v"(k_ptr[kk]));
+#pragma unroll
+        for (int db = 0; db < NDB; ++db) asm volatile("" : "+v"(v_ptr[db]));
 #pragma unroll
         for (int nq = 0; nq < NQ; ++nq) {
             mc_run[nq] = -INFINITY;
@@ -282,28 +296,10 @@ __global__ __launch_bounds__(512 / NQ, 1) void attn_fwd_sp_kernel(const AttnPara
             for (int db = 0; db < NDB; ++db)
 #pragma unroll
                 for (int r = 0; r < 16; ++r) o_acc[nq][db][r] = 0.f;
-#pragma unroll
-            for (int kb = 0; kb < NKB; ++kb)
-#pragma unroll
-                for (int u = 0; u < 2; ++u)
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) p_io[nq][kb][u][j] = 0u;
         }
-        k_dma = kp + 4 * BN * D;
-        v_dma = vp + 2 * BN * D;
-        // prologue: K tiles 0..3, V tiles 0..1; V buffer 3 (read by the first, all-zero-weight PV) is zeroed
-        issue_tile(kp, ld_offk, K_BASE + 0 * TILE, 0);
-        issue_tile(vp, ld_offv, V_BASE + 0 * TILE, 0);
-        issue_tile(kp, ld_offk, K_BASE + 1 * TILE, 1);
-        issue_tile(kp, ld_offk, K_BASE + 2 * TILE, 2);
-        issue_tile(kp, ld_offk, K_BASE + 3 * TILE, 3);
-        issue_tile(vp, ld_offv, V_BASE + 1 * TILE, 1);
-        {
-            const u32x4 z = {0u, 0u, 0u, 0u};
-            for (int i = tid; i < TILE / 16; i += 64 * NW)
-                *reinterpret_cast<u32x4*>(smem + V_BASE + 3 * TILE + i * 16) = z;
-        }
-        // the Q fragments (loaded before the first sweep, resident for both) and the prologue tiles have arrived
+        k_dma = kp + NBUF * BN * D;
+        v_dma = vp + (NBUF - 2) * BN * D;
+        // the Q fragments (resident for both sweeps) and the item's first tiles have arrived
 #pragma unroll
         for (int nq = 0; nq < NQ; ++nq)
 #pragma unroll
@@ -353,25 +349,28 @@ __global__ __launch_bounds__(512 / NQ, 1) void attn_fwd_sp_kernel(const AttnPara
         // fragment i+PF, and slice i of the softmax VALU work: slices 0-3 the row max, 4-5 the
         // reference / rescale factors, the others the 32 exponentials with their packing to bf16 and
         // the row sum.
-        auto iteration = [&](auto tb_c, int t, f32x16 (&s_c)[NQ][NKB], f32x16 (&s_n)[NQ][NKB]) {
+        //   FIRST: t = 0, no PV yet (its slots hold softmax work only)
+        auto iteration = [&](auto tb_c, auto first_c, int t, f32x16 (&s_c)[NQ][NKB], f32x16 (&s_n)[NQ][NKB]) {
             constexpr int TB = decltype(tb_c)::value;
+            constexpr bool FIRST = decltype(first_c)::value;
             constexpr int KN = (TB + 1) % NBUF;           // buffer of K tile t+1
             constexpr int VP = (TB + 3) % NBUF;           // buffer of V tile t-1
-            // DMA of this iteration: K tile t+4 over K tile t, V tile t+2 over V tile t-2 (both last read
-            // in iteration t-1).  Whole tiles take the short path: running scalar tile pointers, fixed
+            constexpr int KD = TB % NBUF, VD = (TB + NBUF - 2) % NBUF;     // buffers this iteration fills
+            // DMA of this iteration: K tile t+NBUF over K tile t, V tile t+NBUF-2 over V tile t-2 (both last
+            // read in iteration t-1).  Whole tiles take the short path: running scalar tile pointers, fixed
             // per-lane offsets, LDS destinations as immediates.
-            if ((t + 5) * BN <= n_v) {
+            if ((t + NBUF + 1) * BN <= n_v) {
                 static_for<0, CPW>([&](auto jc) {
                     constexpr int j = decltype(jc)::value;
-                    lds_dma16_at<K_BASE + TB * TILE + j * (NW * 1024)>(k_dma, ld_k[j], dma_base);
+                    lds_dma16_at<K_BASE + KD * TILE + j * (NW * 1024)>(k_dma, ld_k[j], dma_base);
                 });
                 static_for<0, CPW>([&](auto jc) {
                     constexpr int j = decltype(jc)::value;
-                    lds_dma16_at<V_BASE + ((TB + 2) % NBUF) * TILE + j * (NW * 1024)>(v_dma, ld_v[j], dma_base);
+                    lds_dma16_at<V_BASE + VD * TILE + j * (NW * 1024)>(v_dma, ld_v[j], dma_base);
                 });
             } else {
-                issue_tile(kp, ld_offk, K_BASE + TB * TILE, t + 4);
-                issue_tile(vp, ld_offv, V_BASE + ((TB + 2) % NBUF) * TILE, t + 2);
+                issue_tile(kp, true, K_BASE + KD * TILE, t + NBUF);
+                issue_tile(vp, false, V_BASE + VD * TILE, t + NBUF - 2);
             }
             k_dma += BN * D;
             v_dma += BN * D;
@@ -382,7 +381,8 @@ __global__ __launch_bounds__(512 / NQ, 1) void attn_fwd_sp_kernel(const AttnPara
 
             auto load_frag = [&](auto idx) {
                 constexpr int i = decltype(idx)::value;
-                if constexpr (i < N_PV) {
+                if constexpr (i < N_PV && FIRST) {
+                } else if constexpr (i < N_PV) {
                     constexpr int kb = i / (2 * NDB), u = (i / NDB) % 2, db = i % NDB;
                     constexpr int off0 = VP * TILE + (kb * 32 + u * 16) * (D * 2);
                     s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LDS_PTR(s16x4))(v_ptr[db] + off0));
@@ -397,7 +397,8 @@ __global__ __launch_bounds__(512 / NQ, 1) void attn_fwd_sp_kernel(const AttnPara
             };
             auto do_mfma = [&](auto idx, auto nq_c) {
                 constexpr int i = decltype(idx)::value, nq = decltype(nq_c)::value;
-                if constexpr (i < N_PV) {
+                if constexpr (i < N_PV && FIRST) {
+                } else if constexpr (i < N_PV) {
                     constexpr int kb = i / (2 * NDB), u = (i / NDB) % 2, db = i % NDB;
                     const u32x4 pv = {p_io[nq][kb][u][0], p_io[nq][kb][u][1], p_io[nq][kb][u][2], p_io[nq][kb][u][3]};
                     o_acc[nq][db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag[i % RING], __builtin_bit_cast(bf16x8, pv),
@@ -498,7 +499,11 @@ __global__ __launch_bounds__(512 / NQ, 1) void attn_fwd_sp_kernel(const AttnPara
             };
 
             // ================= interleaved region: softmax(t) | PV(t-1), QK(t+1) =================
-            static_for<0, PF>([&](auto i) { load_frag(i); });
+            // in this order: grouped by base address instead, the second MFMA would wait for six reads
+            static_for<0, PF>([&](auto i) {
+                load_frag(i);
+                __builtin_amdgcn_sched_barrier(0);
+            });
             static_for<0, N_FR>([&](auto idx) {
                 constexpr int i = decltype(idx)::value;
                 static_for<0, NQ>([&](auto nq_c) { do_mfma(idx, nq_c); });
@@ -530,41 +535,63 @@ __global__ __launch_bounds__(512 / NQ, 1) void attn_fwd_sp_kernel(const AttnPara
             }
             if ((t + 2) * BN > n_v) mask_tail(s_n, t + 1);     // S_{t+1} holds hidden keys
 
-            if constexpr (NQ == 2) {
-                // One wavefront per SIMD owns 512 registers, half of them accumulation registers that
-                // only MFMAs (and loads) can address.  Pin what only MFMAs touch there - the O
-                // accumulators and the Q fragments - so that the VALU-visible half is left for the scores.
-#pragma unroll
-                for (int nq = 0; nq < NQ; ++nq) {
-#pragma unroll
-                    for (int db = 0; db < NDB; ++db) asm volatile("" : "+a"(o_acc[nq][db]));
-#pragma unroll
-                    for (int kk = 0; kk < NKK; ++kk) asm volatile("" : "+a"(qf[nq][kk]));
-                }
-            }
-            // Of the DMA batches in flight, all but the two newest (this iteration's, issued at its top,
-            // and the previous one's) must have landed: K tile t+2 and V tile t, which iteration t+1 reads.
-            wait_vmcnt<4 * CPW>();
+            // Iteration t+1 reads K tile t+2 and V tile t.  With four buffers, what this iteration and the
+            // previous one issued may still be in flight; with two, this iteration issued just those two tiles.
+            wait_vmcnt<NBUF == 4 ? 4 * CPW : 0>();
             barrier();
         };
 
-        // The loop runs over tiles 0 .. nt (the extra one only completes PV(nt-1): its scores are all
-        // hidden, so its probabilities are zero), unrolled by four so that buffer offsets are
-        // immediates and the score / probability registers alternate roles without copies.
-        // (the loop is left right after iteration nt, wherever in the group of four that falls)
-        for (int t = 0; t <= nt; t += 4) {
-            iteration(std::integral_constant<int, 0>{}, t, s_a, s_b);
-            if (t == nt) break;
-            iteration(std::integral_constant<int, 1>{}, t + 1, s_b, s_a);
+        // Tiles 0 .. nt-1, unrolled by four so that buffer offsets are immediates and the score /
+        // probability registers alternate roles without copies; the first is peeled off (no PV yet) and
+        // the loop is left right after the last, wherever in the group of four that falls.
+        using no = std::false_type;
+        auto pin_o = [&]() {       // keeps the zeroed accumulators in registers (a constant would be copied at every exit)
+#pragma unroll
+            for (int nq = 0; nq < NQ; ++nq)
+#pragma unroll
+                for (int db = 0; db < NDB; ++db) asm volatile("" : "+v"(o_acc[nq][db]));
+        };
+        pin_o();
+        iteration(std::integral_constant<int, 0>{}, std::true_type{}, 0, s_a, s_b);
+        pin_o();
+        for (int t = 1; t < nt; t += 4) {
+            iteration(std::integral_constant<int, 1>{}, no{}, t, s_b, s_a);
             if (t + 1 == nt) break;
-            iteration(std::integral_constant<int, 2>{}, t + 2, s_a, s_b);
+            iteration(std::integral_constant<int, 2>{}, no{}, t + 1, s_a, s_b);
             if (t + 2 == nt) break;
-            iteration(std::integral_constant<int, 3>{}, t + 3, s_b, s_a);
+            iteration(std::integral_constant<int, 3>{}, no{}, t + 2, s_b, s_a);
+            if (t + 3 == nt) break;
+            iteration(std::integral_constant<int, 0>{}, no{}, t + 3, s_a, s_b);
         }
-        wait_vmcnt<0>();        // no DMA may outlive the workgroup's LDS
+        // PV(nt-1): no scores are left to compute or to exponentiate
+        {
+            const int voff = ((nt - 1) % NBUF) * TILE;
+#pragma unroll
+            for (int i = 0; i < NKB * 2 * NDB; ++i) {
+                const int kb = i / (2 * NDB), u = (i / NDB) % 2, db = i % NDB;
+                LDS_PTR(const unsigned char) a = v_ptr[db] + voff + (kb * 32 + u * 16) * (D * 2);
+                const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LDS_PTR(s16x4))a);
+                const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LDS_PTR(s16x4))(a + 8 * (D * 2)));
+                const bf16x8 av = __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+#pragma unroll
+                for (int nq = 0; nq < NQ; ++nq) {
+                    const u32x4 pv = {p_io[nq][kb][u][0], p_io[nq][kb][u][1], p_io[nq][kb][u][2], p_io[nq][kb][u][3]};
+                    o_acc[nq][db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av, __builtin_bit_cast(bf16x8, pv), o_acc[nq][db], 0, 0, 0);
+                }
+            }
+        }
+        wait_vmcnt<0>();        // no DMA may land in the tiles of the next item or outlive the workgroup's LDS
     };
+
+    if (item < p.n_items) begin_item(item);
+    while (item < p.n_items) {
+    // The next item is claimed as late as possible (the order of the items balances the end of the
+    // launch), but its Q and first tiles travel while this item's results are stored.
     sweep(std::false_type{});
+    int next = p.n_items;
     {
+        int claimed = p.n_items;
+        if (!direct && tid == 0) claimed = (int)gridDim.x + atomicAdd(p.counter, 1);
         // A row whose sum left the safe range (a later score exceeded the first tile's max by more
         // than ~2^64, or non-finite input) or whose accumulators are not finite makes the whole
         // workgroup redo the item with the running max (weights <= 2^8 there).
@@ -582,22 +609,47 @@ __global__ __launch_bounds__(512 / NQ, 1) void attn_fwd_sp_kernel(const AttnPara
             bad |= !(t == 0.f);
         }
         const bool wave_bad = __builtin_amdgcn_ballot_w64(bad) != 0;
-        barrier();                                   // every wavefront is done with the LDS tiles and its DMA
-        LDS_PTR(volatile int) flags = (LDS_PTR(volatile int))smem;
-        if (lane == 0) flags[wave] = wave_bad ? 1 : 0;
-        barrier();
+        if (lane == 0) redo_flag[wave] = wave_bad ? 1 : 0;
+        if (tid == 0) next_item = claimed;
+        barrier();                                   // flags are written, and every wavefront is done with the LDS tiles
         int any = 0;
 #pragma unroll
-        for (int w = 0; w < NW; ++w) any |= flags[w];
-        barrier();                                   // flags are read before the redo's DMA reuses their bytes
-        if (__builtin_amdgcn_readfirstlane(any)) sweep(std::true_type{});
+        for (int w = 0; w < NW; ++w) any |= redo_flag[w];
+        next = __builtin_amdgcn_readfirstlane(next_item);
+        if (__builtin_amdgcn_readfirstlane(any)) {
+            issue_first_tiles();
+            sweep(std::true_type{});
+            barrier();                               // as above, before the next item's tiles are fetched
+        }
     }
 
-    // ---- epilogue: normalise, write out and lse.  The lane's row is formed from a copy of its index
-    // that the compiler cannot trace back, or it would form the store addresses before the sweep and
-    // carry them through it in registers the loop has no room for.
-    int li_e = li;
-    asm volatile("" : "+v"(li_e));
+    // ---- where this item's results go: part 0 writes the tile's rows of out/lse; later parts write
+    // rows 0..255 of their partial slot.  With a bf16 `out` the merge pass needs fp32 partials of ALL
+    // parts of a cut tile, part 0 included.
+    decode(item);
+    const bool cut = p.split > 1 && tile >= p.n_full;
+    const bool to_ws = part > 0 || (cut && p.out_bf16);
+    const bool store_bf16 = p.out_bf16 && !to_ws;
+    float* __restrict__ op;
+    float* __restrict__ lp;
+    int64_t row_sub;                                   // subtracted from the global row on store
+    if (!to_ws) {
+        op = p.out + (p.out_bf16 ? 0 : (int64_t)b * p.o_bs + (int64_t)h * p.o_hs);
+        lp = p.lse + (int64_t)b * p.l_bs + (int64_t)h * p.l_hs;
+        row_sub = 0;
+    } else {
+        const int64_t slot = p.out_bf16 ? (int64_t)(tile - p.n_full) * p.split + part
+                                        : (int64_t)(tile - p.n_full) * (p.split - 1) + (part - 1);
+        op = p.part_out + slot * (kTileRows * D);
+        lp = p.part_lse + slot * kTileRows;
+        row_sub = (int64_t)q_tile * kTileRows;
+    }
+    __bf16* __restrict__ oph = reinterpret_cast<__bf16*>(p.out) + (int64_t)b * p.o_bs + (int64_t)h * p.o_hs;
+    const int64_t q_row0 = (int64_t)q_tile * kTileRows + sub * M + wave * (32 * NQ);
+    if (next < p.n_items) begin_item(next);
+
+    // ---- epilogue: normalise, write out and lse
+    const int lane_e = opaque(lane), li_e = lane_e & 31, lh_e = lane_e >> 5;
 #pragma unroll
     for (int nq = 0; nq < NQ; ++nq) {
         const float l_tot = pair_sum(l_run[nq]);
@@ -612,14 +664,15 @@ __global__ __launch_bounds__(512 / NQ, 1) void attn_fwd_sp_kernel(const AttnPara
                                 o_acc[nq][db][4 * a + 2] * inv, o_acc[nq][db][4 * a + 3] * inv};
                     if (store_bf16) {
                         const u32x2 h2 = {pack_bf16(o4[0], o4[1]), pack_bf16(o4[2], o4[3])};
-                        *reinterpret_cast<u32x2*>(oph + row * D + db * 32 + a * 8 + 4 * lh) = h2;
+                        *reinterpret_cast<u32x2*>(oph + row * D + db * 32 + a * 8 + 4 * lh_e) = h2;
                     } else {
-                        *reinterpret_cast<f32x4*>(op + (row - row_sub) * D + db * 32 + a * 8 + 4 * lh) = o4;
+                        *reinterpret_cast<f32x4*>(op + (row - row_sub) * D + db * 32 + a * 8 + 4 * lh_e) = o4;
                     }
                 }
-            if (lh == 0) lp[row - row_sub] = mc_run[nq] * 0.6931471805599453f + __logf(l_tot);
+            if (lh_e == 0) lp[row - row_sub] = mc_run[nq] * 0.6931471805599453f + __logf(l_tot);
         }
     }
+    item = next;
     }   // next work item
 
     // The last workgroup to leave puts both counters back to zero for the next launch that uses this
@@ -686,15 +739,29 @@ __global__ __launch_bounds__(256) void tail_merge_kernel(const AttnParams p, int
     if (c4 == 0) *lp = m + __logf(tot);
 }
 
-template <int D, int NQ, bool BASE2>
-static hipError_t launch_sp(AttnParams p, int BH, float* ws, int64_t ws_slots, hipStream_t st) {
-    constexpr int smem = 2 * 4 * 64 * D * 2;        // 128 KB (d = 128) or 64 KB
-    constexpr int M = 256;
-    auto kern = attn_fwd_sp_kernel<D, NQ, BASE2>;
+// Launches the items of `p` (already planned) as workgroups of NW wavefronts.
+template <int D, int NW, bool BASE2>
+static hipError_t launch_items(AttnParams p, int64_t items, int n_cu, hipStream_t st) {
+    auto kern = attn_fwd_sp_kernel<D, NW, BASE2>;
+    constexpr int smem = 2 * sp_buffers(D, NW) * 64 * D * 2;       // 128 KB (d = 128, 8 wavefronts) or 64 KB
+    constexpr int alone = 96 * 1024;                               // keeps a second workgroup off the CU
     static KernelSetup setup;
+    hipError_t e = setup.ensure(reinterpret_cast<const void*>(kern), smem > alone ? smem : alone, nullptr);
+    if (e != hipSuccess) return e;
+    items *= kTileRows / (32 * NW);
+    p.n_items = (int)items;
+    // two workgroups of four wavefronts share a CU, unless there are not enough of them to fill every CU
+    const int64_t slots = (int64_t)n_cu * (NW == 8 ? 1 : 2);
+    const int lds = NW < 8 && items <= n_cu ? alone : smem;
+    hipLaunchKernelGGL(kern, dim3((unsigned)(items < slots ? items : slots)), dim3(64 * NW), lds, st, p);
+    return hipGetLastError();
+}
+
+template <int D, bool BASE2>
+static hipError_t launch_sp(AttnParams p, int BH, float* ws, int64_t ws_slots, hipStream_t st) {
     int n_cu = 0;
     {
-        hipError_t e = setup.ensure(reinterpret_cast<const void*>(kern), smem, &n_cu);
+        hipError_t e = device_cu_count(&n_cu);
         if (e != hipSuccess) return e;
     }
     const TailPlan t = plan_tail(p.Sq, BH, p.n_v, n_cu);
@@ -712,22 +779,38 @@ static hipError_t launch_sp(AttnParams p, int BH, float* ws, int64_t ws_slots, h
     p.n_full = (int)(t.n_tiles - t.n_cut);
     for (int j = 0; j <= kMaxSplit; ++j) p.part_off[j] = t.part_off[j];
     p.part_out = slots ? ws : nullptr;
-    p.part_lse = slots ? ws + slots * (M * D) : nullptr;
+    p.part_lse = slots ? ws + slots * (kTileRows * D) : nullptr;
     p.counter = reinterpret_cast<int*>(ws + ws_slots * kSlotFloats);     // two ints behind the slots, zero between launches
     const int64_t items = p.n_full + t.n_cut * t.split;
-    p.n_items = (int)items;
-    const unsigned grid = (unsigned)(items < n_cu ? items : n_cu);
-    hipLaunchKernelGGL(kern, dim3(grid), dim3(512 / NQ), smem, st, p);
-    hipError_t e = hipGetLastError();
+    // Workgroup size (the results are the same bits).  Four wavefronts, 128 rows:
+    //  * where even the halves of the items do not fill every CU: twice the CUs work on the launch, one
+    //    wavefront per SIMD (one head x 2 048 tokens, d = 128: 25.9 -> 19.4 us with the merge; 2 x 1 024,
+    //    d = 64: 18.5 -> 14.6; 1 x 4 096: 33.7 -> 27.3);
+    //  * for short sweeps in many rounds: two workgroups share a CU and one computes while the other
+    //    loads or stores (24 x 16 384 queries on 600 keys: 187 -> 180 us, on 1 500 keys: 323 -> 319).
+    // Eight wavefronts, 256 rows, elsewhere: a K/V tile in LDS serves twice the rows, half the
+    // global -> LDS traffic (3 heads x 67 576: 5.53 ms against 6.12; 10 x 9 600: 0.419 against 0.471).
+    const int64_t key_tiles = (p.n_v + 63) / 64;
+    const bool four = 2 * items <= n_cu || (items >= 4 * (int64_t)n_cu && key_tiles <= 24);
+    hipError_t e = four ? launch_items<D, 4, BASE2>(p, items, n_cu, st) : launch_items<D, 8, BASE2>(p, items, n_cu, st);
     if (e != hipSuccess || t.split <= 1) return e;
-    hipLaunchKernelGGL(tail_merge_kernel<D>, dim3((unsigned)(t.n_cut * (M / (1024 / D)))), dim3(256), 0, st, p, (int)t.n_cut);
+    hipLaunchKernelGGL(tail_merge_kernel<D>, dim3((unsigned)(t.n_cut * (kTileRows / (1024 / D)))), dim3(256), 0, st, p, (int)t.n_cut);
     return hipGetLastError();
 }
 
+// Head dimension 64 is compiled by attn_fwd_sp_d64.hip, which includes this file with
+// PDA_SP_HEAD_DIM 64: the two sets of kernels then build side by side.
+#ifndef PDA_SP_HEAD_DIM
+hipError_t launch_attn_fwd_sp_d64(const AttnParams& p, int BH, float* ws, int64_t ws_slots, hipStream_t st);
+
 hipError_t launch_attn_fwd_sp(const AttnParams& p, int BH, int D, float* ws, int64_t ws_slots, hipStream_t st) {
-    if (D == 64)
-        return p.base2 ? launch_sp<64, 1, true>(p, BH, ws, ws_slots, st) : launch_sp<64, 1, false>(p, BH, ws, ws_slots, st);
-    return p.base2 ? launch_sp<128, 1, true>(p, BH, ws, ws_slots, st) : launch_sp<128, 1, false>(p, BH, ws, ws_slots, st);
+    if (D == 64) return launch_attn_fwd_sp_d64(p, BH, ws, ws_slots, st);
+    return p.base2 ? launch_sp<128, true>(p, BH, ws, ws_slots, st) : launch_sp<128, false>(p, BH, ws, ws_slots, st);
 }
+#else
+hipError_t launch_attn_fwd_sp_d64(const AttnParams& p, int BH, float* ws, int64_t ws_slots, hipStream_t st) {
+    return p.base2 ? launch_sp<64, true>(p, BH, ws, ws_slots, st) : launch_sp<64, false>(p, BH, ws, ws_slots, st);
+}
+#endif
 
 }  // namespace pda

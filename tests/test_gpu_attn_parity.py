@@ -422,3 +422,39 @@ def test_key_axis_beyond_2_gib():
     ro, rl = merge_partials([p[0] for p in parts], [p[1] for p in parts])
     assert rl[1] > rl[0] + 1 and rl[2] > rl[0] + 1            # the planted keys near the end carry weight
     assert_close(o[0, 0], l[0, 0], ro, rl, "K larger than 2 GiB")
+
+
+@pytest.mark.parametrize("d", [128, 64])
+@pytest.mark.parametrize("n_v", [1, 63, 64, 65, 128, 191, 256, 300, 321, 449])
+def test_workgroup_sizes_and_item_chain(d, n_v):
+    """One head alone (fewer items than CUs), many heads (at least four rounds of items, each workgroup
+    taking several one after the other) and, for d = 128, a launch of one to two items per CU: the three
+    launch forms run different workgroup sizes and must give the same bits, and those must be right.
+    Key counts from one key to seven and a bit tiles: every exit of the unrolled loop, tails included."""
+    import torch
+    import paper_2511_12056_amd as pda
+    H, Sq = 520, 300                       # 1 040 tiles of 256 rows; no tile of any of the launches is cut (n_v < 1 024)
+    q, k, v = gen_qkv(31 + n_v, 1, H, Sq, n_v, d, unit_rms=True)
+    dq, dk, dv = to_dev_bf16(q), to_dev_bf16(k), to_dev_bf16(v)
+
+    def run(heads, variant=None):
+        out = torch.full((1, heads, Sq, d), float("nan"), device="cuda")
+        lse = torch.full((1, heads, Sq), float("nan"), device="cuda")
+        a = [t[:, :heads].contiguous() for t in (dq, dk, dv)]
+        if variant is None:
+            pda.attn_fwd(*a, out, lse, d ** -0.5)
+        else:
+            pda.attn_fwd_variant(*a, out, lse, d ** -0.5, variant=variant)
+        torch.cuda.synchronize()
+        return out, lse
+
+    out, lse = run(H)
+    for heads in (1, 200):
+        o, l = run(heads)
+        assert torch.equal(o, out[:, :heads]) and torch.equal(l, lse[:, :heads]), heads
+    redo, redo_lse = run(H, variant=3)     # every item swept a second time with the running max
+    pick = [0, 1, 255, H - 1]
+    ro, rl = _oracle(q[:, pick], k[:, pick], v[:, pick], d ** -0.5)
+    for o, l in ((out, lse), (redo, redo_lse)):
+        assert torch.isfinite(o).all() and torch.isfinite(l).all()
+        assert_close(o[:, pick].cpu().numpy(), l[:, pick].cpu().numpy(), ro, rl, f"d={d} n_v={n_v}")
