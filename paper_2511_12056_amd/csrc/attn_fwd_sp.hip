@@ -508,6 +508,7 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_fwd_sp_kernel(const AttnParam
                 constexpr int i = decltype(idx)::value;
                 static_for<0, NQ>([&](auto nq_c) { do_mfma(idx, nq_c); });
                 load_frag(std::integral_constant<int, i + PF>{});
+                __builtin_amdgcn_sched_barrier(0);       // the reads go first: they are on the path of slot i + PF
                 static_for<0, NQ>([&](auto nq_c) { valu_slice(idx, nq_c); });
                 __builtin_amdgcn_sched_barrier(0);
             });
