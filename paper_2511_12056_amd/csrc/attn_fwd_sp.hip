@@ -60,20 +60,24 @@ constexpr int sp_buffers(int d, int n_waves) { return d == 128 && n_waves < 8 ? 
 // tell apart from the operand reads that follow (it would drain the whole prefetch before every
 // LDS read); completion is tracked by hand with s_waitcnt vmcnt before the barrier.
 // M0 is not restored; it is declared clobbered.
+// The compiler does not see into the assembly, so the wait states it would insert are up to us: one
+// between the write of M0 and the load, and five between a VALU write of the base registers (the
+// v_readlane that restores a spilled pointer) and the load.  Copying the base through VCC is both: an
+// instruction in between, and a scalar write, which the hardware interlocks.
 __device__ __forceinline__ void lds_dma16(const void* sbase, unsigned voff, unsigned lds_addr) {
-    asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2"
+    asm volatile("s_mov_b32 m0, %0\n\ts_mov_b64 vcc, %2\n\tglobal_load_lds_dwordx4 %1, vcc"
                  :
                  : "s"(lds_addr), "v"(voff), "s"(sbase)
-                 : "memory", "m0");
+                 : "memory", "m0", "vcc");
 }
 
 // Same with the LDS address given as wave-uniform base + compile-time offset.
 template <int LDS_OFF>
 __device__ __forceinline__ void lds_dma16_at(const void* sbase, unsigned voff, unsigned lds_base) {
-    asm volatile("s_add_u32 m0, %0, %1\n\tglobal_load_lds_dwordx4 %2, %3"
+    asm volatile("s_add_u32 m0, %0, %1\n\ts_mov_b64 vcc, %3\n\tglobal_load_lds_dwordx4 %2, vcc"
                  :
                  : "s"(lds_base), "n"(LDS_OFF), "v"(voff), "s"(sbase)
-                 : "memory", "scc", "m0");
+                 : "memory", "scc", "m0", "vcc");
 }
 
 template <int N>
