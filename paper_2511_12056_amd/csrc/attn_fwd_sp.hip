@@ -25,7 +25,8 @@
 // first tile, or the input held non-finite values), or an output accumulator is not finite (large
 // weights times large V entries), the workgroup sweeps the item again with the
 // usual running max, where the reference moves only when the max grew by more than 2^8 and O is
-// rescaled after the stream in a rare wave-uniform branch.  The row sum is taken with plain fp32
+// rescaled after the stream in a rare wave-uniform branch; the rows in question take their result
+// from that sweep, the others keep theirs.  The row sum is taken with plain fp32
 // adds on the unrounded probabilities; the dot-product instructions (v_dot2c_f32_bf16), which
 // would sum two rounded ones at a time, occupy the matrix pipe and stall the MFMA stream.
 //
@@ -588,19 +589,76 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_fwd_sp_kernel(const AttnParam
         wait_vmcnt<0>();        // no DMA may land in the tiles of the next item or outlive the workgroup's LDS
     };
 
+    // ---- where the results of `item` go: part 0 writes the tile's rows of out/lse; later parts write
+    // rows 0..255 of their partial slot.  With a bf16 `out` the merge pass needs fp32 partials of ALL
+    // parts of a cut tile, part 0 included.
+    float* op;
+    float* lp;
+    __bf16* oph;
+    int64_t row_sub, q_row0;                           // row_sub: subtracted from the global row on store
+    bool store_bf16;
+    auto locate = [&]() __attribute__((always_inline)) {
+        decode(item);
+        const bool cut = p.split > 1 && tile >= p.n_full;
+        const bool to_ws = part > 0 || (cut && p.out_bf16);
+        store_bf16 = p.out_bf16 && !to_ws;
+        if (!to_ws) {
+            op = p.out + (p.out_bf16 ? 0 : (int64_t)b * p.o_bs + (int64_t)h * p.o_hs);
+            lp = p.lse + (int64_t)b * p.l_bs + (int64_t)h * p.l_hs;
+            row_sub = 0;
+        } else {
+            const int64_t slot = p.out_bf16 ? (int64_t)(tile - p.n_full) * p.split + part
+                                            : (int64_t)(tile - p.n_full) * (p.split - 1) + (part - 1);
+            op = p.part_out + slot * (kTileRows * D);
+            lp = p.part_lse + slot * kTileRows;
+            row_sub = (int64_t)q_tile * kTileRows;
+        }
+        oph = reinterpret_cast<__bf16*>(p.out) + (int64_t)b * p.o_bs + (int64_t)h * p.o_hs;
+        q_row0 = (int64_t)q_tile * kTileRows + sub * M + wave * (32 * NQ);
+    };
+    // ---- epilogue: normalise, write out and lse (the lanes of `mask`)
+    auto store_results = [&](uint64_t mask) __attribute__((always_inline)) {
+        const int lane_e = opaque(lane), li_e = lane_e & 31, lh_e = lane_e >> 5;
+#pragma unroll
+        for (int nq = 0; nq < NQ; ++nq) {
+            const float l_tot = pair_sum(l_run[nq]);
+            const float inv = 1.0f / l_tot;
+            const int64_t row = q_row0 + nq * 32 + li_e;
+            if (row < Sq && (mask >> lane_e & 1)) {
+#pragma unroll
+                for (int db = 0; db < NDB; ++db)
+#pragma unroll
+                    for (int a = 0; a < 4; ++a) {
+                        f32x4 o4 = {o_acc[nq][db][4 * a] * inv, o_acc[nq][db][4 * a + 1] * inv,
+                                    o_acc[nq][db][4 * a + 2] * inv, o_acc[nq][db][4 * a + 3] * inv};
+                        if (store_bf16) {
+                            const u32x2 h2 = {pack_bf16(o4[0], o4[1]), pack_bf16(o4[2], o4[3])};
+                            *reinterpret_cast<u32x2*>(oph + row * D + db * 32 + a * 8 + 4 * lh_e) = h2;
+                        } else {
+                            *reinterpret_cast<f32x4*>(op + (row - row_sub) * D + db * 32 + a * 8 + 4 * lh_e) = o4;
+                        }
+                    }
+                if (lh_e == 0) lp[row - row_sub] = mc_run[nq] * 0.6931471805599453f + __logf(l_tot);
+            }
+        }
+    };
+
     if (item < p.n_items) begin_item(item);
     while (item < p.n_items) {
     // The next item is claimed as late as possible (the order of the items balances the end of the
     // launch), but its Q and first tiles travel while this item's results are stored.
     sweep(std::false_type{});
     int next = p.n_items;
+    uint64_t store_mask = ~0ull;                      // lanes whose results are still to be stored
     {
         int claimed = p.n_items;
         if (!direct && tid == 0) claimed = (int)gridDim.x + atomicAdd(p.counter, 1);
         // A row whose sum left the safe range (a later score exceeded the first tile's max by more
-        // than ~2^64, or non-finite input) or whose accumulators are not finite makes the whole
-        // workgroup redo the item with the running max (weights <= 2^8 there).
-        bool bad = p.redo_always != 0;               // test switch: every item takes the second sweep
+        // than ~2^64, or non-finite input) or whose accumulators are not finite takes its result from a
+        // second sweep with the running max (weights <= 2^8 there).  The workgroup sweeps together, but
+        // the other rows keep the result of the first sweep: what a row gets depends on that row alone,
+        // not on the rows that happen to share its workgroup, whose number depends on the launch.
+        bool bad = p.redo_always != 0;               // test switch: every row takes the second sweep
 #pragma unroll
         for (int nq = 0; nq < NQ; ++nq) {
             bad |= !(pair_sum(l_run[nq]) < 1.8446744e19f);
@@ -613,8 +671,9 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_fwd_sp_kernel(const AttnParam
                 for (int r = 0; r < 16; ++r) t = __builtin_fmaf(o_acc[nq][db][r], 0.0f, t);
             bad |= !(t == 0.f);
         }
-        const bool wave_bad = __builtin_amdgcn_ballot_w64(bad) != 0;
-        if (lane == 0) redo_flag[wave] = wave_bad ? 1 : 0;
+        uint64_t redo = __builtin_amdgcn_ballot_w64(bad);
+        redo |= redo << 32 | redo >> 32;             // lanes l and l + 32 hold one row
+        if (lane == 0) redo_flag[wave] = redo != 0 ? 1 : 0;
         if (tid == 0) next_item = claimed;
         barrier();                                   // flags are written, and every wavefront is done with the LDS tiles
         int any = 0;
@@ -622,61 +681,17 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_fwd_sp_kernel(const AttnParam
         for (int w = 0; w < NW; ++w) any |= redo_flag[w];
         next = __builtin_amdgcn_readfirstlane(next_item);
         if (__builtin_amdgcn_readfirstlane(any)) {
+            locate();
+            store_results(~redo);
+            store_mask = redo;
             issue_first_tiles();
             sweep(std::true_type{});
             barrier();                               // as above, before the next item's tiles are fetched
         }
     }
-
-    // ---- where this item's results go: part 0 writes the tile's rows of out/lse; later parts write
-    // rows 0..255 of their partial slot.  With a bf16 `out` the merge pass needs fp32 partials of ALL
-    // parts of a cut tile, part 0 included.
-    decode(item);
-    const bool cut = p.split > 1 && tile >= p.n_full;
-    const bool to_ws = part > 0 || (cut && p.out_bf16);
-    const bool store_bf16 = p.out_bf16 && !to_ws;
-    float* __restrict__ op;
-    float* __restrict__ lp;
-    int64_t row_sub;                                   // subtracted from the global row on store
-    if (!to_ws) {
-        op = p.out + (p.out_bf16 ? 0 : (int64_t)b * p.o_bs + (int64_t)h * p.o_hs);
-        lp = p.lse + (int64_t)b * p.l_bs + (int64_t)h * p.l_hs;
-        row_sub = 0;
-    } else {
-        const int64_t slot = p.out_bf16 ? (int64_t)(tile - p.n_full) * p.split + part
-                                        : (int64_t)(tile - p.n_full) * (p.split - 1) + (part - 1);
-        op = p.part_out + slot * (kTileRows * D);
-        lp = p.part_lse + slot * kTileRows;
-        row_sub = (int64_t)q_tile * kTileRows;
-    }
-    __bf16* __restrict__ oph = reinterpret_cast<__bf16*>(p.out) + (int64_t)b * p.o_bs + (int64_t)h * p.o_hs;
-    const int64_t q_row0 = (int64_t)q_tile * kTileRows + sub * M + wave * (32 * NQ);
+    locate();
     if (next < p.n_items) begin_item(next);
-
-    // ---- epilogue: normalise, write out and lse
-    const int lane_e = opaque(lane), li_e = lane_e & 31, lh_e = lane_e >> 5;
-#pragma unroll
-    for (int nq = 0; nq < NQ; ++nq) {
-        const float l_tot = pair_sum(l_run[nq]);
-        const float inv = 1.0f / l_tot;
-        const int64_t row = q_row0 + nq * 32 + li_e;
-        if (row < Sq) {
-#pragma unroll
-            for (int db = 0; db < NDB; ++db)
-#pragma unroll
-                for (int a = 0; a < 4; ++a) {
-                    f32x4 o4 = {o_acc[nq][db][4 * a] * inv, o_acc[nq][db][4 * a + 1] * inv,
-                                o_acc[nq][db][4 * a + 2] * inv, o_acc[nq][db][4 * a + 3] * inv};
-                    if (store_bf16) {
-                        const u32x2 h2 = {pack_bf16(o4[0], o4[1]), pack_bf16(o4[2], o4[3])};
-                        *reinterpret_cast<u32x2*>(oph + row * D + db * 32 + a * 8 + 4 * lh_e) = h2;
-                    } else {
-                        *reinterpret_cast<f32x4*>(op + (row - row_sub) * D + db * 32 + a * 8 + 4 * lh_e) = o4;
-                    }
-                }
-            if (lh_e == 0) lp[row - row_sub] = mc_run[nq] * 0.6931471805599453f + __logf(l_tot);
-        }
-    }
+    store_results(store_mask);
     item = next;
     }   // next work item
 

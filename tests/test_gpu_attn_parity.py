@@ -458,3 +458,41 @@ def test_workgroup_sizes_and_item_chain(d, n_v):
     for o, l in ((out, lse), (redo, redo_lse)):
         assert torch.isfinite(o).all() and torch.isfinite(l).all()
         assert_close(o[:, pick].cpu().numpy(), l[:, pick].cpu().numpy(), ro, rl, f"d={d} n_v={n_v}")
+
+
+@pytest.mark.parametrize("d", [128, 64])
+def test_second_sweep_takes_the_same_rows_in_every_launch_form(d):
+    """A row takes the running-max sweep by its own scores alone, so a launch of one head, of 200 heads
+    (eight wavefronts per workgroup on 256 CUs) and of 520 (four, each workgroup several items) give the
+    same bits on every row of a tile in which one row, in its first or second half, needs that sweep."""
+    import torch
+    import paper_2511_12056_amd as pda
+    from oracle import attention
+    H, Sq, n_v = 520, 300, 700
+    rng = np.random.default_rng(606)
+    q = rng.standard_normal((1, H, Sq, d)).astype(np.float32)
+    k = (rng.standard_normal((1, H, n_v, d)) * 0.3).astype(np.float32)
+    v = rng.standard_normal((1, H, n_v, d)).astype(np.float32)
+    row = {0: 5, 1: 127, 2: 128, 3: 250, 4: 255, 5: 280}       # head -> outlier row (heads 6 to 9: none)
+    for h in range(H):
+        if h % 10 in row:
+            r = row[h % 10]
+            k[0, h, 400 + h % 200] = q[0, h, r] * np.float32(1.5 * 128 / d)     # > 100 natural-log units over the first tile
+    qb, kb, vb = (f32_to_bf16_bits(x) for x in (q, k, v))
+    dq, dk, dv = to_dev_bf16(qb), to_dev_bf16(kb), to_dev_bf16(vb)
+
+    def run(a, b):
+        out = torch.full((1, b - a, Sq, d), float("nan"), device="cuda")
+        lse = torch.full((1, b - a, Sq), float("nan"), device="cuda")
+        pda.attn_fwd(*(t[:, a:b].contiguous() for t in (dq, dk, dv)), out, lse, 1.0)
+        torch.cuda.synchronize()
+        return out, lse
+
+    out, lse = run(0, H)
+    s0 = np.einsum("hd,hkd->hk", q[0, :6][np.arange(6), [row[h] for h in range(6)]], k[0, :6])
+    assert (s0[:, 64:].max(1) - s0[:, :64].max(1) > 64 * np.log(2)).all()       # the inputs do what they are meant to
+    ro, rl = attention(qb[:, :10], kb[:, :10], vb[:, :10], 1.0)
+    assert_close(out[:, :10].cpu().numpy(), lse[:, :10].cpu().numpy(), ro, rl, f"outlier rows, d={d}")
+    for a, b in [(0, 200), (200, 400), (320, 520)] + [(h, h + 1) for h in range(8)]:
+        o, l = run(a, b)
+        assert torch.equal(o, out[:, a:b]) and torch.equal(l, lse[:, a:b]), (a, b)
