@@ -592,9 +592,9 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_fwd_sp_kernel(const AttnParam
     // ---- where the results of `item` go: part 0 writes the tile's rows of out/lse; later parts write
     // rows 0..255 of their partial slot.  With a bf16 `out` the merge pass needs fp32 partials of ALL
     // parts of a cut tile, part 0 included.
-    float* op;
-    float* lp;
-    __bf16* oph;
+    float* __restrict__ op;
+    float* __restrict__ lp;
+    __bf16* __restrict__ oph;
     int64_t row_sub, q_row0;                           // row_sub: subtracted from the global row on store
     bool store_bf16;
     auto locate = [&]() __attribute__((always_inline)) {
@@ -624,7 +624,7 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_fwd_sp_kernel(const AttnParam
             const float l_tot = pair_sum(l_run[nq]);
             const float inv = 1.0f / l_tot;
             const int64_t row = q_row0 + nq * 32 + li_e;
-            if (row < Sq && (mask >> lane_e & 1)) {
+            if (row < Sq && __builtin_amdgcn_inverse_ballot_w64(mask)) {
 #pragma unroll
                 for (int db = 0; db < NDB; ++db)
 #pragma unroll
@@ -680,7 +680,7 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_fwd_sp_kernel(const AttnParam
 #pragma unroll
         for (int w = 0; w < NW; ++w) any |= redo_flag[w];
         next = __builtin_amdgcn_readfirstlane(next_item);
-        if (__builtin_amdgcn_readfirstlane(any)) {
+        if (__builtin_expect(__builtin_amdgcn_readfirstlane(any), 0)) {
             locate();
             store_results(~redo);
             store_mask = redo;
