@@ -802,16 +802,7 @@ static hipError_t launch_sp(AttnParams p, int BH, float* ws, int64_t ws_slots, h
     p.part_lse = slots ? ws + slots * (kTileRows * D) : nullptr;
     p.counter = reinterpret_cast<int*>(ws + ws_slots * kSlotFloats);     // two ints behind the slots, zero between launches
     const int64_t items = p.n_full + t.n_cut * t.split;
-    // Workgroup size (the results are the same bits).  Four wavefronts, 128 rows:
-    //  * where even the halves of the items do not fill every CU: twice the CUs work on the launch, one
-    //    wavefront per SIMD (one head x 2 048 tokens, d = 128: 25.9 -> 19.4 us with the merge; 2 x 1 024,
-    //    d = 64: 18.5 -> 14.6; 1 x 4 096: 33.7 -> 27.3);
-    //  * for short sweeps in many rounds: two workgroups share a CU and one computes while the other
-    //    loads or stores (24 x 16 384 queries on 600 keys: 187 -> 180 us, on 1 500 keys: 323 -> 319).
-    // Eight wavefronts, 256 rows, elsewhere: a K/V tile in LDS serves twice the rows, half the
-    // global -> LDS traffic (3 heads x 67 576: 5.53 ms against 6.12; 10 x 9 600: 0.419 against 0.471).
-    const int64_t key_tiles = (p.n_v + 63) / 64;
-    const bool four = 2 * items <= n_cu || (items >= 4 * (int64_t)n_cu && key_tiles <= 24);
+    const bool four = sp_wavefronts(t, p.n_v, D, n_cu) == 4;
     hipError_t e = four ? launch_items<D, 4, BASE2>(p, items, n_cu, st) : launch_items<D, 8, BASE2>(p, items, n_cu, st);
     if (e != hipSuccess || t.split <= 1) return e;
     hipLaunchKernelGGL(tail_merge_kernel<D>, dim3((unsigned)(t.n_cut * (kTileRows / (1024 / D)))), dim3(256), 0, st, p, (int)t.n_cut);

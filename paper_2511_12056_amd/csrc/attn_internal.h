@@ -182,6 +182,34 @@ inline TailPlan plan_tail(int64_t Sq, int BH, int64_t n_v, int n_cu) {
     }
     return t;
 }
+// Wavefronts per workgroup of a launch with plan `t`: eight (256 rows, one workgroup per CU) or four
+// (128 rows, half a tile; two per CU).  The results are the same bits; only the time differs (us,
+// eight -> four).  Eight is the rule: a K/V tile in LDS serves twice the rows, half the global -> LDS
+// traffic (3 heads x 67 576, d = 128: 5 530 -> 6 120; 10 x 9 600: 419 -> 471).  Four
+//  * where even the halves of the items do not fill every CU: twice the CUs work on the launch, one
+//    wavefront per SIMD (112 shapes of 1 to 128 tiles, 64 to 119 056 keys: none slower beyond the noise;
+//    1 head x 2 048 on 2 048, d = 128: 26.2 -> 19.7, d = 64: 19.2 -> 15.9; 1 x 1 024 on 119 056,
+//    d = 128: 149 -> 107);
+//  * for short sweeps (up to 24 key tiles) in more than four rounds of tiles: two workgroups share a CU
+//    and one computes while the other loads or stores, and the last round is spread more evenly (24 x
+//    16 384, d = 128, on 640 keys: 186 -> 177, on 1 536: 318 -> 310; 26 x 10 100 on 866: 167 -> 153,
+//    d = 64: 112 -> 102).  From 28 key tiles on both are the same within 1 %.  Not
+//      - in exactly four rounds (16 x 16 384, d = 128, on 1 536 keys: 210 -> 216), at d = 64 not in four
+//        to six rounds whose last is more than half full (80 x 4 096 on 512 keys: 89 -> 91);
+//      - with too few key tiles to hide the second workgroup's start behind: at d = 64, where a tile
+//        takes half the time, under eight (24 x 16 384 on 128 keys: 65 -> 73), at d = 128 under four
+//        unless there are six rounds (88 x 4 096 on 64 keys: 97 -> 100; 24 x 40 000 on 128: 243 -> 217);
+//      - under eight tiles per head (four with up to four key tiles), where K and V of a head are fetched
+//        for few rows (400 x 700, d = 128, on 1 536 keys: 270 -> 289; 1 126 x 256 on 1 529: 286 -> 315).
+inline int sp_wavefronts(const TailPlan& t, int64_t n_v, int d, int n_cu) {
+    const int64_t items = t.n_tiles - t.n_cut + t.n_cut * t.split, key_tiles = (n_v + 63) / 64;
+    if (2 * items <= n_cu) return 4;
+    if (key_tiles > 24 || t.tiles_per_head < (key_tiles > 4 ? 8 : 4) || t.n_tiles <= 4 * (int64_t)n_cu) return 8;
+    const bool six_rounds = t.n_tiles >= 6 * (int64_t)n_cu;
+    if (d == 128) return six_rounds || key_tiles >= 4 ? 4 : 8;
+    const int64_t rem = t.n_tiles % n_cu;
+    return key_tiles >= 8 && (six_rounds || (rem > 0 && 2 * rem <= n_cu)) ? 4 : 8;
+}
 // One workspace slot holds one key-range partial of a cut tile: 256 x 128 values + 256 lse.
 // A workspace of n slots is n * kSlotFloats floats followed by kCounterFloats floats that hold the
 // kernel's two work counters (zero whenever no launch is running on it).

@@ -120,3 +120,23 @@ def cut_row_mask(B: int, H: int, Sq: int, n_v: int, d: int, n_cu: int):
         bh, qt = divmod(t, tph)
         mask[bh, qt * 256:(qt + 1) * 256] = True
     return mask.reshape(B, H, Sq)
+
+
+def wavefronts(BH: int, Sq: int, n_v: int, d: int, n_cu: int):
+    """Wavefronts per workgroup (32 query rows each) of an attention launch, the rule written out
+    independently: four where twice the work items do not exceed the compute units; four for sweeps of at
+    most 24 key tiles of 64 in more than four rounds of query tiles with at least eight tiles per head (four
+    with up to four key tiles), except: d = 128 with fewer than 4 key tiles and fewer than six rounds; d = 64 with fewer than 8 key
+    tiles, or fewer than six rounds unless the last one is partly and at most half full.  Else eight."""
+    plan = tail_plan(BH, Sq, n_v, d, n_cu)
+    tiles = plan["n_tiles"]
+    items = tiles + plan["n_cut"] * (plan["split"] - 1)
+    if items * 2 <= n_cu:
+        return 4
+    kt = -(-n_v // 64)
+    if kt > 24 or -(-Sq // 256) < (8 if kt > 4 else 4) or tiles <= 4 * n_cu:
+        return 8
+    if d == 128:
+        return 4 if kt >= 4 or tiles >= 6 * n_cu else 8
+    half_round = 0 < tiles % n_cu <= n_cu // 2
+    return 4 if kt >= 8 and (tiles >= 6 * n_cu or half_round) else 8
