@@ -427,20 +427,20 @@ def test_key_axis_beyond_2_gib():
 @pytest.mark.parametrize("d", [128, 64])
 @pytest.mark.parametrize("n_v", [1, 63, 64, 65, 128, 191, 256, 300, 321, 449])
 def test_workgroup_sizes_and_item_chain(d, n_v):
-    """One head alone (fewer items than CUs), many heads (at least four rounds of items, each workgroup
-    taking several one after the other) and, for d = 128, a launch of one to two items per CU: the three
-    launch forms run different workgroup sizes and must give the same bits, and those must be right.
-    Key counts from one key to seven and a bit tiles: every exit of the unrolled loop, tails included."""
+    """One head alone (workgroups of four wavefronts on 256 CUs), 200 heads and 520 heads (eight wavefronts,
+    each workgroup taking up to two and up to five items one after the other): the launches must give the
+    same bits, and those must be right.  Key counts from one key to seven and a bit tiles: every exit of
+    the unrolled loop, tails included.  (Chains of four-wavefront items: test_gpu_launch_forms.py.)"""
     import torch
     import paper_2511_12056_amd as pda
     H, Sq = 520, 300                       # 1 040 tiles of 256 rows; no tile of any of the launches is cut (n_v < 1 024)
     q, k, v = gen_qkv(31 + n_v, 1, H, Sq, n_v, d, unit_rms=True)
     dq, dk, dv = to_dev_bf16(q), to_dev_bf16(k), to_dev_bf16(v)
 
-    def run(heads, variant=None):
+    def run(heads, variant=None, first=0):
         out = torch.full((1, heads, Sq, d), float("nan"), device="cuda")
         lse = torch.full((1, heads, Sq), float("nan"), device="cuda")
-        a = [t[:, :heads].contiguous() for t in (dq, dk, dv)]
+        a = [t[:, first:first + heads].contiguous() for t in (dq, dk, dv)]
         if variant is None:
             pda.attn_fwd(*a, out, lse, d ** -0.5)
         else:
@@ -449,9 +449,9 @@ def test_workgroup_sizes_and_item_chain(d, n_v):
         return out, lse
 
     out, lse = run(H)
-    for heads in (1, 200):
-        o, l = run(heads)
-        assert torch.equal(o, out[:, :heads]) and torch.equal(l, lse[:, :heads]), heads
+    for first, heads in ((0, 1), (0, 200), (200, 200), (320, 200)):
+        o, l = run(heads, first=first)
+        assert torch.equal(o, out[:, first:first + heads]) and torch.equal(l, lse[:, first:first + heads]), (first, heads)
     redo, redo_lse = run(H, variant=3)     # every item swept a second time with the running max
     pick = [0, 1, 255, H - 1]
     ro, rl = _oracle(q[:, pick], k[:, pick], v[:, pick], d ** -0.5)
@@ -462,9 +462,9 @@ def test_workgroup_sizes_and_item_chain(d, n_v):
 
 @pytest.mark.parametrize("d", [128, 64])
 def test_second_sweep_takes_the_same_rows_in_every_launch_form(d):
-    """A row takes the running-max sweep by its own scores alone, so a launch of one head, of 200 heads
-    (eight wavefronts per workgroup on 256 CUs) and of 520 (four, each workgroup several items) give the
-    same bits on every row of a tile in which one row, in its first or second half, needs that sweep."""
+    """A row takes the running-max sweep by its own scores alone, so launches of one head (four wavefronts
+    per workgroup on 256 CUs), of 200 and of 520 heads (eight) give the same bits on every row of a tile in
+    which one row, in its first or second half, needs that sweep."""
     import torch
     import paper_2511_12056_amd as pda
     from oracle import attention
