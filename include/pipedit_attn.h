@@ -127,16 +127,16 @@ int pda_attn_fwd_noalloc(const void* q, const void* k, const void* v, float* out
 /*
  * How an attention launch over B*H (batch, head) pairs is cut into work items (host only;
  * every pointer below is a HOST pointer; no device work).  The kernel takes 256-row query tiles,
- * one workgroup per compute unit at a time, so tiles run in rounds of n_cu.  The last n_cut tiles
- * (in (batch, head, query tile) order: the partly filled last round; all tiles of a launch
- * with fewer tiles than compute units; none where the key ranges would get too short to pay)
- * are each computed as `split` (2..PDA_MAX_KEY_RANGES) partial attentions over consecutive key
- * ranges, range j = keys [part_offsets[j], part_offsets[j+1]) with boundaries at multiples of 64,
- * and merged with the formula of pda_attn_merge; all other tiles are swept in one pass.  The
- * ranges are equal, or a long first one and short others (many left-over tiles after one to three
- * rounds of whole tiles), or of decreasing size (after four or more rounds), whichever balances
- * the end of the launch better.  Hence two launches agree bit for bit on every row that lies in
- * an uncut tile of both, and to the rounding of the probabilities on the others.
+ * one per compute unit at a time (by one workgroup, or half each by two), so tiles run in rounds
+ * of n_cu.  The last n_cut tiles (in (batch, head, query tile) order: the partly filled last round;
+ * all tiles of a launch with fewer tiles than compute units; none where the key ranges would get
+ * too short to pay) are each computed as `split` (2..PDA_MAX_KEY_RANGES) partial attentions over
+ * consecutive key ranges, range j = keys [part_offsets[j], part_offsets[j+1]) with boundaries at
+ * multiples of 64, and merged with the formula of pda_attn_merge; all other tiles are swept in one
+ * pass.  The ranges are equal, or a long first one and short others (many left-over tiles after one
+ * to three rounds of whole tiles), or of decreasing size (after four or more rounds), whichever
+ * balances the end of the launch better.  Hence two launches agree bit for bit on every row that
+ * lies in an uncut tile of both, and to the rounding of the probabilities on the others.
  * n_cu: compute units of the device (0 = ask the current device).  Outputs (any may be NULL):
  * n_tiles; n_cut (0 = nothing is cut); split (1 = nothing is cut); part_offsets, a HOST array of
  * PDA_MAX_KEY_RANGES + 1 values (part_offsets[0] = 0, entries from index split on are

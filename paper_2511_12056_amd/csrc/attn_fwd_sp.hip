@@ -1,7 +1,7 @@
 // Flash-attention forward, software-pipelined schedule for gfx950, d = 128 and 64, 64-key tiles.
 // A workgroup of NW wavefronts sweeps 32 NW query rows: eight wavefronts (256 rows, one workgroup per
 // CU) or four (128 rows, two per CU); either way two wavefronts share a SIMD.  A wavefront owns 32 rows
-// (NQ = 1 sub-tile).  Two sub-tiles in one wavefront per SIMD, each K/V fragment feeding two MFMAs,
+// of them.  Two such sub-tiles in one wavefront per SIMD, each K/V fragment feeding two MFMAs,
 // were slower: a single wavefront leaves the latencies at the iteration boundary exposed.
 //
 // MFMA formulation and LDS tile layout are those of attn_fwd.hip (S^T = K Q^T, O^T = V^T P^T on
@@ -39,9 +39,9 @@
 //
 // Between items nothing but the claim of the next one is serial: its Q fragments and first tiles are
 // fetched while the results are stored.  The first iteration carries no PV and the last PV no softmax.
-// What an item costs besides its key tiles went from 14 to 10 us (24 x 16 384 queries on 600 keys,
-// ten tiles per item: 196 -> 187 us with eight wavefronts; about 3 us of the rest are the loads of Q
-// and the first tiles, 3 us the stores).
+// What an item costs besides its key tiles went from 14 to 12 us (24 x 16 384 queries on 600 keys,
+// ten tiles per item, six items one after the other: 196 -> 187 us with eight wavefronts; 3 us of the
+// rest are issuing the loads of Q and the first tiles, 3 us waiting for them, 3 us the stores).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 #include "attn_internal.h"
@@ -104,7 +104,6 @@ template <int D, int NW, bool BASE2>
 __global__ __launch_bounds__(64 * NW, 2) void attn_fwd_sp_kernel(const AttnParams p) {
     static_assert(D == 128 || D == 64, "head dimension");
     static_assert(NW == 8 || NW == 4, "wavefronts per workgroup");
-    constexpr int NQ = 1;
     constexpr int BN = 64;
     constexpr int M = 32 * NW;            // query rows of an item
     constexpr int SUB = kTileRows / M;    // items per query tile (and key range)
@@ -116,7 +115,7 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_fwd_sp_kernel(const AttnParam
     constexpr int NBUF = sp_buffers(D, NW);
     constexpr int K_BASE = 0, V_BASE = NBUF * TILE;       // LDS byte offsets
     constexpr int CHUNKS = TILE / 1024;   // DMA chunks of 1 KB per tile: 16 or 8
-    constexpr int CPW = CHUNKS / NW;      // per wavefront: 2 (4 with NQ = 2), or 1 for d = 64
+    constexpr int CPW = CHUNKS / NW;      // per wavefront: 2 (eight wavefronts) or 4 for d = 128, 1 or 2 for d = 64
     constexpr int RPC = 1024 / (D * 2);   // rows per chunk: 4 or 8
     static_assert(CPW >= 1, "every wavefront fetches at least one chunk of a tile");
 
@@ -135,7 +134,7 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_fwd_sp_kernel(const AttnParam
     const int64_t Sq = p.Sq;
     const unsigned lds0 = (unsigned)(uintptr_t)(LDS_PTR(const void))smem;
 
-    // Persistent workgroups (one per CU) take work items in index order: workgroup i starts with item
+    // Persistent workgroups (one per CU, or two of four wavefronts) take work items in index order: workgroup i starts with item
     // i and fetches the following ones from a device counter.  The chip's XCDs run at persistently
     // different speeds (several percent apart under the power limit) and the hardware deals the
     // workgroups of a grid to them round robin, so a grid with one workgroup per item would end with
@@ -212,7 +211,7 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_fwd_sp_kernel(const AttnParam
     };
 
     // ---- Q operand fragments, resident for the whole sweep
-    bf16x8 qf[NQ][NKK];
+    bf16x8 qf[NKK];
     // Makes `it` the current item: its key range [kv0, kv1) (tile aligned; all keys, or range `part` of a
     // cut tile), its Q fragments and first K/V tiles on their way.
     auto begin_item = [&](int it) __attribute__((always_inline)) {
@@ -227,15 +226,12 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_fwd_sp_kernel(const AttnParam
         vp = p.v + (int64_t)b * p.kv_bs + (int64_t)h * p.kv_hs + kv0 * D;
         n_v = (int)(kv1 - kv0);
         nt = (n_v + BN - 1) / BN;
+        const int l = opaque(lane);
+        int64_t row = (int64_t)q_tile * kTileRows + sub * M + wave * 32 + (l & 31);
+        row = row < Sq ? row : Sq - 1;
 #pragma unroll
-        for (int nq = 0; nq < NQ; ++nq) {
-            const int l = opaque(lane);
-            int64_t row = (int64_t)q_tile * kTileRows + sub * M + wave * (32 * NQ) + nq * 32 + (l & 31);
-            row = row < Sq ? row : Sq - 1;
-#pragma unroll
-            for (int kk = 0; kk < NKK; ++kk)
-                qf[nq][kk] = *reinterpret_cast<const bf16x8*>(qp + row * D + kk * 16 + 8 * (l >> 5));
-        }
+        for (int kk = 0; kk < NKK; ++kk)
+            qf[kk] = *reinterpret_cast<const bf16x8*>(qp + row * D + kk * 16 + 8 * (l >> 5));
         issue_first_tiles();
     };
 
@@ -255,24 +251,23 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_fwd_sp_kernel(const AttnParam
         v_ptr[db] = (LDS_PTR(const unsigned char))smem + (V_BASE + v_key_in * (D * 2) + g * 16 + (t16 & 1) * 8);
     }
 
-    float mc_run[NQ], l_run[NQ];     // reference max in exp2 units (max * scale * log2 e), lane's share of the running sum
-    f32x16 o_acc[NQ][NDB];
-    f32x16 nref[NQ];                                   // BASE2, first sweep: minus the row's reference, as an accumulator seed
-    f32x16 s_a[NQ][NKB], s_b[NQ][NKB];                 // scores of two consecutive tiles, alternating roles
+    float mc_run, l_run;     // reference max in exp2 units (max * scale * log2 e), lane's share of the running sum
+    f32x16 o_acc[NDB];
+    f32x16 nref;                         // BASE2, first sweep: minus the row's reference, as an accumulator seed
+    f32x16 s_a[NKB], s_b[NKB];           // scores of two consecutive tiles, alternating roles
     // Packed bf16 P (MFMA operand order).  One buffer serves two consecutive tiles: group (kb,u) of
     // tile t-1 is consumed by the PV MFMAs of slots (d/32)(2kb+u) .. +d/32-1, before the softmax of tile t writes it.
-    unsigned p_io[NQ][NKB][2][4];
+    unsigned p_io[NKB][2][4];
     const float c = BASE2 ? 1.0f : p.scale_log2e;   // > 0 (the host substitutes a tiny positive value for scale 0)
 
-    auto mask_tail = [&](f32x16 (&s)[NQ][NKB], int t) __attribute__((always_inline)) {
+    auto mask_tail = [&](f32x16 (&s)[NKB], int t) __attribute__((always_inline)) {
         const int hidden = n_v - t * BN - 4 * (opaque(lane) >> 5);      // key 4 lh + x is hidden if x >= this
 #pragma unroll
         for (int kb = 0; kb < NKB; ++kb)
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
                 if (kb * 32 + (r >> 2) * 8 + (r & 3) >= hidden) {
-#pragma unroll
-                    for (int nq = 0; nq < NQ; ++nq) s[nq][kb][r] = -INFINITY;
+                    s[kb][r] = -INFINITY;
                 }
             }
     };
@@ -293,22 +288,17 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_fwd_sp_kernel(const AttnParam
         for (int kk = 0; kk < NKK; ++kk) asm volatile("" : "+v"(k_ptr[kk]));
 #pragma unroll
         for (int db = 0; db < NDB; ++db) asm volatile("" : "+v"(v_ptr[db]));
+        mc_run = -INFINITY;
+        l_run = 0.f;
 #pragma unroll
-        for (int nq = 0; nq < NQ; ++nq) {
-            mc_run[nq] = -INFINITY;
-            l_run[nq] = 0.f;
+        for (int db = 0; db < NDB; ++db)
 #pragma unroll
-            for (int db = 0; db < NDB; ++db)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) o_acc[nq][db][r] = 0.f;
-        }
+            for (int r = 0; r < 16; ++r) o_acc[db][r] = 0.f;
         k_dma = kp + NBUF * BN * D;
         v_dma = vp + (NBUF - 2) * BN * D;
         // the Q fragments (resident for both sweeps) and the item's first tiles have arrived
 #pragma unroll
-        for (int nq = 0; nq < NQ; ++nq)
-#pragma unroll
-            for (int kk = 0; kk < NKK; ++kk) asm volatile("" : "+v"(qf[nq][kk]));
+        for (int kk = 0; kk < NKK; ++kk) asm volatile("" : "+v"(qf[kk]));
         wait_vmcnt<0>();
         barrier();
 
@@ -320,28 +310,23 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_fwd_sp_kernel(const AttnParam
 #pragma unroll
                 for (int kb = 0; kb < NKB; ++kb) {
                     const bf16x8 a = *(LDS_PTR(const bf16x8))(k_ptr[kk] + kb * 32 * (D * 2));
-#pragma unroll
-                    for (int nq = 0; nq < NQ; ++nq)
-                        s_a[nq][kb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, qf[nq][kk], kk == 0 ? zero : s_a[nq][kb], 0, 0, 0);
+                    s_a[kb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, qf[kk], kk == 0 ? zero : s_a[kb], 0, 0, 0);
                 }
             if (BN > n_v) mask_tail(s_a, 0);
             if constexpr (!SAFE) {
                 // fixed reference: the row max over the first key tile (key 0 is always valid)
+                float m0 = s_a[0][0], m1 = s_a[0][1];
 #pragma unroll
-                for (int nq = 0; nq < NQ; ++nq) {
-                    float m0 = s_a[nq][0][0], m1 = s_a[nq][0][1];
+                for (int e = 2; e < 32; e += 2) {
+                    m0 = fmaxf(m0, s_a[e / 16][e % 16]);
+                    m1 = fmaxf(m1, s_a[(e + 1) / 16][(e + 1) % 16]);
+                }
+                mc_run = pair_max(fmaxf(m0, m1)) * c;
+                if constexpr (BASE2) {
 #pragma unroll
-                    for (int e = 2; e < 32; e += 2) {
-                        m0 = fmaxf(m0, s_a[nq][e / 16][e % 16]);
-                        m1 = fmaxf(m1, s_a[nq][(e + 1) / 16][(e + 1) % 16]);
-                    }
-                    mc_run[nq] = pair_max(fmaxf(m0, m1)) * c;
-                    if constexpr (BASE2) {
+                    for (int r = 0; r < 16; ++r) nref[r] = -mc_run;
 #pragma unroll
-                        for (int r = 0; r < 16; ++r) nref[nq][r] = -mc_run[nq];
-#pragma unroll
-                        for (int e = 0; e < 32; ++e) s_a[nq][e / 16][e % 16] -= mc_run[nq];
-                    }
+                    for (int e = 0; e < 32; ++e) s_a[e / 16][e % 16] -= mc_run;
                 }
             }
         }
@@ -350,12 +335,11 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_fwd_sp_kernel(const AttnParam
         // One iteration; TB = t % 4 fixes every LDS buffer offset at compile time.
         //   s_c: scores of tile t (in, overwritten by its probabilities)   s_n: scores of tile t+1 (out)
         // Slot i (0..N_FR-1; N_FR = 32 for d = 128, 16 for d = 64) = the MFMAs fed by operand fragment
-        // i (first the PV fragments, then as many QK fragments; NQ MFMAs each), the LDS reads of
-        // fragment i+PF, and slice i of the softmax VALU work: slices 0-3 the row max, 4-5 the
-        // reference / rescale factors, the others the 32 exponentials with their packing to bf16 and
-        // the row sum.
+        // i (first the PV fragments, then as many QK fragments), the LDS reads of fragment i+PF, and slice i
+        // of the softmax VALU work: slices 0-3 the row max, 4-5 the reference / rescale factors, the others
+        // the 32 exponentials with their packing to bf16 and the row sum.
         //   FIRST: t = 0, no PV yet (its slots hold softmax work only)
-        auto iteration = [&](auto tb_c, auto first_c, int t, f32x16 (&s_c)[NQ][NKB], f32x16 (&s_n)[NQ][NKB]) {
+        auto iteration = [&](auto tb_c, auto first_c, int t, f32x16 (&s_c)[NKB], f32x16 (&s_n)[NKB]) {
             constexpr int TB = decltype(tb_c)::value;
             constexpr bool FIRST = decltype(first_c)::value;
             constexpr int KN = (TB + 1) % NBUF;           // buffer of K tile t+1
@@ -400,35 +384,28 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_fwd_sp_kernel(const AttnParam
                     frag[i % RING] = *(LDS_PTR(const bf16x8))(k_ptr[kk] + (KN * TILE + kb * 32 * (D * 2)));
                 }
             };
-            auto do_mfma = [&](auto idx, auto nq_c) {
-                constexpr int i = decltype(idx)::value, nq = decltype(nq_c)::value;
+            auto do_mfma = [&](auto idx) {
+                constexpr int i = decltype(idx)::value;
                 if constexpr (i < N_PV && FIRST) {
                 } else if constexpr (i < N_PV) {
                     constexpr int kb = i / (2 * NDB), u = (i / NDB) % 2, db = i % NDB;
-                    const u32x4 pv = {p_io[nq][kb][u][0], p_io[nq][kb][u][1], p_io[nq][kb][u][2], p_io[nq][kb][u][3]};
-                    o_acc[nq][db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag[i % RING], __builtin_bit_cast(bf16x8, pv),
-                                                                            o_acc[nq][db], 0, 0, 0);
+                    const u32x4 pv = {p_io[kb][u][0], p_io[kb][u][1], p_io[kb][u][2], p_io[kb][u][3]};
+                    o_acc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag[i % RING], __builtin_bit_cast(bf16x8, pv), o_acc[db], 0, 0, 0);
                 } else {
                     constexpr int j = i - N_PV, kk = j / 2, kb = j % 2;
                     if constexpr (kk == 0) {
                         const f32x16 zero = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
-                        s_n[nq][kb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag[i % RING], qf[nq][kk],
-                                                                              (BASE2 && !SAFE) ? nref[nq] : zero, 0, 0, 0);
+                        s_n[kb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag[i % RING], qf[kk], (BASE2 && !SAFE) ? nref : zero, 0, 0, 0);
                     } else {
-                        s_n[nq][kb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag[i % RING], qf[nq][kk], s_n[nq][kb], 0, 0, 0);
+                        s_n[kb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag[i % RING], qf[kk], s_n[kb], 0, 0, 0);
                     }
                 }
             };
 
             // Softmax of tile t, slice by slice (anchored with empty asm statements: pure arithmetic
             // would otherwise drift out of the slot it is written in).
-            float mx[NQ], mx2[NQ], mc_new[NQ], alpha[NQ], lsum[NQ], lsum2[NQ];
-#pragma unroll
-            for (int nq = 0; nq < NQ; ++nq) {
-                mx[nq] = s_c[nq][0][0];
-                mx2[nq] = s_c[nq][0][1];
-                mc_new[nq] = SAFE ? 0.f : mc_run[nq]; alpha[nq] = 1.f; lsum[nq] = 0.f; lsum2[nq] = 0.f;
-            }
+            float mx = s_c[0][0], mx2 = s_c[0][1];
+            float mc_new = SAFE ? 0.f : mc_run, alpha = 1.f, lsum = 0.f, lsum2 = 0.f;
             // Elements of the lane's 32 scores handled by exponential slot k (0..NX-1): [e_lo(k), e_lo(k+1)).
             // The work on an element is spread over consecutive slots so that no instruction needs a
             // result produced in its own slot: slot k-1 forms z = s*c - m, slot k takes exp2(z), slot k+1
@@ -439,67 +416,67 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_fwd_sp_kernel(const AttnParam
             // the first half of the slots, have read it).
             constexpr int X0 = SAFE ? 6 : 3, NX = N_FR - X0;
             auto e_lo = [](int k) constexpr { return k <= 0 ? 0 : (k >= NX ? 32 : k * 32 / NX); };
-            auto fma_of = [&](auto kc, auto nq_c) {
-                constexpr int k = decltype(kc)::value, nq = decltype(nq_c)::value;
+            auto fma_of = [&](auto kc) {
+                constexpr int k = decltype(kc)::value;
                 if constexpr (BASE2 && !SAFE) return;             // the MFMA output already is s - reference
                 static_for<e_lo(k), e_lo(k + 1)>([&](auto ec) {
                     constexpr int e = decltype(ec)::value;
-                    float z = __builtin_fmaf(s_c[nq][e / 16][e % 16], c, -mc_new[nq]);
+                    float z = __builtin_fmaf(s_c[e / 16][e % 16], c, -mc_new);
                     asm volatile("" : "+v"(z));
-                    s_c[nq][e / 16][e % 16] = z;
+                    s_c[e / 16][e % 16] = z;
                 });
             };
-            auto exp_of = [&](auto kc, auto nq_c) {
-                constexpr int k = decltype(kc)::value, nq = decltype(nq_c)::value;
+            auto exp_of = [&](auto kc) {
+                constexpr int k = decltype(kc)::value;
                 static_for<e_lo(k), e_lo(k + 1)>([&](auto ec) {
                     constexpr int e = decltype(ec)::value;
-                    float pe = __builtin_amdgcn_exp2f(s_c[nq][e / 16][e % 16]);
+                    float pe = __builtin_amdgcn_exp2f(s_c[e / 16][e % 16]);
                     asm volatile("" : "+v"(pe));
-                    s_c[nq][e / 16][e % 16] = pe;
+                    s_c[e / 16][e % 16] = pe;
                 });
             };
-            auto sum_pack_of = [&](auto kc, auto nq_c) {
-                constexpr int k = decltype(kc)::value, nq = decltype(nq_c)::value;
+            auto sum_pack_of = [&](auto kc) {
+                constexpr int k = decltype(kc)::value;
                 static_for<e_lo(k), e_lo(k + 1)>([&](auto ec) {
                     constexpr int e = decltype(ec)::value;
                     // row sum with plain adds, two chains (the dot-product instructions would take two
                     // values at a time, but they occupy the matrix pipe and stall the MFMA stream)
                     if constexpr (e % 2 == 0) {
-                        lsum[nq] += s_c[nq][e / 16][e % 16];
-                        asm volatile("" : "+v"(lsum[nq]));
+                        lsum += s_c[e / 16][e % 16];
+                        asm volatile("" : "+v"(lsum));
                     } else {
-                        lsum2[nq] += s_c[nq][e / 16][e % 16];
-                        asm volatile("" : "+v"(lsum2[nq]));
+                        lsum2 += s_c[e / 16][e % 16];
+                        asm volatile("" : "+v"(lsum2));
                         constexpr int q = e / 2, kb = q / 8, u = (q % 8) / 4, j = q % 4;   // pair q = elements 2q, 2q+1
-                        unsigned pk = pack_bf16(s_c[nq][kb][8 * u + 2 * j], s_c[nq][kb][8 * u + 2 * j + 1]);
+                        unsigned pk = pack_bf16(s_c[kb][8 * u + 2 * j], s_c[kb][8 * u + 2 * j + 1]);
                         asm volatile("" : "+v"(pk));
-                        p_io[nq][kb][u][j] = pk;
+                        p_io[kb][u][j] = pk;
                     }
                 });
             };
-            auto valu_slice = [&](auto idx, auto nq_c) {
-                constexpr int i = decltype(idx)::value, nq = decltype(nq_c)::value;
+            auto valu_slice = [&](auto idx) {
+                constexpr int i = decltype(idx)::value;
                 if constexpr (SAFE && i < 4) {                          // row max over the lane's 32 scores, two chains
 #pragma unroll
                     for (int e = 8 * i; e < 8 * i + 8; e += 4) {
-                        mx[nq] = fmaxf(fmaxf(mx[nq], s_c[nq][e / 16][e % 16]), s_c[nq][(e + 2) / 16][(e + 2) % 16]);
-                        mx2[nq] = fmaxf(fmaxf(mx2[nq], s_c[nq][(e + 1) / 16][(e + 1) % 16]), s_c[nq][(e + 3) / 16][(e + 3) % 16]);
+                        mx = fmaxf(fmaxf(mx, s_c[e / 16][e % 16]), s_c[(e + 2) / 16][(e + 2) % 16]);
+                        mx2 = fmaxf(fmaxf(mx2, s_c[(e + 1) / 16][(e + 1) % 16]), s_c[(e + 3) / 16][(e + 3) % 16]);
                     }
                 } else if constexpr (SAFE && i == 4) {
                     // Move the reference only if the max grew by more than 2^8 (or there is none yet:
                     // -inf gives an infinite difference; a fully hidden tile gives -inf and no move).
-                    const float mxc = pair_max(fmaxf(mx[nq], mx2[nq])) * c;
-                    mc_new[nq] = (mxc - mc_run[nq] > 8.0f) ? mxc : mc_run[nq];
+                    const float mxc = pair_max(fmaxf(mx, mx2)) * c;
+                    mc_new = (mxc - mc_run > 8.0f) ? mxc : mc_run;
                 } else if constexpr (SAFE && i == 5) {
-                    alpha[nq] = __builtin_amdgcn_exp2f(mc_run[nq] - mc_new[nq]);      // 1 if unmoved, 0 on the first tile
-                    fma_of(std::integral_constant<int, 0>{}, nq_c);
+                    alpha = __builtin_amdgcn_exp2f(mc_run - mc_new);      // 1 if unmoved, 0 on the first tile
+                    fma_of(std::integral_constant<int, 0>{});
                 } else if constexpr (!SAFE && i == X0 - 1) {
-                    fma_of(std::integral_constant<int, 0>{}, nq_c);
+                    fma_of(std::integral_constant<int, 0>{});
                 } else if constexpr (i >= X0) {                         // 32 exponentials over NX slots
                     constexpr int k = i - X0;
-                    exp_of(std::integral_constant<int, k>{}, nq_c);
-                    fma_of(std::integral_constant<int, k + 1>{}, nq_c);
-                    sum_pack_of(std::integral_constant<int, k - 1>{}, nq_c);
+                    exp_of(std::integral_constant<int, k>{});
+                    fma_of(std::integral_constant<int, k + 1>{});
+                    sum_pack_of(std::integral_constant<int, k - 1>{});
                 }
             };
 
@@ -511,33 +488,27 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_fwd_sp_kernel(const AttnParam
             });
             static_for<0, N_FR>([&](auto idx) {
                 constexpr int i = decltype(idx)::value;
-                static_for<0, NQ>([&](auto nq_c) { do_mfma(idx, nq_c); });
+                do_mfma(idx);
                 load_frag(std::integral_constant<int, i + PF>{});
                 __builtin_amdgcn_sched_barrier(0);       // the reads go first: they are on the path of slot i + PF
-                static_for<0, NQ>([&](auto nq_c) { valu_slice(idx, nq_c); });
+                valu_slice(idx);
                 __builtin_amdgcn_sched_barrier(0);
             });
-            static_for<0, NQ>([&](auto nq_c) {
-                constexpr int nq = decltype(nq_c)::value;
-                sum_pack_of(std::integral_constant<int, NX - 1>{}, nq_c);
-                if constexpr (SAFE) {
-                    l_run[nq] = __builtin_fmaf(l_run[nq], alpha[nq], lsum[nq] + lsum2[nq]);
-                    mc_run[nq] = mc_new[nq];
-                } else {
-                    l_run[nq] += lsum[nq] + lsum2[nq];
-                }
-            });
+            sum_pack_of(std::integral_constant<int, NX - 1>{});
+            if constexpr (SAFE) {
+                l_run = __builtin_fmaf(l_run, alpha, lsum + lsum2);
+                mc_run = mc_new;
+            } else {
+                l_run += lsum + lsum2;
+            }
             // =====================================================================================
 
             // rescale O once PV(t-1) is in, if some lane moved its reference (rare after the first tiles)
+            if (SAFE && __builtin_amdgcn_ballot_w64(alpha != 1.0f) != 0) {
 #pragma unroll
-            for (int nq = 0; nq < NQ; ++nq) {
-                if (SAFE && __builtin_amdgcn_ballot_w64(alpha[nq] != 1.0f) != 0) {
+                for (int db = 0; db < NDB; ++db)
 #pragma unroll
-                    for (int db = 0; db < NDB; ++db)
-#pragma unroll
-                        for (int r = 0; r < 16; ++r) o_acc[nq][db][r] *= alpha[nq];
-                }
+                    for (int r = 0; r < 16; ++r) o_acc[db][r] *= alpha;
             }
             if ((t + 2) * BN > n_v) mask_tail(s_n, t + 1);     // S_{t+1} holds hidden keys
 
@@ -553,9 +524,7 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_fwd_sp_kernel(const AttnParam
         using no = std::false_type;
         auto pin_o = [&]() {       // keeps the zeroed accumulators in registers (a constant would be copied at every exit)
 #pragma unroll
-            for (int nq = 0; nq < NQ; ++nq)
-#pragma unroll
-                for (int db = 0; db < NDB; ++db) asm volatile("" : "+v"(o_acc[nq][db]));
+            for (int db = 0; db < NDB; ++db) asm volatile("" : "+v"(o_acc[db]));
         };
         pin_o();
         iteration(std::integral_constant<int, 0>{}, std::true_type{}, 0, s_a, s_b);
@@ -579,11 +548,8 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_fwd_sp_kernel(const AttnParam
                 const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LDS_PTR(s16x4))a);
                 const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LDS_PTR(s16x4))(a + 8 * (D * 2)));
                 const bf16x8 av = __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
-#pragma unroll
-                for (int nq = 0; nq < NQ; ++nq) {
-                    const u32x4 pv = {p_io[nq][kb][u][0], p_io[nq][kb][u][1], p_io[nq][kb][u][2], p_io[nq][kb][u][3]};
-                    o_acc[nq][db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av, __builtin_bit_cast(bf16x8, pv), o_acc[nq][db], 0, 0, 0);
-                }
+                const u32x4 pv = {p_io[kb][u][0], p_io[kb][u][1], p_io[kb][u][2], p_io[kb][u][3]};
+                o_acc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av, __builtin_bit_cast(bf16x8, pv), o_acc[db], 0, 0, 0);
             }
         }
         wait_vmcnt<0>();        // no DMA may land in the tiles of the next item or outlive the workgroup's LDS
@@ -614,32 +580,29 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_fwd_sp_kernel(const AttnParam
             row_sub = (int64_t)q_tile * kTileRows;
         }
         oph = reinterpret_cast<__bf16*>(p.out) + (int64_t)b * p.o_bs + (int64_t)h * p.o_hs;
-        q_row0 = (int64_t)q_tile * kTileRows + sub * M + wave * (32 * NQ);
+        q_row0 = (int64_t)q_tile * kTileRows + sub * M + wave * 32;
     };
     // ---- epilogue: normalise, write out and lse (the lanes of `mask`)
     auto store_results = [&](uint64_t mask) __attribute__((always_inline)) {
         const int lane_e = opaque(lane), li_e = lane_e & 31, lh_e = lane_e >> 5;
+        const float l_tot = pair_sum(l_run);
+        const float inv = 1.0f / l_tot;
+        const int64_t row = q_row0 + li_e;
+        if (row < Sq && __builtin_amdgcn_inverse_ballot_w64(mask)) {
 #pragma unroll
-        for (int nq = 0; nq < NQ; ++nq) {
-            const float l_tot = pair_sum(l_run[nq]);
-            const float inv = 1.0f / l_tot;
-            const int64_t row = q_row0 + nq * 32 + li_e;
-            if (row < Sq && __builtin_amdgcn_inverse_ballot_w64(mask)) {
+            for (int db = 0; db < NDB; ++db)
 #pragma unroll
-                for (int db = 0; db < NDB; ++db)
-#pragma unroll
-                    for (int a = 0; a < 4; ++a) {
-                        f32x4 o4 = {o_acc[nq][db][4 * a] * inv, o_acc[nq][db][4 * a + 1] * inv,
-                                    o_acc[nq][db][4 * a + 2] * inv, o_acc[nq][db][4 * a + 3] * inv};
-                        if (store_bf16) {
-                            const u32x2 h2 = {pack_bf16(o4[0], o4[1]), pack_bf16(o4[2], o4[3])};
-                            *reinterpret_cast<u32x2*>(oph + row * D + db * 32 + a * 8 + 4 * lh_e) = h2;
-                        } else {
-                            *reinterpret_cast<f32x4*>(op + (row - row_sub) * D + db * 32 + a * 8 + 4 * lh_e) = o4;
-                        }
+                for (int a = 0; a < 4; ++a) {
+                    f32x4 o4 = {o_acc[db][4 * a] * inv, o_acc[db][4 * a + 1] * inv,
+                                o_acc[db][4 * a + 2] * inv, o_acc[db][4 * a + 3] * inv};
+                    if (store_bf16) {
+                        const u32x2 h2 = {pack_bf16(o4[0], o4[1]), pack_bf16(o4[2], o4[3])};
+                        *reinterpret_cast<u32x2*>(oph + row * D + db * 32 + a * 8 + 4 * lh_e) = h2;
+                    } else {
+                        *reinterpret_cast<f32x4*>(op + (row - row_sub) * D + db * 32 + a * 8 + 4 * lh_e) = o4;
                     }
-                if (lh_e == 0) lp[row - row_sub] = mc_run[nq] * 0.6931471805599453f + __logf(l_tot);
-            }
+                }
+            if (lh_e == 0) lp[row - row_sub] = mc_run * 0.6931471805599453f + __logf(l_tot);
         }
     };
 
@@ -659,18 +622,15 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_fwd_sp_kernel(const AttnParam
         // the other rows keep the result of the first sweep: what a row gets depends on that row alone,
         // not on the rows that happen to share its workgroup, whose number depends on the launch.
         bool bad = p.redo_always != 0;               // test switch: every row takes the second sweep
+        bad |= !(pair_sum(l_run) < 1.8446744e19f);
+        // Weights of up to 2^64 times large finite V entries can overflow the accumulators while the
+        // row sum stays in range: inf * 0 and NaN * 0 are NaN, any finite value * 0 is 0.
+        float t = 0.f;
 #pragma unroll
-        for (int nq = 0; nq < NQ; ++nq) {
-            bad |= !(pair_sum(l_run[nq]) < 1.8446744e19f);
-            // Weights of up to 2^64 times large finite V entries can overflow the accumulators while the
-            // row sum stays in range: inf * 0 and NaN * 0 are NaN, any finite value * 0 is 0.
-            float t = 0.f;
+        for (int db = 0; db < NDB; ++db)
 #pragma unroll
-            for (int db = 0; db < NDB; ++db)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) t = __builtin_fmaf(o_acc[nq][db][r], 0.0f, t);
-            bad |= !(t == 0.f);
-        }
+            for (int r = 0; r < 16; ++r) t = __builtin_fmaf(o_acc[db][r], 0.0f, t);
+        bad |= !(t == 0.f);
         uint64_t redo = __builtin_amdgcn_ballot_w64(bad);
         redo |= redo << 32 | redo >> 32;             // lanes l and l + 32 hold one row
         if (lane == 0) redo_flag[wave] = redo != 0 ? 1 : 0;
@@ -712,7 +672,7 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_fwd_sp_kernel(const AttnParam
 // quarter of a wavefront) per row, so a row's lse is read by all its lanes before one of them
 // overwrites it.
 template <int D>
-__global__ __launch_bounds__(256) void tail_merge_kernel(const AttnParams p, int n_tail) {
+__global__ __launch_bounds__(256) void tail_merge_kernel(const AttnParams p) {
     constexpr int M = 256, LPR = D / 4, RPB = 256 / LPR;      // lanes per row, rows per workgroup
     const int tile = p.n_full + blockIdx.x / (M / RPB);
     const int r_in = (blockIdx.x % (M / RPB)) * RPB + (threadIdx.x / LPR);
@@ -805,7 +765,7 @@ static hipError_t launch_sp(AttnParams p, int BH, float* ws, int64_t ws_slots, h
     const bool four = sp_wavefronts(t, p.n_v, D, n_cu) == 4;
     hipError_t e = four ? launch_items<D, 4, BASE2>(p, items, n_cu, st) : launch_items<D, 8, BASE2>(p, items, n_cu, st);
     if (e != hipSuccess || t.split <= 1) return e;
-    hipLaunchKernelGGL(tail_merge_kernel<D>, dim3((unsigned)(t.n_cut * (kTileRows / (1024 / D)))), dim3(256), 0, st, p, (int)t.n_cut);
+    hipLaunchKernelGGL(tail_merge_kernel<D>, dim3((unsigned)(t.n_cut * (kTileRows / (1024 / D)))), dim3(256), 0, st, p);
     return hipGetLastError();
 }
 

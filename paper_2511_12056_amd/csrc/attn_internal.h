@@ -48,9 +48,11 @@ struct AttnParams {
     float scale;            // softmax scale
     float scale_log2e;      // scale * log2(e)
     // Work items of the software-pipelined kernel, taken in index order by persistent workgroups.
-    // Items [0, n_full) are whole 256-row query tiles (tile = item; head = tile / tiles_per_head).
-    // Every later tile is cut into `split` key ranges [part_off[j], part_off[j+1]), one item each
-    // (item = n_full + part * n_cut + cut tile), so that the end of the launch is made of short items;
+    // Units [0, n_full) are whole 256-row query tiles (tile = unit; head = tile / tiles_per_head).
+    // Every later tile is cut into `split` key ranges [part_off[j], part_off[j+1]), one unit each
+    // (unit = n_full + part * n_cut + cut tile), so that the end of the launch is made of short ones.
+    // With workgroups of eight wavefronts an item is a unit; with four, items 2u and 2u + 1 are the
+    // upper and the lower 128 rows of unit u.
     // part 0 writes out/lse, parts >= 1 write normalised partials to part_out/part_lse, which a
     // merge pass folds into out/lse.  split <= 1: no cut.
     int tiles_per_head;
@@ -60,15 +62,15 @@ struct AttnParams {
     float* part_out;        // [(tile - n_full) * (split - 1) + part - 1][256][d]
     float* part_lse;        // [(tile - n_full) * (split - 1) + part - 1][256]
     int n_cut;              // number of cut tiles (the last n_cut of the launch)
-    int n_items;            // n_full + n_cut * split
-    int* counter;           // two ints, zero between launches: next work item, workgroups that have finished
+    int n_items;            // n_full + n_cut * split, twice that with four wavefronts (set by the launch)
+    int* counter;           // two ints, zero between launches: items taken beyond each workgroup's first, workgroups that have finished
     int out_bf16;           // software-pipelined kernel: `out` points to bf16 elements (same element strides)
     int base2;              // scores are already in log2 units: weights 2^(q.k), scale_log2e == 1
     int redo_always;        // software-pipelined kernel: sweep every item a second time with the running max (testing aid)
 };
 
-// Tail plan of the software-pipelined kernel (256-row query tiles, one persistent
-// workgroup per CU taking items in order).  Whole tiles are long items (a 119 056-key sweep takes
+// Tail plan of the software-pipelined kernel (256-row query tiles; persistent workgroups, one per CU
+// or two that take half a tile each, taking items in order).  Whole tiles are long items (a 119 056-key sweep takes
 // 3 ms), the XCDs run at different speeds, and a launch ends when the last item does; so the
 // `rem` = n_tiles mod n_cu tiles that do not fill a round of whole tiles are cut into `split` key
 // ranges, short items that the workgroups pick up as they run out of whole tiles.  Measured on
