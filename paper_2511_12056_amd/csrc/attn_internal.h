@@ -228,13 +228,13 @@ inline int64_t max_tail_slots(int n_cu, bool out_bf16) {
 }
 
 // Enqueue the forward kernel for B*Hg = BH (batch, head) pairs.  variant selects a tiling (0 = the
-// software-pipelined kernel for d = 128; 1, 2 = reference tilings; 3 = 0 with its running-max sweep
-// forced on every item).  ws / ws_slots: device workspace for the key-range partials of the
+// software-pipelined kernel; 1, 2 = reference tilings; 3 = 0 with its running-max sweep forced on
+// every item).  ws / ws_slots: device workspace for the key-range partials of the
 // software-pipelined kernel and its capacity in slots of kSlotFloats floats; a launch that needs
 // more returns hipErrorInvalidValue (the caller sizes it with plan_tail / tail_slots).
 hipError_t launch_attn_fwd(const AttnParams& p, int BH, int D, int variant, float* ws, int64_t ws_slots, hipStream_t st);
 
-// Software-pipelined kernel for d = 128 (attn_fwd_sp.hip); p.n_v >= 1, p.scale_log2e > 0.
+// Software-pipelined kernel for d = 128 and 64 (attn_fwd_sp.hip); p.n_v >= 1, p.scale_log2e > 0.
 hipError_t launch_attn_fwd_sp(const AttnParams& p, int BH, int D, float* ws, int64_t ws_slots, hipStream_t st);
 
 // Does this (d, variant, valid key count) take the software-pipelined kernel (and so possibly a workspace)?
