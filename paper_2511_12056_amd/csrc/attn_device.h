@@ -15,6 +15,7 @@ typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
 
 #define LDS_PTR(T) T __attribute__((address_space(3)))*
+#define GLOBAL_PTR(T) T __attribute__((address_space(1)))*
 
 // Lanes l and l^32 hold the two halves of one query's keys.  v_permlane32_swap hands every lane
 // both halves' values (one in each result register), so max and sum need no select.

@@ -39,9 +39,12 @@
 //
 // Between items nothing but the claim of the next one is serial: its Q fragments and first tiles are
 // fetched while the results are stored.  The first iteration carries no PV and the last PV no softmax.
-// What an item costs besides its key tiles went from 14 to 12 us (24 x 16 384 queries on 600 keys,
-// ten tiles per item, six items one after the other: 196 -> 187 us with eight wavefronts; 3 us of the
-// rest are issuing the loads of Q and the first tiles, 3 us waiting for them, 3 us the stores).
+// What an item costs besides its key tiles (24 heads x 9 600, eight wavefronts, timestamps): claim 0.6 us,
+// issue of the next item's loads 2.9, stores 2.9, arrival of both at the next barrier 3.3, first scores
+// 0.9, last PV 0.7.  All CUs pass through it at about the same time: 192 KB of Q and results per CU in
+// 9 us are 5.5 TB/s, so what is left of it is mostly HBM time.  Q and the results move in 64-byte
+// pieces, the sweep does not wait for the stores before it, and the claim travels under the last PV:
+// 24 x 16 384 on 570 keys 174 -> 166 us, 24 x 4 797 in bf16 268 -> 261, 24 x 9 600 921 -> 913.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 #include "attn_internal.h"
@@ -50,6 +53,8 @@
 namespace pda {
 
 constexpr int kTileRows = 256;       // query rows of a tile of the launch plan
+constexpr int kRawBuffer = 0x00027000;   // buffer descriptor of untyped data (bounds-checked by bytes)
+constexpr int kWaitVm0 = 0x0f70;     // s_waitcnt vmcnt(0), the other counters not waited for
 
 // LDS tile buffers per tensor (see the top of the file): four, or two where two workgroups of d = 128
 // share a CU's 160 KB.
@@ -100,7 +105,7 @@ __device__ __forceinline__ constexpr int swz_k(int row) { return D == 128 ? (row
 template <int D>
 __device__ __forceinline__ constexpr int swz_v(int row) { return D == 128 ? ((row & 3) << 2) : (((row >> 1) & 1) << 2); }
 
-template <int D, int NW, bool BASE2>
+template <int D, int NW, bool BASE2, bool OUT16>
 __global__ __launch_bounds__(64 * NW, 2) void attn_fwd_sp_kernel(const AttnParams p) {
     static_assert(D == 128 || D == 64, "head dimension");
     static_assert(NW == 8 || NW == 4, "wavefronts per workgroup");
@@ -117,6 +122,7 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_fwd_sp_kernel(const AttnParam
     constexpr int CHUNKS = TILE / 1024;   // DMA chunks of 1 KB per tile: 16 or 8
     constexpr int CPW = CHUNKS / NW;      // per wavefront: 2 (eight wavefronts) or 4 for d = 128, 1 or 2 for d = 64
     constexpr int RPC = 1024 / (D * 2);   // rows per chunk: 4 or 8
+    constexpr int kStores = (OUT16 ? 2 : 4) * NDB + 1;    // at least as many stores as an item's results take
     static_assert(CPW >= 1, "every wavefront fetches at least one chunk of a tile");
 
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
@@ -210,7 +216,9 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_fwd_sp_kernel(const AttnParam
         }
     };
 
-    // ---- Q operand fragments, resident for the whole sweep
+    // ---- Q operand fragments, resident for the whole sweep.  A fragment holds 16 bytes of each of 32 rows
+    // in either half of the wavefront; loaded as such, an instruction would touch 32 bytes in each of 32 rows.
+    // A pair (kk, kk + 1) is loaded as 64 bytes of each of 16 rows instead, rows 0-15 and then 16-31.
     bf16x8 qf[NKK];
     // Makes `it` the current item: its key range [kv0, kv1) (tile aligned; all keys, or range `part` of a
     // cut tile), its Q fragments and first K/V tiles on their way.
@@ -227,12 +235,30 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_fwd_sp_kernel(const AttnParam
         n_v = (int)(kv1 - kv0);
         nt = (n_v + BN - 1) / BN;
         const int l = opaque(lane);
-        int64_t row = (int64_t)q_tile * kTileRows + sub * M + wave * 32 + (l & 31);
-        row = row < Sq ? row : Sq - 1;
+        const int64_t row0 = (int64_t)q_tile * kTileRows + sub * M + wave * 32 + (l & 15);
 #pragma unroll
-        for (int kk = 0; kk < NKK; ++kk)
-            qf[kk] = *reinterpret_cast<const bf16x8*>(qp + row * D + kk * 16 + 8 * (l >> 5));
+        for (int r = 0; r < 2; ++r) {
+            const int64_t row = row0 + 16 * r < Sq ? row0 + 16 * r : Sq - 1;
+            const __bf16* src = qp + row * D + ((l >> 4) & 1) * 16 + 8 * (l >> 5);
+#pragma unroll
+            for (int kk = r; kk < NKK; kk += 2) qf[kk] = *reinterpret_cast<const bf16x8*>(src + (kk & ~1) * 16);
+        }
         issue_first_tiles();
+    };
+    // Once the loads have arrived: 16-lane rows of each pair trade places, which puts the fragments into MFMA order.
+    auto arrange_q = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int kk = 0; kk < NKK; kk += 2) {
+            u32x4 x = __builtin_bit_cast(u32x4, qf[kk]), y = __builtin_bit_cast(u32x4, qf[kk + 1]);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const auto r = __builtin_amdgcn_permlane16_swap(x[j], y[j], false, false);
+                x[j] = r[0];
+                y[j] = r[1];
+            }
+            qf[kk] = __builtin_bit_cast(bf16x8, x);
+            qf[kk + 1] = __builtin_bit_cast(bf16x8, y);
+        }
     };
 
     // ---- per-lane LDS operand addresses (loop invariant; buffer and block offsets are immediates)
@@ -251,6 +277,7 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_fwd_sp_kernel(const AttnParam
         v_ptr[db] = (LDS_PTR(const unsigned char))smem + (V_BASE + v_key_in * (D * 2) + g * 16 + (t16 & 1) * 8);
     }
 
+    int claimed = 0;
     float mc_run, l_run;     // reference max in exp2 units (max * scale * log2 e), lane's share of the running sum
     f32x16 o_acc[NDB];
     f32x16 nref;                         // BASE2, first sweep: minus the row's reference, as an accumulator seed
@@ -296,10 +323,11 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_fwd_sp_kernel(const AttnParam
             for (int r = 0; r < 16; ++r) o_acc[db][r] = 0.f;
         k_dma = kp + NBUF * BN * D;
         v_dma = vp + (NBUF - 2) * BN * D;
-        // the Q fragments (resident for both sweeps) and the item's first tiles have arrived
+        // The Q fragments (resident for both sweeps) and the item's first tiles have arrived.  They were
+        // requested before the previous item's stores, which need not have reached memory.
 #pragma unroll
         for (int kk = 0; kk < NKK; ++kk) asm volatile("" : "+v"(qf[kk]));
-        wait_vmcnt<0>();
+        if constexpr (SAFE) wait_vmcnt<0>(); else { wait_vmcnt<kStores>(); arrange_q(); }
         barrier();
 
         // ---- S_0 = K_0 Q^T (not overlapped with anything)
@@ -514,7 +542,8 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_fwd_sp_kernel(const AttnParam
 
             // Iteration t+1 reads K tile t+2 and V tile t.  With four buffers, what this iteration and the
             // previous one issued may still be in flight; with two, this iteration issued just those two tiles.
-            wait_vmcnt<NBUF == 4 ? 4 * CPW : 0>();
+            // In the first iteration of four-buffer sweeps both came with the item's first tiles.
+            if constexpr (!(FIRST && NBUF == 4)) wait_vmcnt<NBUF == 4 ? 4 * CPW : 0>();
             barrier();
         };
 
@@ -537,6 +566,12 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_fwd_sp_kernel(const AttnParam
             iteration(std::integral_constant<int, 3>{}, no{}, t + 2, s_b, s_a);
             if (t + 3 == nt) break;
             iteration(std::integral_constant<int, 0>{}, no{}, t + 3, s_a, s_b);
+        }
+        if constexpr (!SAFE) {      // claim the next item; the answer travels under the last products
+            // (a lane's own address: for a uniform one the compiler would broadcast the answer at once)
+            int lane0 = 0;
+            asm volatile("" : "+v"(lane0));
+            if (!direct && tid == 0) claimed = __hip_atomic_fetch_add((GLOBAL_PTR(int))p.counter + lane0, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
         // PV(nt-1): no scores are left to compute or to exponentiate
         {
@@ -566,14 +601,14 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_fwd_sp_kernel(const AttnParam
     auto locate = [&]() __attribute__((always_inline)) {
         decode(item);
         const bool cut = p.split > 1 && tile >= p.n_full;
-        const bool to_ws = part > 0 || (cut && p.out_bf16);
-        store_bf16 = p.out_bf16 && !to_ws;
+        const bool to_ws = part > 0 || (cut && OUT16);
+        store_bf16 = OUT16 && !to_ws;
         if (!to_ws) {
-            op = p.out + (p.out_bf16 ? 0 : (int64_t)b * p.o_bs + (int64_t)h * p.o_hs);
+            op = p.out + (OUT16 ? 0 : (int64_t)b * p.o_bs + (int64_t)h * p.o_hs);
             lp = p.lse + (int64_t)b * p.l_bs + (int64_t)h * p.l_hs;
             row_sub = 0;
         } else {
-            const int64_t slot = p.out_bf16 ? (int64_t)(tile - p.n_full) * p.split + part
+            const int64_t slot = OUT16 ? (int64_t)(tile - p.n_full) * p.split + part
                                             : (int64_t)(tile - p.n_full) * (p.split - 1) + (part - 1);
             op = p.part_out + slot * (kTileRows * D);
             lp = p.part_lse + slot * kTileRows;
@@ -582,31 +617,75 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_fwd_sp_kernel(const AttnParam
         oph = reinterpret_cast<__bf16*>(p.out) + (int64_t)b * p.o_bs + (int64_t)h * p.o_hs;
         q_row0 = (int64_t)q_tile * kTileRows + sub * M + wave * 32;
     };
-    // ---- epilogue: normalise, write out and lse (the lanes of `mask`)
+    // ---- epilogue: normalise, write out and lse (rows of the lanes in `mask`).  A lane holds 16-byte pieces
+    // of one row; stored as such, an instruction would write 32 bytes in each of 32 rows.  Neighbouring pieces
+    // trade places between the 16-lane rows (and, for bf16, the halves) of the wavefront first, so that an
+    // instruction writes 64 bytes in each of 16 rows.  Buffer stores: rows beyond Sq and rows outside the mask
+    // fall to the bounds check, so their number is the same on every path and the next sweep can wait for
+    // the loads that precede them without waiting for all of them.
     auto store_results = [&](uint64_t mask) __attribute__((always_inline)) {
-        const int lane_e = opaque(lane), li_e = lane_e & 31, lh_e = lane_e >> 5;
+        const int l = opaque(lane), l16 = l & 15, r16 = (l >> 4) & 1, half = l >> 5;
         const float l_tot = pair_sum(l_run);
         const float inv = 1.0f / l_tot;
-        const int64_t row = q_row0 + li_e;
-        if (row < Sq && __builtin_amdgcn_inverse_ballot_w64(mask)) {
+        const int64_t left = Sq - q_row0;
+        const int rows = left < 0 ? 0 : (left < 32 ? (int)left : 32);
+        constexpr int kOutside = 1 << 30;
+        const unsigned m32 = (unsigned)mask;
+        const bool ok0 = (m32 >> l16) & 1, ok1 = (m32 >> (16 + l16)) & 1;
+        if (OUT16 && store_bf16) {
+            const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(oph + q_row0 * D, 0, rows * (D * 2), kRawBuffer);
+            const int base = l16 * (D * 2) + r16 * 32 + half * 16;
+            const int off0 = ok0 ? base : kOutside, off1 = ok1 ? base + 16 * D * 2 : kOutside;
+#pragma unroll
+            for (int db = 0; db < NDB; ++db) {
+                u32x4 z[2];
+#pragma unroll
+                for (int m = 0; m < 2; ++m)          // 16 columns: the halves exchange their inner 4
+#pragma unroll
+                    for (int j = 0; j < 2; ++j) {
+                        const unsigned x = pack_bf16(o_acc[db][8 * m + 2 * j] * inv, o_acc[db][8 * m + 2 * j + 1] * inv);
+                        const unsigned y = pack_bf16(o_acc[db][8 * m + 4 + 2 * j] * inv, o_acc[db][8 * m + 5 + 2 * j] * inv);
+                        const auto r = __builtin_amdgcn_permlane32_swap(x, y, false, false);
+                        z[m][j] = r[0];
+                        z[m][2 + j] = r[1];
+                    }
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const auto r = __builtin_amdgcn_permlane16_swap(z[0][j], z[1][j], false, false);
+                    z[0][j] = r[0];
+                    z[1][j] = r[1];
+                }
+                __builtin_amdgcn_raw_buffer_store_b128(z[0], rsrc, off0 + db * 64, 0, 0);
+                __builtin_amdgcn_raw_buffer_store_b128(z[1], rsrc, off1 + db * 64, 0, 0);
+            }
+        } else {
+            const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(op + (q_row0 - row_sub) * D, 0, rows * (D * 4), kRawBuffer);
+            const int base = l16 * (D * 4) + r16 * 32 + half * 16;
+            const int off0 = ok0 ? base : kOutside, off1 = ok1 ? base + 16 * D * 4 : kOutside;
 #pragma unroll
             for (int db = 0; db < NDB; ++db)
 #pragma unroll
-                for (int a = 0; a < 4; ++a) {
-                    f32x4 o4 = {o_acc[db][4 * a] * inv, o_acc[db][4 * a + 1] * inv,
-                                o_acc[db][4 * a + 2] * inv, o_acc[db][4 * a + 3] * inv};
-                    if (store_bf16) {
-                        const u32x2 h2 = {pack_bf16(o4[0], o4[1]), pack_bf16(o4[2], o4[3])};
-                        *reinterpret_cast<u32x2*>(oph + row * D + db * 32 + a * 8 + 4 * lh_e) = h2;
-                    } else {
-                        *reinterpret_cast<f32x4*>(op + (row - row_sub) * D + db * 32 + a * 8 + 4 * lh_e) = o4;
+                for (int m = 0; m < 2; ++m) {
+                    u32x4 x, y;
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(o_acc[db][8 * m + j] * inv),
+                                                                        __float_as_uint(o_acc[db][8 * m + 4 + j] * inv), false, false);
+                        x[j] = r[0];
+                        y[j] = r[1];
                     }
+                    __builtin_amdgcn_raw_buffer_store_b128(x, rsrc, off0 + db * 128 + m * 64, 0, 0);
+                    __builtin_amdgcn_raw_buffer_store_b128(y, rsrc, off1 + db * 128 + m * 64, 0, 0);
                 }
-            if (lh_e == 0) lp[row - row_sub] = mc_run * 0.6931471805599453f + __logf(l_tot);
         }
+        const auto lse_rsrc = __builtin_amdgcn_make_buffer_rsrc(lp + (q_row0 - row_sub), 0, rows * 4, kRawBuffer);
+        const bool ok = half == 0 && ((m32 >> (l & 31)) & 1);
+        __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(mc_run * 0.6931471805599453f + __logf(l_tot)), lse_rsrc,
+                                              ok ? (l & 31) * 4 : kOutside, 0, 0);
     };
 
     if (item < p.n_items) begin_item(item);
+    __builtin_amdgcn_s_waitcnt(kWaitVm0);     // no stores follow the first item's loads
     while (item < p.n_items) {
     // The next item is claimed as late as possible (the order of the items balances the end of the
     // launch), but its Q and first tiles travel while this item's results are stored.
@@ -614,8 +693,6 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_fwd_sp_kernel(const AttnParam
     int next = p.n_items;
     uint64_t store_mask = ~0ull;                      // lanes whose results are still to be stored
     {
-        int claimed = p.n_items;
-        if (!direct && tid == 0) claimed = (int)gridDim.x + atomicAdd(p.counter, 1);
         // A row whose sum left the safe range (a later score exceeded the first tile's max by more
         // than ~2^64, or non-finite input) or whose accumulators are not finite takes its result from a
         // second sweep with the running max (weights <= 2^8 there).  The workgroup sweeps together, but
@@ -634,7 +711,7 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_fwd_sp_kernel(const AttnParam
         uint64_t redo = __builtin_amdgcn_ballot_w64(bad);
         redo |= redo << 32 | redo >> 32;             // lanes l and l + 32 hold one row
         if (lane == 0) redo_flag[wave] = redo != 0 ? 1 : 0;
-        if (tid == 0) next_item = claimed;
+        if (tid == 0) next_item = direct ? p.n_items : (int)gridDim.x + claimed;
         barrier();                                   // flags are written, and every wavefront is done with the LDS tiles
         int any = 0;
 #pragma unroll
@@ -720,9 +797,9 @@ __global__ __launch_bounds__(256) void tail_merge_kernel(const AttnParams p) {
 }
 
 // Launches the items of `p` (already planned) as workgroups of NW wavefronts.
-template <int D, int NW, bool BASE2>
+template <int D, int NW, bool BASE2, bool OUT16>
 static hipError_t launch_items(AttnParams p, int64_t items, int n_cu, hipStream_t st) {
-    auto kern = attn_fwd_sp_kernel<D, NW, BASE2>;
+    auto kern = attn_fwd_sp_kernel<D, NW, BASE2, OUT16>;
     constexpr int smem = 2 * sp_buffers(D, NW) * 64 * D * 2;       // 128 KB (d = 128, 8 wavefronts) or 64 KB
     constexpr int alone = 96 * 1024;                               // keeps a second workgroup off the CU
     static KernelSetup setup;
@@ -737,7 +814,7 @@ static hipError_t launch_items(AttnParams p, int64_t items, int n_cu, hipStream_
     return hipGetLastError();
 }
 
-template <int D, bool BASE2>
+template <int D, bool BASE2, bool OUT16>
 static hipError_t launch_sp(AttnParams p, int BH, float* ws, int64_t ws_slots, hipStream_t st) {
     int n_cu = 0;
     {
@@ -763,7 +840,7 @@ static hipError_t launch_sp(AttnParams p, int BH, float* ws, int64_t ws_slots, h
     p.counter = reinterpret_cast<int*>(ws + ws_slots * kSlotFloats);     // two ints behind the slots, zero between launches
     const int64_t items = p.n_full + t.n_cut * t.split;
     const bool four = sp_wavefronts(t, p.n_v, D, n_cu) == 4;
-    hipError_t e = four ? launch_items<D, 4, BASE2>(p, items, n_cu, st) : launch_items<D, 8, BASE2>(p, items, n_cu, st);
+    hipError_t e = four ? launch_items<D, 4, BASE2, OUT16>(p, items, n_cu, st) : launch_items<D, 8, BASE2, OUT16>(p, items, n_cu, st);
     if (e != hipSuccess || t.split <= 1) return e;
     hipLaunchKernelGGL(tail_merge_kernel<D>, dim3((unsigned)(t.n_cut * (kTileRows / (1024 / D)))), dim3(256), 0, st, p);
     return hipGetLastError();
@@ -771,16 +848,21 @@ static hipError_t launch_sp(AttnParams p, int BH, float* ws, int64_t ws_slots, h
 
 // Head dimension 64 is compiled by attn_fwd_sp_d64.hip, which includes this file with
 // PDA_SP_HEAD_DIM 64: the two sets of kernels then build side by side.
+template <int D>
+static hipError_t launch_sp_form(const AttnParams& p, int BH, float* ws, int64_t ws_slots, hipStream_t st) {
+    if (p.out_bf16) return p.base2 ? hipErrorInvalidValue : launch_sp<D, false, true>(p, BH, ws, ws_slots, st);
+    return p.base2 ? launch_sp<D, true, false>(p, BH, ws, ws_slots, st) : launch_sp<D, false, false>(p, BH, ws, ws_slots, st);
+}
+
 #ifndef PDA_SP_HEAD_DIM
 hipError_t launch_attn_fwd_sp_d64(const AttnParams& p, int BH, float* ws, int64_t ws_slots, hipStream_t st);
 
 hipError_t launch_attn_fwd_sp(const AttnParams& p, int BH, int D, float* ws, int64_t ws_slots, hipStream_t st) {
-    if (D == 64) return launch_attn_fwd_sp_d64(p, BH, ws, ws_slots, st);
-    return p.base2 ? launch_sp<128, true>(p, BH, ws, ws_slots, st) : launch_sp<128, false>(p, BH, ws, ws_slots, st);
+    return D == 64 ? launch_attn_fwd_sp_d64(p, BH, ws, ws_slots, st) : launch_sp_form<128>(p, BH, ws, ws_slots, st);
 }
 #else
 hipError_t launch_attn_fwd_sp_d64(const AttnParams& p, int BH, float* ws, int64_t ws_slots, hipStream_t st) {
-    return p.base2 ? launch_sp<64, true>(p, BH, ws, ws_slots, st) : launch_sp<64, false>(p, BH, ws, ws_slots, st);
+    return launch_sp_form<64>(p, BH, ws, ws_slots, st);
 }
 #endif
 
