@@ -58,10 +58,10 @@ Strides compact_strides(int H, int64_t Sq, int64_t Skv, int d) {
     return {(int64_t)H * Sq * d, Sq * d, (int64_t)H * Skv * d, Skv * d, (int64_t)H * Sq * d, Sq * d, (int64_t)H * Sq, Sq};
 }
 
-// Launch attention for hg heads of B batches; the pointers address the first of those heads.
+// Launch attention for n_groups groups of hg heads of B batches; the pointers address the first of those heads.
 // base2: the scores q.k are already in log2 units (scale is then ln 2 and is not applied again).
 hipError_t launch_strided(const void* q, const void* k, const void* v, float* out, float* lse,
-                          int B, int hg, int64_t Sq, int d, const Strides& s, float scale, int64_t n_v, hipStream_t st,
+                          int B, int hg, int n_groups, int64_t Sq, int d, const Strides& s, float scale, int64_t n_v, hipStream_t st,
                           int variant, bool base2, bool out_bf16, float* ws, int64_t ws_slots) {
     pda::AttnParams p{};
     p.q = static_cast<const __bf16*>(q);
@@ -76,6 +76,7 @@ hipError_t launch_strided(const void* q, const void* k, const void* v, float* ou
     p.o_hs = s.o_hs;   p.o_bs = s.o_bs;
     p.l_hs = s.l_hs;   p.l_bs = s.l_bs;
     p.Hg = hg;
+    p.n_groups = n_groups;
     p.scale = scale;
     // scale 0 is run with a tiny positive factor so that hidden keys (-inf scores) still get exp2(-inf) = 0
     p.scale_log2e = base2 ? 1.0f : std::fmax(scale * 1.4426950408889634f, 1e-37f);
@@ -176,7 +177,7 @@ enum WsKind { WS_CACHED, WS_STATIC };
 // Validated attention launch for hg heads of B batches with the workspace the launch needs.
 int launch_checked(const void* q, const void* k, const void* v, float* out, float* lse,
                    int B, int hg, int64_t Sq, int d, const Strides& s, float scale, int64_t n_v, hipStream_t st,
-                   int variant, bool base2, bool out_bf16, WsKind kind) {
+                   int variant, bool base2, bool out_bf16, WsKind kind, int n_groups = 1) {
     float* ws = nullptr;
     int64_t ws_slots = 0;
     if (out_bf16 && variant != 3) variant = 0;           // only the software-pipelined kernel writes bf16
@@ -185,7 +186,7 @@ int launch_checked(const void* q, const void* k, const void* v, float* out, floa
         hipError_t e = pda::device_cu_count(&n_cu);
         if (e != hipSuccess) return hip_fail(e, "device query");
         // every launch of this kernel uses a workspace: its work counters, and the partial slots of cut tiles
-        const int64_t need = pda::tail_slots(pda::plan_tail(Sq, B * hg, n_v, n_cu), out_bf16);
+        const int64_t need = n_groups * pda::tail_slots(pda::plan_tail(Sq, B * hg, n_v, n_cu), out_bf16);
         if (kind == WS_STATIC) {
             if (need > kStaticSlots)
                 return fail(PDA_ERR_UNSUPPORTED, "this launch needs %lld partial slots (%lld bytes) of scratch; the static buffer holds %lld (%lld bytes)",
@@ -202,7 +203,7 @@ int launch_checked(const void* q, const void* k, const void* v, float* out, floa
             ws_slots = w.slots;
         }
     }
-    hipError_t e = launch_strided(q, k, v, out, lse, B, hg, Sq, d, s, scale, n_v, st, variant, base2, out_bf16, ws, ws_slots);
+    hipError_t e = launch_strided(q, k, v, out, lse, B, hg, n_groups, Sq, d, s, scale, n_v, st, variant, base2, out_bf16, ws, ws_slots);
     if (e != hipSuccess) return hip_fail(e, "attention launch");
     return PDA_OK;
 }
@@ -211,15 +212,16 @@ int launch_checked(const void* q, const void* k, const void* v, float* out, floa
 
 namespace {
 
-// Launch attention for heads [h0, h0+hg) of compact [B,H,S,d] tensors.  Returns a pda_status.
+// Launch attention for heads [h0, h0 + n_groups*hg) of compact [B,H,S,d] tensors, n_groups groups of hg
+// heads in one launch.  Returns a pda_status.
 int launch_heads(const void* q, const void* k, const void* v, float* out, float* lse,
                  int B, int H, int64_t Sq, int64_t Skv, int d, float scale, int64_t n_v,
-                 int h0, int hg, hipStream_t st, int variant = 0, WsKind kind = WS_CACHED) {
+                 int h0, int hg, hipStream_t st, int variant = 0, WsKind kind = WS_CACHED, int n_groups = 1) {
     return launch_checked(static_cast<const __bf16*>(q) + (int64_t)h0 * Sq * d,
                           static_cast<const __bf16*>(k) + (int64_t)h0 * Skv * d,
                           static_cast<const __bf16*>(v) + (int64_t)h0 * Skv * d,
                           out + (int64_t)h0 * Sq * d, lse + (int64_t)h0 * Sq,
-                          B, hg, Sq, d, compact_strides(H, Sq, Skv, d), scale, n_v, st, variant, false, false, kind);
+                          B, hg, Sq, d, compact_strides(H, Sq, Skv, d), scale, n_v, st, variant, false, false, kind, n_groups);
 }
 
 // The head-chunk pipeline (Algorithm 1, steps 2-9) over the given groups; arguments already validated.
@@ -235,7 +237,7 @@ int run_pipeline(const void* q, const void* k, const void* v, float* out, float*
         const size_t bytes = (size_t)B * H * Sq * d * sizeof(float);
         if (o0 < s0 + bytes && s0 < o0 + bytes) return fail(PDA_ERR_INVALID_ARG, "sink must not overlap out");
     }
-    const int n_groups = (int)sizes.size();
+    const int n_groups = (int)sizes.size();        // entries of group_ms
     if (B == 0 || H == 0 || Sq == 0) {
         if (total_ms) *total_ms = 0.f;
         for (int g = 0; group_ms && g < n_groups; ++g) group_ms[g] = 0.f;
@@ -244,41 +246,60 @@ int run_pipeline(const void* q, const void* k, const void* v, float* out, float*
     hipStream_t cs = static_cast<hipStream_t>(compute_stream), ds = static_cast<hipStream_t>(drain_stream);
     const bool timed = group_ms != nullptr || total_ms != nullptr;
 
-    // Events: done[g] orders the hand-off of group g after its attention (Algorithm 1, steps 5-6);
-    // beg[g]/done[g] also time the group when timing is requested.
-    std::vector<hipEvent_t> done(n_groups, nullptr), beg(timed ? n_groups : 0, nullptr);
-    hipEvent_t drain_end = nullptr;
+    // Steps of the pipeline: one group each, or several equal small groups in one launch (see
+    // batch_of_groups) unless every group is to be timed.
+    struct Step { int h0, hg, groups; };
+    std::vector<Step> steps;
     hipError_t e = hipSuccess;
+    int n_cu = 0;
+    if ((e = pda::device_cu_count(&n_cu)) != hipSuccess) return hip_fail(e, "device query");
+    for (int g = 0, h0 = 0; g < n_groups;) {
+        int equal = 1, k = 1;
+        if (!group_ms) {
+            while (g + equal < n_groups && sizes[g + equal] == sizes[g]) ++equal;
+            k = pda::batch_of_groups(Sq, B * sizes[g], kv_valid_len, n_cu, equal);
+        }
+        steps.push_back({h0, sizes[g], k});
+        h0 += k * sizes[g];
+        g += k;
+    }
+    const int n_steps = (int)steps.size();
+
+    // Events: done[i] orders the hand-off of step i after its attention (Algorithm 1, steps 5-6);
+    // beg[i]/done[i] also time it when timing is requested (a step is a group then).
+    std::vector<hipEvent_t> done(n_steps, nullptr), beg(timed ? n_steps : 0, nullptr);
+    hipEvent_t drain_end = nullptr;
     const unsigned flags = timed ? hipEventDefault : hipEventDisableTiming;
     auto cleanup = [&]() {
         for (auto ev : done) if (ev) (void)hipEventDestroy(ev);
         for (auto ev : beg) if (ev) (void)hipEventDestroy(ev);
         if (drain_end) (void)hipEventDestroy(drain_end);
     };
-    for (int g = 0; g < n_groups && e == hipSuccess; ++g) {
-        e = hipEventCreateWithFlags(&done[g], flags);
-        if (e == hipSuccess && timed) e = hipEventCreateWithFlags(&beg[g], hipEventDefault);
+    for (int i = 0; i < n_steps && e == hipSuccess; ++i) {
+        e = hipEventCreateWithFlags(&done[i], flags);
+        if (e == hipSuccess && timed) e = hipEventCreateWithFlags(&beg[i], hipEventDefault);
     }
     if (e == hipSuccess && timed) e = hipEventCreateWithFlags(&drain_end, hipEventDefault);
     if (e != hipSuccess) { cleanup(); return hip_fail(e, "event creation"); }
 
     const int h_local = H / sp_ranks;
     int rc = PDA_OK;
-    for (int g = 0, h0 = 0; g < n_groups; h0 += sizes[g], ++g) {
-        const int hg = sizes[g];
-        if (timed && (e = hipEventRecord(beg[g], cs)) != hipSuccess) break;
-        if ((rc = launch_heads(q, k, v, out, lse, B, H, Sq, Skv, d, scale, kv_valid_len, h0, hg, cs)) != PDA_OK) break;
-        if ((e = hipEventRecord(done[g], cs)) != hipSuccess) break;
-        if ((e = hipStreamWaitEvent(ds, done[g], 0)) != hipSuccess) break;
+    for (int i = 0; i < n_steps; ++i) {
+        const int h0 = steps[i].h0, hs = steps[i].hg * steps[i].groups;
+        if (timed && (e = hipEventRecord(beg[i], cs)) != hipSuccess) break;
+        if ((rc = launch_heads(q, k, v, out, lse, B, H, Sq, Skv, d, scale, kv_valid_len, h0, steps[i].hg, cs, 0, WS_CACHED,
+                               steps[i].groups)) != PDA_OK) break;
+        if ((e = hipEventRecord(done[i], cs)) != hipSuccess) break;
+        if ((e = hipStreamWaitEvent(ds, done[i], 0)) != hipSuccess) break;
         if (sink) {
-            // hand-off of this group's result (step 7): its slice of out goes to the same slice of
+            // hand-off of the step's heads (step 7): their slice of out goes to the same slice of
             // sink, or into the token-major buffer at the head slots the layout asks for
             for (int b = 0; b < B && e == hipSuccess; ++b) {
                 const int64_t off = ((int64_t)b * H + h0) * Sq * d;
                 if (sink_layout == PDA_SINK_HEAD_MAJOR)
-                    e = pda::launch_copy_f32(out + off, sink + off, (int64_t)hg * Sq * d, ds);
+                    e = pda::launch_copy_f32(out + off, sink + off, (int64_t)hs * Sq * d, ds);
                 else
-                    e = pda::launch_scatter_heads(out + off, sink + (int64_t)b * Sq * H * d, Sq, d, hg, H, h0, h_local,
+                    e = pda::launch_scatter_heads(out + off, sink + (int64_t)b * Sq * H * d, Sq, d, hs, H, h0, h_local,
                                                   sp_ranks, sink_layout == PDA_SINK_TOKEN_ARRIVAL, ds);
             }
             if (e != hipSuccess) break;
@@ -294,9 +315,9 @@ int run_pipeline(const void* q, const void* k, const void* v, float* out, float*
     if (timed) {
         if ((e = hipStreamSynchronize(cs)) == hipSuccess) e = hipStreamSynchronize(ds);
         float ms = 0.f;
-        for (int g = 0; g < n_groups && e == hipSuccess; ++g) {
+        for (int g = 0; group_ms && g < n_groups && e == hipSuccess; ++g) {      // group g is step g
             e = hipEventElapsedTime(&ms, beg[g], done[g]);
-            if (group_ms) group_ms[g] = ms;
+            group_ms[g] = ms;
         }
         if (e == hipSuccess && total_ms) {
             e = hipEventElapsedTime(&ms, beg[0], drain_end);

@@ -310,10 +310,12 @@ static hipError_t launch_variant(const AttnParams& p, int BH, hipStream_t st) {
 
 hipError_t launch_attn_fwd(const AttnParams& p, int BH, int D, int variant, float* ws, int64_t ws_slots, hipStream_t st) {
     if (p.n_v == 0) {
+        if (p.n_groups > 1) return hipErrorInvalidValue;
         dim3 grid((unsigned)((p.Sq * D + 255) / 256 < 4096 ? (p.Sq * D + 255) / 256 : 4096), (unsigned)BH);
         hipLaunchKernelGGL(attn_empty_kernel, grid, dim3(256), 0, st, p, D);
         return hipGetLastError();
     }
+    if (p.n_groups > 1 && variant != 0 && variant != 3) return hipErrorInvalidValue;
     if (p.out_bf16 && variant != 3) variant = 0;                       // only the software-pipelined kernel writes bf16
     switch (variant) {
         case 1:                                                        // reference tiling, M=128, two workgroups per CU

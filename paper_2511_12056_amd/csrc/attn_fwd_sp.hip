@@ -149,7 +149,7 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_fwd_sp_kernel(const AttnParam
     const bool direct = p.n_items <= (int)gridDim.x;
     int item = (int)blockIdx.x;
 
-    // ---- work item -> (query tile, head, key range).  Items [0, n_full) are whole tiles; then the
+    // ---- work item -> (query tile, head, key range), inside the group of heads blockIdx.y.  Items [0, n_full) are whole tiles; then the
     // cut tiles' key ranges, range-major, so that the items in flight at any time sweep the same keys.
     int tile, part, b, h, q_tile, sub;
     auto decode = [&](int it) __attribute__((always_inline)) {
@@ -165,7 +165,7 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_fwd_sp_kernel(const AttnParam
         const int bh = tile / p.tiles_per_head;
         q_tile = tile - bh * p.tiles_per_head;
         b = bh / p.Hg;
-        h = bh - b * p.Hg;
+        h = bh - b * p.Hg + (int)blockIdx.y * p.Hg;
     };
 
     // ---- tile DMA: wavefront w fetches the 1 KB chunks w, w+NW, ... of a tile (4 key rows each).
@@ -608,8 +608,8 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_fwd_sp_kernel(const AttnParam
             lp = p.lse + (int64_t)b * p.l_bs + (int64_t)h * p.l_hs;
             row_sub = 0;
         } else {
-            const int64_t slot = OUT16 ? (int64_t)(tile - p.n_full) * p.split + part
-                                            : (int64_t)(tile - p.n_full) * (p.split - 1) + (part - 1);
+            const int64_t slot = (int)blockIdx.y * p.group_slots + (OUT16 ? (tile - p.n_full) * p.split + part
+                                                                          : (tile - p.n_full) * (p.split - 1) + (part - 1));
             op = p.part_out + slot * (kTileRows * D);
             lp = p.part_lse + slot * kTileRows;
             row_sub = (int64_t)q_tile * kTileRows;
@@ -756,13 +756,13 @@ __global__ __launch_bounds__(256) void tail_merge_kernel(const AttnParams p) {
     const int c4 = threadIdx.x % LPR;
     const int bh = tile / p.tiles_per_head;
     const int q_tile = tile - bh * p.tiles_per_head;
-    const int b = bh / p.Hg, h = bh - b * p.Hg;
+    const int b = bh / p.Hg, h = bh - b * p.Hg + (int)blockIdx.y * p.Hg;
     const int64_t row = (int64_t)q_tile * M + r_in;
     if (row >= p.Sq) return;
     float* lp = p.lse + (int64_t)b * p.l_bs + (int64_t)h * p.l_hs + row;
     // fp32 out: part 0 sits in out/lse and parts 1.. in the workspace; bf16 out: all parts in the workspace
     const int n_ws = p.out_bf16 ? p.split : p.split - 1;
-    const int64_t slot0 = (int64_t)(tile - p.n_full) * n_ws;
+    const int64_t slot0 = (int)blockIdx.y * p.group_slots + (tile - p.n_full) * n_ws;
     // one pass with a running reference (the parts of a cut tile are never empty: lse is finite)
     float m = -INFINITY, tot = 0.f;
     float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -809,8 +809,10 @@ static hipError_t launch_items(AttnParams p, int64_t items, int n_cu, hipStream_
     p.n_items = (int)items;
     // two workgroups of four wavefronts share a CU, unless there are not enough of them to fill every CU
     const int64_t slots = (int64_t)n_cu * (NW == 8 ? 1 : 2);
-    const int lds = NW < 8 && items <= n_cu ? alone : smem;
-    hipLaunchKernelGGL(kern, dim3((unsigned)(items < slots ? items : slots)), dim3(64 * NW), lds, st, p);
+    const int lds = NW < 8 && items * p.n_groups <= n_cu ? alone : smem;
+    // several groups: one workgroup per item (they fit the chip at once), no chains and no counter
+    if (p.n_groups > 1 && items * p.n_groups > slots) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(kern, dim3((unsigned)(items < slots ? items : slots), (unsigned)p.n_groups), dim3(64 * NW), lds, st, p);
     return hipGetLastError();
 }
 
@@ -822,7 +824,8 @@ static hipError_t launch_sp(AttnParams p, int BH, float* ws, int64_t ws_slots, h
         if (e != hipSuccess) return e;
     }
     const TailPlan t = plan_tail(p.Sq, BH, p.n_v, n_cu);
-    const int64_t slots = tail_slots(t, p.out_bf16 != 0);
+    p.group_slots = (int)tail_slots(t, p.out_bf16 != 0);
+    const int64_t slots = (int64_t)p.group_slots * p.n_groups;
     if (ws == nullptr || slots > ws_slots) return hipErrorInvalidValue;
     // no key range may be empty or start off a 64-key boundary
     if (t.split > 1) {
@@ -842,7 +845,7 @@ static hipError_t launch_sp(AttnParams p, int BH, float* ws, int64_t ws_slots, h
     const bool four = sp_wavefronts(t, p.n_v, D, n_cu) == 4;
     hipError_t e = four ? launch_items<D, 4, BASE2, OUT16>(p, items, n_cu, st) : launch_items<D, 8, BASE2, OUT16>(p, items, n_cu, st);
     if (e != hipSuccess || t.split <= 1) return e;
-    hipLaunchKernelGGL(tail_merge_kernel<D>, dim3((unsigned)(t.n_cut * (kTileRows / (1024 / D)))), dim3(256), 0, st, p);
+    hipLaunchKernelGGL(tail_merge_kernel<D>, dim3((unsigned)(t.n_cut * (kTileRows / (1024 / D))), (unsigned)p.n_groups), dim3(256), 0, st, p);
     return hipGetLastError();
 }
 

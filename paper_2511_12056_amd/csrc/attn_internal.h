@@ -44,7 +44,9 @@ struct AttnParams {
     int64_t kv_bs, kv_hs;   // k and v batch / head stride
     int64_t o_bs, o_hs;     // out batch / head stride
     int64_t l_bs, l_hs;     // lse batch / head stride
-    int Hg;                 // heads in this launch
+    int Hg;                 // heads of a group
+    int n_groups;           // groups of Hg heads, one after the other, each with the same plan: grid.y (1: the launch is one group)
+    int group_slots;        // workspace slots of a group
     float scale;            // softmax scale
     float scale_log2e;      // scale * log2(e)
     // Work items of the software-pipelined kernel, taken in index order by persistent workgroups.
@@ -61,8 +63,8 @@ struct AttnParams {
     int64_t part_off[17];   // first key of each range (multiples of 64); part_off[split] = n_v
     float* part_out;        // [(tile - n_full) * (split - 1) + part - 1][256][d]
     float* part_lse;        // [(tile - n_full) * (split - 1) + part - 1][256]
-    int n_cut;              // number of cut tiles (the last n_cut of the launch)
-    int n_items;            // n_full + n_cut * split, twice that with four wavefronts (set by the launch)
+    int n_cut;              // number of cut tiles (the last n_cut of a group)
+    int n_items;            // n_full + n_cut * split per group, twice that with four wavefronts (set by the launch)
     int* counter;           // two ints, zero between launches: items taken beyond each workgroup's first, workgroups that have finished
     int out_bf16;           // software-pipelined kernel: `out` points to bf16 elements (same element strides)
     int base2;              // scores are already in log2 units: weights 2^(q.k), scale_log2e == 1
@@ -211,6 +213,20 @@ inline int sp_wavefronts(const TailPlan& t, int64_t n_v, int d, int n_cu) {
     if (d == 128) return six_rounds || key_tiles >= 4 ? 4 : 8;
     const int64_t rem = t.n_tiles % n_cu;
     return key_tiles >= 8 && (six_rounds || (rem > 0 && 2 * rem <= n_cu)) ? 4 : 8;
+}
+// Head groups of a pipeline that share a launch: `left` groups of BH (batch, head) pairs each remain.
+// A group whose half tiles do not fill every CU (the four-wavefront rule above) leaves most of the chip idle,
+// and its launch, merge, event and hand-off cost the host more than the GPU.  As many such groups as fill
+// the chip once, two workgroups per CU, go out as one launch, each with the plan and so the bits it has
+// alone; their hand-off waits for that one launch.  24 x 2 048, d = 128, head by head (8 items a group,
+// batches of eight): 680 -> 151 us, host time.  From one item per CU on, a group fills the chip by itself.
+inline int batch_of_groups(int64_t Sq, int BH, int64_t n_v, int n_cu, int left) {
+    if (n_v <= 0 || left < 2) return 1;
+    const TailPlan t = plan_tail(Sq, BH, n_v, n_cu);
+    const int64_t items = t.n_tiles + t.n_cut * (t.split - 1);
+    if (2 * items > n_cu) return 1;
+    const int64_t fit = n_cu / items;
+    return (int)(fit < left ? fit : left);
 }
 // One workspace slot holds one key-range partial of a cut tile: 256 x 128 values + 256 lse.
 // A workspace of n slots is n * kSlotFloats floats followed by kCounterFloats floats that hold the
