@@ -31,14 +31,21 @@
 // would sum two rounded ones at a time, occupy the matrix pipe and stall the MFMA stream.
 //
 // K/V tiles go from global memory straight into LDS (global_load_lds_dwordx4), NBUF buffers per tensor
-// (four; two for d = 128 with four wavefronts, so that two workgroups fit the CU's LDS); the loop is
-// unrolled four times so that every buffer offset is an immediate.  At the top of iteration t a
+// (four; two for d = 128 with four wavefronts, so that two workgroups fit the CU's LDS); the main loop is
+// unrolled four times so that every buffer offset is an immediate, and runs as long as all tiles that a
+// group of four fetches are whole.  What is left goes through one iteration whose operand bases are moved
+// instead; it knows the ragged tile, hidden keys and that nothing is fetched beyond the last tile.  The last
+// tile has no further scores to compute and carries its own PV.  With one form of iteration for all of it
+// (branches in every copy, scores of a tile beyond the end, PV of the last tile by itself) the last three
+// iterations of a sweep took 0.3, 0.5 and 1.8 us longer than the others (d = 128, two workgroups per CU), and
+// every copy of the loop body was 780 instructions instead of 550: 24 x 16 384 on 570 keys 166 -> 161 us,
+// 24 x 9 600 -1.7 %, 3 x 67 576 -1.1 %, d = 64, 6 x 67 576 -2.7 %.  At the top of iteration t a
 // wavefront issues its share of K tile t+NBUF (over K tile t) and V tile t+NBUF-2 (over V tile t-2),
 // both last read in iteration t-1; before the barrier that closes the iteration it waits for K tile
 // t+2 and V tile t, which iteration t+1 reads: with four buffers all but its two newest batches.
 //
 // Between items nothing but the claim of the next one is serial: its Q fragments and first tiles are
-// fetched while the results are stored.  The first iteration carries no PV and the last PV no softmax.
+// fetched while the results are stored.
 // What an item costs besides its key tiles (24 heads x 9 600, eight wavefronts, timestamps): claim 0.6 us,
 // issue of the next item's loads 2.9, stores 2.9, arrival of both at the next barrier 3.3, first scores
 // 0.9, last PV 0.7.  All CUs pass through it at about the same time: 192 KB of Q and results per CU in
@@ -104,6 +111,8 @@ template <int D>
 __device__ __forceinline__ constexpr int swz_k(int row) { return D == 128 ? (row & 15) : ((row >> 1) & 7); }
 template <int D>
 __device__ __forceinline__ constexpr int swz_v(int row) { return D == 128 ? ((row & 3) << 2) : (((row >> 1) & 1) << 2); }
+
+enum class Iter { MAIN, FIRST, TAIL, LAST };      // forms of an iteration of the sweep
 
 template <int D, int NW, bool BASE2, bool OUT16>
 __global__ __launch_bounds__(64 * NW, 2) void attn_fwd_sp_kernel(const AttnParams p) {
@@ -186,21 +195,21 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_fwd_sp_kernel(const AttnParam
         ld_v[j] = row_off + granule_off(lane, j, false);
     }
     const unsigned dma_base = lds0 + wave * 1024;
-    const __bf16* k_dma = nullptr;                    // K tile t+NBUF and V tile t+NBUF-2 of the coming iteration
+    const __bf16* k_dma = nullptr;                    // main loop: K tile t+NBUF and V tile t+NBUF-2 of the coming iteration
     const __bf16* v_dma = nullptr;
-    // this wavefront's share (chunks 0..CPW-1) of a tile of K or V
+    // this wavefront's share (chunks 0..CPW-1) of a tile of K or V, tile < nt
     auto issue_tile = [&](const __bf16* base, bool is_k, unsigned lds_tile, int tile) __attribute__((always_inline)) {
+        const __bf16* src = base + (int64_t)tile * BN * D;
+        const int rows = n_v - tile * BN;
+        if (rows >= BN) {                             // whole tile valid
 #pragma unroll
-        for (int j = 0; j < CPW; ++j) {
-            const unsigned dst = dma_base + lds_tile + j * (NW * 1024);
-            if ((tile + 1) * BN <= n_v) {             // whole tile valid
-                lds_dma16(base + (int64_t)tile * BN * D, is_k ? ld_k[j] : ld_v[j], dst);
-            } else {                                  // tail or beyond: rows clamped to the last valid key
-                const int l = opaque(lane);
-                const int tb = tile < nt ? tile : nt - 1;
-                int row = tile * BN + wave * RPC + l / G + j * (NW * RPC);
-                row = row < n_v ? row : n_v - 1;      // hidden / out-of-range keys are never read
-                lds_dma16(base + (int64_t)tb * BN * D, (unsigned)(row - tb * BN) * (D * 2) + granule_off(l, j, is_k), dst);
+            for (int j = 0; j < CPW; ++j) lds_dma16(src, is_k ? ld_k[j] : ld_v[j], dma_base + lds_tile + j * (NW * 1024));
+        } else {                                      // rows clamped to the last valid key: hidden keys are never read
+            const int l = opaque(lane);
+#pragma unroll
+            for (int j = 0; j < CPW; ++j) {
+                const int row = wave * RPC + l / G + j * (NW * RPC);
+                lds_dma16(src, (unsigned)(row < rows ? row : rows - 1) * (D * 2) + granule_off(l, j, is_k), dma_base + lds_tile + j * (NW * 1024));
             }
         }
     };
@@ -298,6 +307,27 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_fwd_sp_kernel(const AttnParam
                 }
             }
     };
+    // The operand bases normally point at buffer 0; a tail moves them to the buffer it reads.
+    int k_at = 0, v_at = 0;
+    auto move_k = [&](int off) __attribute__((always_inline)) {
+#pragma unroll
+        for (int kk = 0; kk < NKK; ++kk) k_ptr[kk] += off - k_at;
+        k_at = off;
+    };
+    auto move_v = [&](int off) __attribute__((always_inline)) {
+#pragma unroll
+        for (int db = 0; db < NDB; ++db) v_ptr[db] += off - v_at;
+        v_at = off;
+    };
+    // rescales O if some lane moved its reference (rare after the first tiles)
+    auto rescale = [&](float alpha) __attribute__((always_inline)) {
+        if (__builtin_amdgcn_ballot_w64(alpha != 1.0f) != 0) {
+#pragma unroll
+            for (int db = 0; db < NDB; ++db)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) o_acc[db][r] *= alpha;
+        }
+    };
     auto barrier = [&]() __attribute__((always_inline)) {
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
         __builtin_amdgcn_s_barrier();
@@ -317,12 +347,15 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_fwd_sp_kernel(const AttnParam
         for (int db = 0; db < NDB; ++db) asm volatile("" : "+v"(v_ptr[db]));
         mc_run = -INFINITY;
         l_run = 0.f;
+        // (an opaque zero: the compiler would keep a register vector of constant zeros for all items)
+        float zero_o = 0.f;
+        asm volatile("" : "+v"(zero_o));
 #pragma unroll
         for (int db = 0; db < NDB; ++db)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) o_acc[db][r] = 0.f;
-        k_dma = kp + NBUF * BN * D;
-        v_dma = vp + (NBUF - 2) * BN * D;
+            for (int r = 0; r < 16; ++r) o_acc[db][r] = zero_o;
+        k_dma = kp + (1 + NBUF) * BN * D;
+        v_dma = vp + (NBUF - 1) * BN * D;
         // The Q fragments (resident for both sweeps) and the item's first tiles have arrived.  They were
         // requested before the previous item's stores, which need not have reached memory.
 #pragma unroll
@@ -366,17 +399,21 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_fwd_sp_kernel(const AttnParam
         // i (first the PV fragments, then as many QK fragments), the LDS reads of fragment i+PF, and slice i
         // of the softmax VALU work: slices 0-3 the row max, 4-5 the reference / rescale factors, the others
         // the 32 exponentials with their packing to bf16 and the row sum.
+        //   MAIN:  every tile it fetches is whole: running scalar tile pointers, fixed per-lane offsets, LDS
+        //          destinations as immediates, no hidden keys
         //   FIRST: t = 0, no PV yet (its slots hold softmax work only)
-        auto iteration = [&](auto tb_c, auto first_c, int t, f32x16 (&s_c)[NKB], f32x16 (&s_n)[NKB]) {
+        //   TAIL:  any t with a tile t+1; operand bases moved to the tiles it reads (TB is not used)
+        //   LAST:  t = nt-1 >= 1: no scores are left to compute, PV(t) takes the place of QK(t+1)
+        auto iteration = [&](auto tb_c, auto kind_c, int t, f32x16 (&s_c)[NKB], f32x16 (&s_n)[NKB]) {
             constexpr int TB = decltype(tb_c)::value;
-            constexpr bool FIRST = decltype(first_c)::value;
-            constexpr int KN = (TB + 1) % NBUF;           // buffer of K tile t+1
-            constexpr int VP = (TB + 3) % NBUF;           // buffer of V tile t-1
-            constexpr int KD = TB % NBUF, VD = (TB + NBUF - 2) % NBUF;     // buffers this iteration fills
+            constexpr Iter KIND = decltype(kind_c)::value;
+            constexpr bool FIRST = KIND == Iter::FIRST, LAST = KIND == Iter::LAST, MOVED = KIND == Iter::TAIL || LAST;
+            constexpr int KN = MOVED ? 0 : (TB + 1) % NBUF;           // buffer of K tile t+1
+            constexpr int VP = MOVED ? 0 : (TB + 3) % NBUF;           // buffer of V tile t-1
             // DMA of this iteration: K tile t+NBUF over K tile t, V tile t+NBUF-2 over V tile t-2 (both last
-            // read in iteration t-1).  Whole tiles take the short path: running scalar tile pointers, fixed
-            // per-lane offsets, LDS destinations as immediates.
-            if ((t + NBUF + 1) * BN <= n_v) {
+            // read in iteration t-1).
+            if constexpr (KIND == Iter::MAIN) {
+                constexpr int KD = TB % NBUF, VD = (TB + NBUF - 2) % NBUF;
                 static_for<0, CPW>([&](auto jc) {
                     constexpr int j = decltype(jc)::value;
                     lds_dma16_at<K_BASE + KD * TILE + j * (NW * 1024)>(k_dma, ld_k[j], dma_base);
@@ -385,15 +422,24 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_fwd_sp_kernel(const AttnParam
                     constexpr int j = decltype(jc)::value;
                     lds_dma16_at<V_BASE + VD * TILE + j * (NW * 1024)>(v_dma, ld_v[j], dma_base);
                 });
+                k_dma += BN * D;
+                v_dma += BN * D;
             } else {
-                issue_tile(kp, true, K_BASE + KD * TILE, t + NBUF);
-                issue_tile(vp, false, V_BASE + VD * TILE, t + NBUF - 2);
+                if (!LAST && t + NBUF < nt) issue_tile(kp, true, K_BASE + (t % NBUF) * TILE, t + NBUF);
+                if ((!LAST || NBUF == 2) && t + NBUF - 2 < nt) issue_tile(vp, false, V_BASE + ((t + NBUF - 2) % NBUF) * TILE, t + NBUF - 2);
             }
-            k_dma += BN * D;
-            v_dma += BN * D;
+            if constexpr (KIND == Iter::TAIL) move_k(((t + 1) % NBUF) * TILE);
+            if constexpr (MOVED) move_v(((t - 1) % NBUF) * TILE);
+            LDS_PTR(const unsigned char) v_last[NDB];                 // LAST: V tile t
+            if constexpr (LAST) {
+                const int off = (t % NBUF) * TILE - v_at;
+#pragma unroll
+                for (int db = 0; db < NDB; ++db) v_last[db] = v_ptr[db] + off;
+            }
             constexpr int N_PV = NKB * 2 * NDB, N_QK = NKK * NKB, N_FR = N_PV + N_QK;
             constexpr int PF = 3, RING = 4;
             static_assert(N_FR == 32 || N_FR == 16, "slot plan below is written for 64-key tiles and d = 128 or 64");
+            static_assert(N_PV == N_QK, "PV fragments of the last tile take the slots of QK fragments");
             bf16x8 frag[RING];
 
             auto load_frag = [&](auto idx) {
@@ -407,6 +453,12 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_fwd_sp_kernel(const AttnParam
                     typedef short s16x8 __attribute__((ext_vector_type(8)));
                     const s16x8 av = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
                     frag[i % RING] = __builtin_bit_cast(bf16x8, av);
+                } else if constexpr (i < N_FR && LAST) {
+                    constexpr int n = i - N_PV, kb = n / (2 * NDB), u = (n / NDB) % 2, db = n % NDB;
+                    constexpr int off0 = (kb * 32 + u * 16) * (D * 2);
+                    const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LDS_PTR(s16x4))(v_last[db] + off0));
+                    const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LDS_PTR(s16x4))(v_last[db] + off0 + 8 * (D * 2)));
+                    frag[i % RING] = __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
                 } else if constexpr (i < N_FR) {
                     constexpr int j = i - N_PV, kk = j / 2, kb = j % 2;
                     frag[i % RING] = *(LDS_PTR(const bf16x8))(k_ptr[kk] + (KN * TILE + kb * 32 * (D * 2)));
@@ -415,8 +467,8 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_fwd_sp_kernel(const AttnParam
             auto do_mfma = [&](auto idx) {
                 constexpr int i = decltype(idx)::value;
                 if constexpr (i < N_PV && FIRST) {
-                } else if constexpr (i < N_PV) {
-                    constexpr int kb = i / (2 * NDB), u = (i / NDB) % 2, db = i % NDB;
+                } else if constexpr (i < N_PV || LAST) {
+                    constexpr int n = i % N_PV, kb = n / (2 * NDB), u = (n / NDB) % 2, db = n % NDB;
                     const u32x4 pv = {p_io[kb][u][0], p_io[kb][u][1], p_io[kb][u][2], p_io[kb][u][3]};
                     o_acc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag[i % RING], __builtin_bit_cast(bf16x8, pv), o_acc[db], 0, 0, 0);
                 } else {
@@ -442,8 +494,20 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_fwd_sp_kernel(const AttnParam
             // exponentials start at slot 3 (not earlier: the packed pair q of this tile may replace that of
             // the previous tile only after the PV MFMAs of its group, which come d/32 slots per group in
             // the first half of the slots, have read it).
-            constexpr int X0 = SAFE ? 6 : 3, NX = N_FR - X0;
+            // LAST: the exponentials end early enough for PV(t), whose group g of 8 weights comes d/32 slots per
+            // group into the second half.
+            constexpr int X0 = SAFE ? 6 : 3;
+            constexpr int NX = !LAST ? N_FR - X0 : N_FR == 32 ? (SAFE ? 20 : 23) : (SAFE ? 4 : 9);
             auto e_lo = [](int k) constexpr { return k <= 0 ? 0 : (k >= NX ? 32 : k * 32 / NX); };
+            static_assert([](auto lo) constexpr {
+                for (int k = 0; k < NX; ++k)
+                    for (int e = lo(k); e < lo(k + 1); ++e) {
+                        const int packed = X0 + k + 1, g = e / 8;           // slot that packs element e of group g
+                        if (e % 2 && packed < NDB * g + NDB - 1) return false;                  // PV(t-1) has read the group
+                        if (LAST && packed >= N_PV + NDB * g) return false;                     // PV(t) has not
+                    }
+                return true;
+            }(e_lo), "slots of the exponentials");
             auto fma_of = [&](auto kc) {
                 constexpr int k = decltype(kc)::value;
                 if constexpr (BASE2 && !SAFE) return;             // the MFMA output already is s - reference
@@ -516,13 +580,22 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_fwd_sp_kernel(const AttnParam
             });
             static_for<0, N_FR>([&](auto idx) {
                 constexpr int i = decltype(idx)::value;
+                if constexpr (LAST && i == N_PV) {
+                    if constexpr (SAFE) rescale(alpha);
+                    if constexpr (NBUF == 2) {      // V tile t was fetched in this iteration
+                        wait_vmcnt<0>();
+                        barrier();
+                        static_for<0, PF>([&](auto j) { load_frag(std::integral_constant<int, N_PV + decltype(j)::value>{}); });
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+                }
                 do_mfma(idx);
-                load_frag(std::integral_constant<int, i + PF>{});
+                if constexpr (!(LAST && NBUF == 2 && i < N_PV && i + PF >= N_PV)) load_frag(std::integral_constant<int, i + PF>{});
                 __builtin_amdgcn_sched_barrier(0);       // the reads go first: they are on the path of slot i + PF
                 valu_slice(idx);
                 __builtin_amdgcn_sched_barrier(0);
             });
-            sum_pack_of(std::integral_constant<int, NX - 1>{});
+            if constexpr (X0 + NX == N_FR) sum_pack_of(std::integral_constant<int, NX - 1>{});
             if constexpr (SAFE) {
                 l_run = __builtin_fmaf(l_run, alpha, lsum + lsum2);
                 mc_run = mc_new;
@@ -531,41 +604,55 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_fwd_sp_kernel(const AttnParam
             }
             // =====================================================================================
 
-            // rescale O once PV(t-1) is in, if some lane moved its reference (rare after the first tiles)
-            if (SAFE && __builtin_amdgcn_ballot_w64(alpha != 1.0f) != 0) {
-#pragma unroll
-                for (int db = 0; db < NDB; ++db)
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) o_acc[db][r] *= alpha;
-            }
-            if ((t + 2) * BN > n_v) mask_tail(s_n, t + 1);     // S_{t+1} holds hidden keys
+            if constexpr (LAST) return;
+            if constexpr (SAFE) rescale(alpha);       // once PV(t-1) is in
+            if constexpr (KIND != Iter::MAIN)
+                if ((t + 2) * BN > n_v) mask_tail(s_n, t + 1);     // S_{t+1} holds hidden keys
 
-            // Iteration t+1 reads K tile t+2 and V tile t.  With four buffers, what this iteration and the
-            // previous one issued may still be in flight; with two, this iteration issued just those two tiles.
-            // In the first iteration of four-buffer sweeps both came with the item's first tiles.
-            if constexpr (!(FIRST && NBUF == 4)) wait_vmcnt<NBUF == 4 ? 4 * CPW : 0>();
+            // Iteration t+1 reads K tile t+2 and V tile t; the last one, t+1 = nt-1, V tiles t and t+1.  With four
+            // buffers, what this iteration and the previous one issued may still be in flight (two batches of K and
+            // V, in a tail fewer); with two, this iteration issued just the tiles that are wanted.  In the first
+            // iteration of four-buffer sweeps all of them came with the item's first tiles.
+            if constexpr (NBUF == 2 || KIND == Iter::MAIN) {
+                wait_vmcnt<NBUF == 4 ? 4 * CPW : 0>();
+            } else if constexpr (KIND == Iter::TAIL) {
+                if (nt - t > 4) wait_vmcnt<4 * CPW>();
+                else if (nt - t == 4) wait_vmcnt<3 * CPW>();
+                else if (nt - t == 3) wait_vmcnt<2 * CPW>();
+                else wait_vmcnt<0>();
+            }
             barrier();
         };
 
-        // Tiles 0 .. nt-1, unrolled by four so that buffer offsets are immediates and the score /
-        // probability registers alternate roles without copies; the first is peeled off (no PV yet) and
-        // the loop is left right after the last, wherever in the group of four that falls.
-        using no = std::false_type;
+        // Tiles 0 .. nt-1: the first and the last peeled off, groups of four (buffer offsets are immediates and the
+        // score / probability registers alternate roles without copies) as long as all tiles they fetch are whole,
+        // and what is left one at a time.
         auto pin_o = [&]() {       // keeps the zeroed accumulators in registers (a constant would be copied at every exit)
 #pragma unroll
             for (int db = 0; db < NDB; ++db) asm volatile("" : "+v"(o_acc[db]));
         };
+        auto run = [&](auto tb_c, auto kind_c, int t, f32x16 (&s_c)[NKB], f32x16 (&s_n)[NKB]) __attribute__((always_inline)) {
+            iteration(tb_c, kind_c, t, s_c, s_n);
+        };
+        constexpr std::integral_constant<Iter, Iter::MAIN> MAIN{};
+        constexpr std::integral_constant<int, 0> B0{};
+        constexpr std::integral_constant<int, 1> B1{};
+        constexpr std::integral_constant<int, 2> B2{};
+        constexpr std::integral_constant<int, 3> B3{};
         pin_o();
-        iteration(std::integral_constant<int, 0>{}, std::true_type{}, 0, s_a, s_b);
+        run(B0, std::integral_constant<Iter, Iter::FIRST>{}, 0, s_a, s_b);
         pin_o();
-        for (int t = 1; t < nt; t += 4) {
-            iteration(std::integral_constant<int, 1>{}, no{}, t, s_b, s_a);
-            if (t + 1 == nt) break;
-            iteration(std::integral_constant<int, 2>{}, no{}, t + 1, s_a, s_b);
-            if (t + 2 == nt) break;
-            iteration(std::integral_constant<int, 3>{}, no{}, t + 2, s_b, s_a);
-            if (t + 3 == nt) break;
-            iteration(std::integral_constant<int, 0>{}, no{}, t + 3, s_a, s_b);
+        int t = 1;
+        for (const int whole = n_v / BN; t + NBUF + 4 <= whole; t += 4) {
+            run(B1, MAIN, t, s_b, s_a);
+            run(B2, MAIN, t + 1, s_a, s_b);
+            run(B3, MAIN, t + 2, s_b, s_a);
+            run(B0, MAIN, t + 3, s_a, s_b);
+        }
+        for (; t < nt - 1; ++t) {
+            run(B0, std::integral_constant<Iter, Iter::TAIL>{}, t, s_b, s_a);
+#pragma unroll
+            for (int kb = 0; kb < NKB; ++kb) s_b[kb] = s_a[kb];
         }
         if constexpr (!SAFE) {      // claim the next item; the answer travels under the last products
             // (a lane's own address: for a uniform one the compiler would broadcast the answer at once)
@@ -573,13 +660,13 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_fwd_sp_kernel(const AttnParam
             asm volatile("" : "+v"(lane0));
             if (!direct && tid == 0) claimed = __hip_atomic_fetch_add((GLOBAL_PTR(int))p.counter + lane0, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
-        // PV(nt-1): no scores are left to compute or to exponentiate
-        {
-            const int voff = ((nt - 1) % NBUF) * TILE;
+        if (nt > 1) {
+            run(B0, std::integral_constant<Iter, Iter::LAST>{}, t, s_b, s_a);
+        } else {                    // a single tile: its PV alone
 #pragma unroll
             for (int i = 0; i < NKB * 2 * NDB; ++i) {
                 const int kb = i / (2 * NDB), u = (i / NDB) % 2, db = i % NDB;
-                LDS_PTR(const unsigned char) a = v_ptr[db] + voff + (kb * 32 + u * 16) * (D * 2);
+                LDS_PTR(const unsigned char) a = v_ptr[db] + (kb * 32 + u * 16) * (D * 2);
                 const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LDS_PTR(s16x4))a);
                 const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LDS_PTR(s16x4))(a + 8 * (D * 2)));
                 const bf16x8 av = __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
@@ -587,7 +674,8 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_fwd_sp_kernel(const AttnParam
                 o_acc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av, __builtin_bit_cast(bf16x8, pv), o_acc[db], 0, 0, 0);
             }
         }
-        wait_vmcnt<0>();        // no DMA may land in the tiles of the next item or outlive the workgroup's LDS
+        move_k(0);
+        move_v(0);
     };
 
     // ---- where the results of `item` go: part 0 writes the tile's rows of out/lse; later parts write
