@@ -44,14 +44,14 @@
 // both last read in iteration t-1; before the barrier that closes the iteration it waits for K tile
 // t+2 and V tile t, which iteration t+1 reads: with four buffers all but its two newest batches.
 //
-// Between items nothing but the claim of the next one is serial: its Q fragments and first tiles are
-// fetched while the results are stored.
-// What an item costs besides its key tiles (24 heads x 9 600, eight wavefronts, timestamps): claim 0.6 us,
-// issue of the next item's loads 2.9, stores 2.9, arrival of both at the next barrier 3.3, first scores
-// 0.9, last PV 0.7.  All CUs pass through it at about the same time: 192 KB of Q and results per CU in
-// 9 us are 5.5 TB/s, so what is left of it is mostly HBM time.  Q and the results move in 64-byte
-// pieces, the sweep does not wait for the stores before it, and the claim travels under the last PV:
-// 24 x 16 384 on 570 keys 174 -> 166 us, 24 x 4 797 in bf16 268 -> 261, 24 x 9 600 921 -> 913.
+// Between items: the next one is claimed in the last iteration but one; its Q fragments and first K tiles are
+// fetched under the last iteration, which computes no scores and so needs neither the registers of Q nor the
+// buffers of K (before that, together with the stores: 24 x 16 384 on 570 keys 156.7 -> 155.5 us, on 192 keys
+// 102 -> 98, 26 x 10 100 on 866 keys 145 -> 143, 24 x 9 600 920 -> 917); its V tiles follow with the stores.
+// All CUs pass through it at about the same time: 192 KB of Q and results per CU in 9 us are 5.5 TB/s, so what
+// is left of it is mostly HBM time.  Q and the results move in 64-byte pieces, and a sweep does not wait for
+// the stores before it (with the claim under the last PV: 24 x 16 384 on 570 keys 174 -> 166 us, 24 x 4 797 in
+// bf16 268 -> 261, 24 x 9 600 921 -> 913).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 #include "attn_internal.h"
@@ -213,14 +213,18 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_fwd_sp_kernel(const AttnParam
             }
         }
     };
-    // the tiles an item starts with: K 0..NBUF-1 and V 0..NBUF-3 (every wavefront is done with the LDS tiles)
-    auto issue_first_tiles = [&]() __attribute__((always_inline)) {
+    // the tiles an item starts with: K 0..NBUF-1 and V 0..NBUF-3 (every wavefront is done with those buffers)
+    auto issue_first_k = [&]() __attribute__((always_inline)) {
         issue_tile(kp, true, K_BASE + 0 * TILE, 0);
-        if constexpr (NBUF == 4) issue_tile(vp, false, V_BASE + 0 * TILE, 0);
         if (nt > 1) issue_tile(kp, true, K_BASE + 1 * TILE, 1);
         if constexpr (NBUF == 4) {
             if (nt > 2) issue_tile(kp, true, K_BASE + 2 * TILE, 2);
             if (nt > 3) issue_tile(kp, true, K_BASE + 3 * TILE, 3);
+        }
+    };
+    auto issue_first_v = [&]() __attribute__((always_inline)) {
+        if constexpr (NBUF == 4) {
+            issue_tile(vp, false, V_BASE + 0 * TILE, 0);
             if (nt > 1) issue_tile(vp, false, V_BASE + 1 * TILE, 1);
         }
     };
@@ -229,8 +233,8 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_fwd_sp_kernel(const AttnParam
     // in either half of the wavefront; loaded as such, an instruction would touch 32 bytes in each of 32 rows.
     // A pair (kk, kk + 1) is loaded as 64 bytes of each of 16 rows instead, rows 0-15 and then 16-31.
     bf16x8 qf[NKK];
-    // Makes `it` the current item: its key range [kv0, kv1) (tile aligned; all keys, or range `part` of a
-    // cut tile), its Q fragments and first K/V tiles on their way.
+    // Makes `it` the item to come: its key range [kv0, kv1) (tile aligned; all keys, or range `part` of a
+    // cut tile), its Q fragments and first K tiles on their way (issue_first_v is left to the caller).
     auto begin_item = [&](int it) __attribute__((always_inline)) {
         decode(it);
         int64_t kv0 = 0, kv1 = p.n_v;
@@ -252,7 +256,7 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_fwd_sp_kernel(const AttnParam
 #pragma unroll
             for (int kk = r; kk < NKK; kk += 2) qf[kk] = *reinterpret_cast<const bf16x8*>(src + (kk & ~1) * 16);
         }
-        issue_first_tiles();
+        issue_first_k();
     };
     // Once the loads have arrived: 16-lane rows of each pair trade places, which puts the fragments into MFMA order.
     auto arrange_q = [&]() __attribute__((always_inline)) {
@@ -286,7 +290,15 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_fwd_sp_kernel(const AttnParam
         v_ptr[db] = (LDS_PTR(const unsigned char))smem + (V_BASE + v_key_in * (D * 2) + g * 16 + (t16 & 1) * 8);
     }
 
-    int claimed = 0;
+    // The item after this one, claimed by one lane, and whether its Q and K are on their way.
+    int next = p.n_items;
+    bool begun = false;
+    auto claim = [&]() __attribute__((always_inline)) {
+        int lane0 = 0;                   // a lane's own address: for a uniform one the compiler would broadcast the answer at once
+        asm volatile("" : "+v"(lane0));
+        return __hip_atomic_fetch_add((GLOBAL_PTR(int))p.counter + lane0, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    };
+    auto publish = [&](int claimed) __attribute__((always_inline)) { next_item = direct ? p.n_items : (int)gridDim.x + claimed; };
     float mc_run, l_run;     // reference max in exp2 units (max * scale * log2 e), lane's share of the running sum
     f32x16 o_acc[NDB];
     f32x16 nref;                         // BASE2, first sweep: minus the row's reference, as an accumulator seed
@@ -393,6 +405,7 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_fwd_sp_kernel(const AttnParam
         }
         barrier();           // K tile 0 is overwritten by the first DMA of the loop
 
+        int claimed = 0;
         // One iteration; TB = t % 4 fixes every LDS buffer offset at compile time.
         //   s_c: scores of tile t (in, overwritten by its probabilities)   s_n: scores of tile t+1 (out)
         // Slot i (0..N_FR-1; N_FR = 32 for d = 128, 16 for d = 64) = the MFMAs fed by operand fragment
@@ -426,16 +439,13 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_fwd_sp_kernel(const AttnParam
                 v_dma += BN * D;
             } else {
                 if (!LAST && t + NBUF < nt) issue_tile(kp, true, K_BASE + (t % NBUF) * TILE, t + NBUF);
-                if ((!LAST || NBUF == 2) && t + NBUF - 2 < nt) issue_tile(vp, false, V_BASE + ((t + NBUF - 2) % NBUF) * TILE, t + NBUF - 2);
+                if (!LAST && t + NBUF - 2 < nt) issue_tile(vp, false, V_BASE + ((t + NBUF - 2) % NBUF) * TILE, t + NBUF - 2);
             }
+            // The next item is claimed in the last iteration but one, where the answer has an iteration to arrive.
+            if constexpr (KIND == Iter::TAIL && !SAFE)
+                if (t == nt - 2 && !direct && tid == 0) claimed = claim();
             if constexpr (KIND == Iter::TAIL) move_k(((t + 1) % NBUF) * TILE);
             if constexpr (MOVED) move_v(((t - 1) % NBUF) * TILE);
-            LDS_PTR(const unsigned char) v_last[NDB];                 // LAST: V tile t
-            if constexpr (LAST) {
-                const int off = (t % NBUF) * TILE - v_at;
-#pragma unroll
-                for (int db = 0; db < NDB; ++db) v_last[db] = v_ptr[db] + off;
-            }
             constexpr int N_PV = NKB * 2 * NDB, N_QK = NKK * NKB, N_FR = N_PV + N_QK;
             constexpr int PF = 3, RING = 4;
             static_assert(N_FR == 32 || N_FR == 16, "slot plan below is written for 64-key tiles and d = 128 or 64");
@@ -456,8 +466,8 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_fwd_sp_kernel(const AttnParam
                 } else if constexpr (i < N_FR && LAST) {
                     constexpr int n = i - N_PV, kb = n / (2 * NDB), u = (n / NDB) % 2, db = n % NDB;
                     constexpr int off0 = (kb * 32 + u * 16) * (D * 2);
-                    const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LDS_PTR(s16x4))(v_last[db] + off0));
-                    const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LDS_PTR(s16x4))(v_last[db] + off0 + 8 * (D * 2)));
+                    const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LDS_PTR(s16x4))(v_ptr[db] + off0));
+                    const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LDS_PTR(s16x4))(v_ptr[db] + off0 + 8 * (D * 2)));
                     frag[i % RING] = __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
                 } else if constexpr (i < N_FR) {
                     constexpr int j = i - N_PV, kk = j / 2, kb = j % 2;
@@ -580,10 +590,13 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_fwd_sp_kernel(const AttnParam
             });
             static_for<0, N_FR>([&](auto idx) {
                 constexpr int i = decltype(idx)::value;
+                // LAST: the fragments from here on are read from V tile t
+                if constexpr (LAST && i == (NBUF == 2 ? N_PV : N_PV - PF)) move_v((t % NBUF) * TILE);
                 if constexpr (LAST && i == N_PV) {
                     if constexpr (SAFE) rescale(alpha);
-                    if constexpr (NBUF == 2) {      // V tile t was fetched in this iteration
-                        wait_vmcnt<0>();
+                    if constexpr (NBUF == 2) {      // V tile t was fetched in this iteration, then what the next item starts with
+                        if (begun && next < p.n_items) wait_vmcnt<NKK + CPW>();
+                        else wait_vmcnt<0>();
                         barrier();
                         static_for<0, PF>([&](auto j) { load_frag(std::integral_constant<int, N_PV + decltype(j)::value>{}); });
                         __builtin_amdgcn_sched_barrier(0);
@@ -621,6 +634,8 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_fwd_sp_kernel(const AttnParam
                 else if (nt - t == 3) wait_vmcnt<2 * CPW>();
                 else wait_vmcnt<0>();
             }
+            if constexpr (KIND == Iter::TAIL && !SAFE)
+                if (t == nt - 2 && tid == 0) publish(claimed);
             barrier();
         };
 
@@ -654,13 +669,21 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_fwd_sp_kernel(const AttnParam
 #pragma unroll
             for (int kb = 0; kb < NKB; ++kb) s_b[kb] = s_a[kb];
         }
-        if constexpr (!SAFE) {      // claim the next item; the answer travels under the last products
-            // (a lane's own address: for a uniform one the compiler would broadcast the answer at once)
-            int lane0 = 0;
-            asm volatile("" : "+v"(lane0));
-            if (!direct && tid == 0) claimed = __hip_atomic_fetch_add((GLOBAL_PTR(int))p.counter + lane0, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        asm volatile("" :: "v"(claimed));        // its register is not in flight beyond the tail
+        const bool single = nt == 1;
+        if constexpr (NBUF == 2)
+            if (!single) issue_tile(vp, false, V_BASE + (t % NBUF) * TILE, t);
+        begun = !SAFE && nt >= 3;
+        if constexpr (!SAFE) {
+            // No scores are left to compute: the registers of Q and the buffers of K are free for the next item.
+            if (begun) {
+                next = __builtin_amdgcn_readfirstlane(next_item);
+                if (next < p.n_items) begin_item(next);
+            } else if (tid == 0) {
+                publish(direct ? 0 : claim());
+            }
         }
-        if (nt > 1) {
+        if (!single) {
             run(B0, std::integral_constant<Iter, Iter::LAST>{}, t, s_b, s_a);
         } else {                    // a single tile: its PV alone
 #pragma unroll
@@ -772,13 +795,16 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_fwd_sp_kernel(const AttnParam
                                               ok ? (l & 31) * 4 : kOutside, 0, 0);
     };
 
-    if (item < p.n_items) begin_item(item);
+    if (item < p.n_items) {
+        begin_item(item);
+        issue_first_v();
+    }
     __builtin_amdgcn_s_waitcnt(kWaitVm0);     // no stores follow the first item's loads
     while (item < p.n_items) {
     // The next item is claimed as late as possible (the order of the items balances the end of the
-    // launch), but its Q and first tiles travel while this item's results are stored.
+    // launch): one iteration before the last, in which its Q and first K tiles travel; V follows with the stores.
+    // Sweeps of one or two tiles claim it in the last one and begin it with the stores.
     sweep(std::false_type{});
-    int next = p.n_items;
     uint64_t store_mask = ~0ull;                      // lanes whose results are still to be stored
     {
         // A row whose sum left the safe range (a later score exceeded the first tile's max by more
@@ -799,23 +825,28 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_fwd_sp_kernel(const AttnParam
         uint64_t redo = __builtin_amdgcn_ballot_w64(bad);
         redo |= redo << 32 | redo >> 32;             // lanes l and l + 32 hold one row
         if (lane == 0) redo_flag[wave] = redo != 0 ? 1 : 0;
-        if (tid == 0) next_item = direct ? p.n_items : (int)gridDim.x + claimed;
         barrier();                                   // flags are written, and every wavefront is done with the LDS tiles
         int any = 0;
 #pragma unroll
         for (int w = 0; w < NW; ++w) any |= redo_flag[w];
-        next = __builtin_amdgcn_readfirstlane(next_item);
+        if (!begun) next = __builtin_amdgcn_readfirstlane(next_item);
         if (__builtin_expect(__builtin_amdgcn_readfirstlane(any), 0)) {
             locate();
             store_results(~redo);
             store_mask = redo;
-            issue_first_tiles();
+            begin_item(item);                        // again: the next one may have taken its place
+            issue_first_v();
+            __builtin_amdgcn_s_waitcnt(kWaitVm0);
+            arrange_q();
             sweep(std::true_type{});
             barrier();                               // as above, before the next item's tiles are fetched
         }
     }
     locate();
-    if (next < p.n_items) begin_item(next);
+    if (next < p.n_items) {
+        if (!begun) begin_item(next);
+        issue_first_v();
+    }
     store_results(store_mask);
     item = next;
     }   // next work item
