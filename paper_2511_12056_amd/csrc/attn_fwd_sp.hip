@@ -298,7 +298,7 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_fwd_sp_kernel(const AttnParam
         asm volatile("" : "+v"(lane0));
         return __hip_atomic_fetch_add((GLOBAL_PTR(int))p.counter + lane0, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     };
-    auto publish = [&](int claimed) __attribute__((always_inline)) { next_item = direct ? p.n_items : (int)gridDim.x + claimed; };
+    auto publish = [&](int claimed) __attribute__((always_inline)) { next_item = (int)gridDim.x + claimed; };
     float mc_run, l_run;     // reference max in exp2 units (max * scale * log2 e), lane's share of the running sum
     f32x16 o_acc[NDB];
     f32x16 nref;                         // BASE2, first sweep: minus the row's reference, as an accumulator seed
@@ -635,7 +635,7 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_fwd_sp_kernel(const AttnParam
                 else wait_vmcnt<0>();
             }
             if constexpr (KIND == Iter::TAIL && !SAFE)
-                if (t == nt - 2 && tid == 0) publish(claimed);
+                if (t == nt - 2 && !direct && tid == 0) publish(claimed);
             barrier();
         };
 
@@ -673,14 +673,14 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_fwd_sp_kernel(const AttnParam
         const bool single = nt == 1;
         if constexpr (NBUF == 2)
             if (!single) issue_tile(vp, false, V_BASE + (t % NBUF) * TILE, t);
-        begun = !SAFE && nt >= 3;
+        begun = !SAFE && !direct && nt >= 3;
         if constexpr (!SAFE) {
             // No scores are left to compute: the registers of Q and the buffers of K are free for the next item.
             if (begun) {
                 next = __builtin_amdgcn_readfirstlane(next_item);
                 if (next < p.n_items) begin_item(next);
-            } else if (tid == 0) {
-                publish(direct ? 0 : claim());
+            } else if (!direct && tid == 0) {
+                publish(claim());
             }
         }
         if (!single) {
@@ -829,7 +829,7 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_fwd_sp_kernel(const AttnParam
         int any = 0;
 #pragma unroll
         for (int w = 0; w < NW; ++w) any |= redo_flag[w];
-        if (!begun) next = __builtin_amdgcn_readfirstlane(next_item);
+        if (!begun && !direct) next = __builtin_amdgcn_readfirstlane(next_item);
         if (__builtin_expect(__builtin_amdgcn_readfirstlane(any), 0)) {
             locate();
             store_results(~redo);
