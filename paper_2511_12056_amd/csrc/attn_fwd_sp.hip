@@ -146,6 +146,9 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_fwd_sp_kernel(const AttnParam
     // addresses) start from a copy that the compiler cannot trace back: it would otherwise form them
     // once, ahead of the item loop, and carry them in registers that the sweep has no room for.
     auto opaque = [](int x) { asm volatile("" : "+v"(x)); return x; };
+    // The one lane that claims items for the workgroup.  (Not by threadIdx.x, which would be a register more to carry:
+    // the d = 128 forms have none to spare, and one that spills gives the kernel a private segment.)
+    auto leader = [&]() __attribute__((always_inline)) { return wave == 0 && lane == 0; };
     const int64_t Sq = p.Sq;
     const unsigned lds0 = (unsigned)(uintptr_t)(LDS_PTR(const void))smem;
 
@@ -248,13 +251,17 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_fwd_sp_kernel(const AttnParam
         n_v = (int)(kv1 - kv0);
         nt = (n_v + BN - 1) / BN;
         const int l = opaque(lane);
-        const int64_t row0 = (int64_t)q_tile * kTileRows + sub * M + wave * 32 + (l & 15);
+        int64_t row0 = (int64_t)q_tile * kTileRows + sub * M + wave * 32;      // rows beyond the last one: the last one again
+        row0 = row0 < Sq ? row0 : Sq - 1;
+        const int last = (int)(Sq - 1 - row0 < 31 ? Sq - 1 - row0 : 31);
+        // scalar base and 32-bit offset: 64-bit addresses per lane were two registers too many (base 2, four wavefronts)
+        const char* src = reinterpret_cast<const char*>(qp + row0 * D);
 #pragma unroll
         for (int r = 0; r < 2; ++r) {
-            const int64_t row = row0 + 16 * r < Sq ? row0 + 16 * r : Sq - 1;
-            const __bf16* src = qp + row * D + ((l >> 4) & 1) * 16 + 8 * (l >> 5);
+            const int row = (l & 15) + 16 * r;
+            const unsigned off = (unsigned)((row < last ? row : last) * (D * 2) + ((l >> 4) & 1) * 32 + (l >> 5) * 16);
 #pragma unroll
-            for (int kk = r; kk < NKK; kk += 2) qf[kk] = *reinterpret_cast<const bf16x8*>(src + (kk & ~1) * 16);
+            for (int kk = r; kk < NKK; kk += 2) qf[kk] = *reinterpret_cast<const bf16x8*>(src + off + (kk & ~1) * 32);
         }
         issue_first_k();
     };
@@ -443,7 +450,7 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_fwd_sp_kernel(const AttnParam
             }
             // The next item is claimed in the last iteration but one, where the answer has an iteration to arrive.
             if constexpr (KIND == Iter::TAIL && !SAFE)
-                if (t == nt - 2 && !direct && tid == 0) claimed = claim();
+                if (t == nt - 2 && !direct && leader()) claimed = claim();
             if constexpr (KIND == Iter::TAIL) move_k(((t + 1) % NBUF) * TILE);
             if constexpr (MOVED) move_v(((t - 1) % NBUF) * TILE);
             constexpr int N_PV = NKB * 2 * NDB, N_QK = NKK * NKB, N_FR = N_PV + N_QK;
@@ -635,7 +642,7 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_fwd_sp_kernel(const AttnParam
                 else wait_vmcnt<0>();
             }
             if constexpr (KIND == Iter::TAIL && !SAFE)
-                if (t == nt - 2 && !direct && tid == 0) publish(claimed);
+                if (t == nt - 2 && !direct && leader()) publish(claimed);
             barrier();
         };
 
@@ -679,7 +686,7 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_fwd_sp_kernel(const AttnParam
             if (begun) {
                 next = __builtin_amdgcn_readfirstlane(next_item);
                 if (next < p.n_items) begin_item(next);
-            } else if (!direct && tid == 0) {
+            } else if (!direct && leader()) {
                 publish(claim());
             }
         }
@@ -839,6 +846,10 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_fwd_sp_kernel(const AttnParam
             __builtin_amdgcn_s_waitcnt(kWaitVm0);
             arrange_q();
             sweep(std::true_type{});
+            // Q is fetched anew from here.  The compiler does not know it and would keep the old fragments through the
+            // last iteration above, five registers more than there are.
+#pragma unroll
+            for (int kk = 0; kk < NKK; ++kk) asm volatile("" : "=v"(qf[kk]));
             barrier();                               // as above, before the next item's tiles are fetched
         }
     }
@@ -854,7 +865,7 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_fwd_sp_kernel(const AttnParam
     // The last workgroup to leave puts both counters back to zero for the next launch that uses this
     // workspace (launches sharing a workspace are ordered on one stream).  Every workgroup has made
     // its last fetch before it counts itself out, so nobody fetches after the reset.
-    if (!direct && tid == 0) {
+    if (!direct && leader()) {
         __threadfence();
         if (atomicAdd(p.counter + 1, 1) == (int)gridDim.x - 1) {
             __hip_atomic_store(p.counter, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
