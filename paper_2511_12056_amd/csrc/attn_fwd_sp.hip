@@ -131,7 +131,7 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_fwd_sp_kernel(const AttnParam
     constexpr int CHUNKS = TILE / 1024;   // DMA chunks of 1 KB per tile: 16 or 8
     constexpr int CPW = CHUNKS / NW;      // per wavefront: 2 (eight wavefronts) or 4 for d = 128, 1 or 2 for d = 64
     constexpr int RPC = 1024 / (D * 2);   // rows per chunk: 4 or 8
-    constexpr int kStores = (OUT16 ? 2 : 4) * NDB + 1;    // at least as many stores as an item's results take
+    constexpr int kStores = (OUT16 ? 2 : 4) * NDB + 1;    // an item's results take at least this many stores
     static_assert(CPW >= 1, "every wavefront fetches at least one chunk of a tile");
 
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
@@ -739,8 +739,11 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_fwd_sp_kernel(const AttnParam
     // of one row; stored as such, an instruction would write 32 bytes in each of 32 rows.  Neighbouring pieces
     // trade places between the 16-lane rows (and, for bf16, the halves) of the wavefront first, so that an
     // instruction writes 64 bytes in each of 16 rows.  Buffer stores: rows beyond Sq and rows outside the mask
-    // fall to the bounds check, so their number is the same on every path and the next sweep can wait for
-    // the loads that precede them without waiting for all of them.
+    // fall to the bounds check, so no path has fewer than kStores stores and the next sweep can wait for the loads
+    // that precede them without waiting for all of the stores.  That takes more than equal branches: of two
+    // alternatives the compiler makes two conditional blocks, counts the path through neither, and then waits for all
+    // stores but one in front of the first use of Q.  So bf16 results and the fp32 partials of a cut tile share their
+    // first 2 NDB stores, with selected contents, and only what fp32 has beyond them is conditional.
     auto store_results = [&](uint64_t mask) __attribute__((always_inline)) {
         const int l = opaque(lane), l16 = l & 15, r16 = (l >> 4) & 1, half = l >> 5;
         const float l_tot = pair_sum(l_run);
@@ -750,50 +753,63 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_fwd_sp_kernel(const AttnParam
         constexpr int kOutside = 1 << 30;
         const unsigned m32 = (unsigned)mask;
         const bool ok0 = (m32 >> l16) & 1, ok1 = (m32 >> (16 + l16)) & 1;
-        if (OUT16 && store_bf16) {
-            const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(oph + q_row0 * D, 0, rows * (D * 2), kRawBuffer);
-            const int base = l16 * (D * 2) + r16 * 32 + half * 16;
-            const int off0 = ok0 ? base : kOutside, off1 = ok1 ? base + 16 * D * 2 : kOutside;
+        const bool bf16 = OUT16 && store_bf16;
+        const int row_bytes = D * (bf16 ? 2 : 4);
+        char* first = bf16 ? reinterpret_cast<char*>(oph + q_row0 * D) : reinterpret_cast<char*>(op + (q_row0 - row_sub) * D);
+        const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(first, 0, rows * row_bytes, kRawBuffer);
+        const int base = l16 * row_bytes + r16 * 32 + half * 16;
+        const int off0 = ok0 ? base : kOutside, off1 = ok1 ? base + 16 * row_bytes : kOutside;
+        auto store = [&](const u32x4 (&x)[2], int at) __attribute__((always_inline)) {       // 64 bytes of rows 0-15, of rows 16-31
+            __builtin_amdgcn_raw_buffer_store_b128(x[0], rsrc, off0 + at, 0, 0);
+            __builtin_amdgcn_raw_buffer_store_b128(x[1], rsrc, off1 + at, 0, 0);
+        };
+        auto fp32 = [&](int db, int m, u32x4 (&x)[2]) __attribute__((always_inline)) {        // 16 of the 32 columns of block db
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(o_acc[db][8 * m + j] * inv),
+                                                                __float_as_uint(o_acc[db][8 * m + 4 + j] * inv), false, false);
+                x[0][j] = r[0];
+                x[1][j] = r[1];
+            }
+        };
+        if constexpr (!OUT16) {
+#pragma unroll
+            for (int db = 0; db < NDB; ++db)
+#pragma unroll
+                for (int m = 0; m < 2; ++m) {
+                    u32x4 x[2];
+                    fp32(db, m, x);
+                    store(x, db * 128 + m * 64);
+                }
+        } else {
 #pragma unroll
             for (int db = 0; db < NDB; ++db) {
-                u32x4 z[2];
+                u32x4 x[2], z[2];
+                fp32(db, 0, x);
 #pragma unroll
                 for (int m = 0; m < 2; ++m)          // 16 columns: the halves exchange their inner 4
 #pragma unroll
                     for (int j = 0; j < 2; ++j) {
-                        const unsigned x = pack_bf16(o_acc[db][8 * m + 2 * j] * inv, o_acc[db][8 * m + 2 * j + 1] * inv);
-                        const unsigned y = pack_bf16(o_acc[db][8 * m + 4 + 2 * j] * inv, o_acc[db][8 * m + 5 + 2 * j] * inv);
-                        const auto r = __builtin_amdgcn_permlane32_swap(x, y, false, false);
+                        const unsigned a = pack_bf16(o_acc[db][8 * m + 2 * j] * inv, o_acc[db][8 * m + 2 * j + 1] * inv);
+                        const unsigned b = pack_bf16(o_acc[db][8 * m + 4 + 2 * j] * inv, o_acc[db][8 * m + 5 + 2 * j] * inv);
+                        const auto r = __builtin_amdgcn_permlane32_swap(a, b, false, false);
                         z[m][j] = r[0];
                         z[m][2 + j] = r[1];
                     }
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
                     const auto r = __builtin_amdgcn_permlane16_swap(z[0][j], z[1][j], false, false);
-                    z[0][j] = r[0];
-                    z[1][j] = r[1];
+                    x[0][j] = bf16 ? r[0] : x[0][j];
+                    x[1][j] = bf16 ? r[1] : x[1][j];
                 }
-                __builtin_amdgcn_raw_buffer_store_b128(z[0], rsrc, off0 + db * 64, 0, 0);
-                __builtin_amdgcn_raw_buffer_store_b128(z[1], rsrc, off1 + db * 64, 0, 0);
+                store(x, db * (bf16 ? 64 : 128));
             }
-        } else {
-            const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(op + (q_row0 - row_sub) * D, 0, rows * (D * 4), kRawBuffer);
-            const int base = l16 * (D * 4) + r16 * 32 + half * 16;
-            const int off0 = ok0 ? base : kOutside, off1 = ok1 ? base + 16 * D * 4 : kOutside;
+            if (!bf16)
 #pragma unroll
-            for (int db = 0; db < NDB; ++db)
-#pragma unroll
-                for (int m = 0; m < 2; ++m) {
-                    u32x4 x, y;
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) {
-                        const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(o_acc[db][8 * m + j] * inv),
-                                                                        __float_as_uint(o_acc[db][8 * m + 4 + j] * inv), false, false);
-                        x[j] = r[0];
-                        y[j] = r[1];
-                    }
-                    __builtin_amdgcn_raw_buffer_store_b128(x, rsrc, off0 + db * 128 + m * 64, 0, 0);
-                    __builtin_amdgcn_raw_buffer_store_b128(y, rsrc, off1 + db * 128 + m * 64, 0, 0);
+                for (int db = 0; db < NDB; ++db) {
+                    u32x4 x[2];
+                    fp32(db, 1, x);
+                    store(x, db * 128 + 64);
                 }
         }
         const auto lse_rsrc = __builtin_amdgcn_make_buffer_rsrc(lp + (q_row0 - row_sub), 0, rows * 4, kRawBuffer);
