@@ -246,23 +246,10 @@ int run_pipeline(const void* q, const void* k, const void* v, float* out, float*
     hipStream_t cs = static_cast<hipStream_t>(compute_stream), ds = static_cast<hipStream_t>(drain_stream);
     const bool timed = group_ms != nullptr || total_ms != nullptr;
 
-    // Steps of the pipeline: one group each, or several equal small groups in one launch (see
-    // batch_of_groups) unless every group is to be timed.
-    struct Step { int h0, hg, groups; };
-    std::vector<Step> steps;
     hipError_t e = hipSuccess;
     int n_cu = 0;
     if ((e = pda::device_cu_count(&n_cu)) != hipSuccess) return hip_fail(e, "device query");
-    for (int g = 0, h0 = 0; g < n_groups;) {
-        int equal = 1, k = 1;
-        if (!group_ms) {
-            while (g + equal < n_groups && sizes[g + equal] == sizes[g]) ++equal;
-            k = pda::batch_of_groups(Sq, B * sizes[g], kv_valid_len, n_cu, equal);
-        }
-        steps.push_back({h0, sizes[g], k});
-        h0 += k * sizes[g];
-        g += k;
-    }
+    const std::vector<pda::PipelineStep> steps = pda::pipeline_steps(sizes, B, Sq, kv_valid_len, n_cu, group_ms != nullptr);
     const int n_steps = (int)steps.size();
 
     // Events: done[i] orders the hand-off of step i after its attention (Algorithm 1, steps 5-6);

@@ -4,6 +4,7 @@
 #include <stdint.h>
 
 #include <atomic>
+#include <vector>
 
 namespace pda {
 
@@ -227,6 +228,26 @@ inline int batch_of_groups(int64_t Sq, int BH, int64_t n_v, int n_cu, int left) 
     if (2 * items > n_cu) return 1;
     const int64_t fit = n_cu / items;
     return (int)(fit < left ? fit : left);
+}
+// The launches of a pipeline over head groups of the given sizes (B batches): `groups` groups of hg heads each from
+// head h0 on.  One group each if their times are wanted (`alone`), otherwise runs of equal groups in batches.
+// Every size is looked at twice, the plan of a run made once: 65 535 groups are allowed.
+struct PipelineStep { int h0, hg, groups; };
+template <class Sizes>
+std::vector<PipelineStep> pipeline_steps(const Sizes& sizes, int B, int64_t Sq, int64_t n_v, int n_cu, bool alone) {
+    std::vector<PipelineStep> steps;
+    const int n = (int)sizes.size();
+    for (int g = 0, h0 = 0; g < n;) {
+        const int hg = sizes[g];
+        int end = g + 1;
+        while (end < n && sizes[end] == hg) ++end;
+        const int fit = alone ? 1 : batch_of_groups(Sq, B * hg, n_v, n_cu, end - g);
+        for (; g < end; g += steps.back().groups) {
+            steps.push_back({h0, hg, fit < end - g ? fit : end - g});
+            h0 += hg * steps.back().groups;
+        }
+    }
+    return steps;
 }
 // One workspace slot holds one key-range partial of a cut tile: 256 x 128 values + 256 lse.
 // A workspace of n slots is n * kSlotFloats floats followed by kCounterFloats floats that hold the
