@@ -109,9 +109,9 @@ def _stream_handle(stream) -> Optional[int]:
         # The handle without the Stream object around it: a call on a short sequence is bound by host time, and
         # torch.cuda.current_stream() was 3.0 of its 14 us (2 x 1 024, d = 64), the tensor checks 2.8.
         import torch
-        raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
-        if raw is not None and torch.cuda.is_initialized():
-            return raw(torch._C._cuda_getDevice()) or None
+        raw, device = getattr(torch._C, "_cuda_getCurrentRawStream", None), getattr(torch._C, "_cuda_getDevice", None)
+        if raw is not None and device is not None and torch.cuda.is_initialized():     # neither is a public name
+            return raw(device()) or None
         stream = torch.cuda.current_stream()
     return stream.cuda_stream or None
 
