@@ -213,11 +213,13 @@ int pda_attn_merge(const float* const* partials, const float* const* lses, int n
  *                 All-to-All, which needs more than one GPU: the group's slice
  *                 of out is copied to the same slice of sink)
  *
- * so the hand-off of group g overlaps the attention of group g+1.  Unless group_ms is
- * given, consecutive equal groups too small to give every CU work (their launch uses half
- * of the CUs or fewer) share one launch, as many as fill the device once, and one hand-off
- * after it; every group keeps the results it has in a launch of its own.  out/lse of
- * group g are what one pda_attn_fwd call over the group's heads writes (a call
+ * so the hand-off of group g overlaps the attention of group g+1.  Unless group_ms is given,
+ * small groups share a launch: consecutive equal groups whose work items number at most half the
+ * compute units go out floor(compute units / items) at a time (items = n_tiles + n_cut * (split - 1)
+ * of pda_attn_tail_plan for one group; one head of 2 048 tokens is 32 items, eight such groups share
+ * a launch with 256 compute units).  The hand-off of groups that share a launch is one, after that
+ * launch, and overlaps the launch that follows.  Every group keeps the results it has in a launch of
+ * its own: out/lse of group g are what one pda_attn_fwd call over the group's heads writes (a call
  * over all heads agrees up to the rounding of probabilities: which query tiles
  * are computed as merged key-range partials depends on the launch size).
  *

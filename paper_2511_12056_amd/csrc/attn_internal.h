@@ -216,11 +216,12 @@ inline int sp_wavefronts(const TailPlan& t, int64_t n_v, int d, int n_cu) {
     return key_tiles >= 8 && (six_rounds || (rem > 0 && 2 * rem <= n_cu)) ? 4 : 8;
 }
 // Head groups of a pipeline that share a launch: `left` groups of BH (batch, head) pairs each remain.
-// A group whose half tiles do not fill every CU (the four-wavefront rule above) leaves most of the chip idle,
-// and its launch, merge, event and hand-off cost the host more than the GPU.  As many such groups as fill
-// the chip once, two workgroups per CU, go out as one launch, each with the plan and so the bits it has
-// alone; their hand-off waits for that one launch.  24 x 2 048, d = 128, head by head (8 items a group,
-// batches of eight): 680 -> 151 us, host time.  From one item per CU on, a group fills the chip by itself.
+// A group of at most half an item per CU (the four-wavefront rule above: its half items are alone on a CU or leave
+// CUs without work) cannot fill the chip, and its launch, merge, event and hand-off cost the host more than the GPU.
+// As many such groups as give each CU one item go out as one launch, two workgroups per CU, each group with the plan
+// and so the bits it has alone; their hand-off waits for that one launch.  24 x 2 048, d = 128, head by head (8 tiles
+// in 4 ranges = 32 items a group, batches of eight): 680 -> 151 us, host time.  Above half an item per CU a group
+// goes out alone: two of them would not fit the chip at once.
 inline int batch_of_groups(int64_t Sq, int BH, int64_t n_v, int n_cu, int left) {
     if (n_v <= 0 || left < 2) return 1;
     const TailPlan t = plan_tail(Sq, BH, n_v, n_cu);
