@@ -296,6 +296,12 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_fwd_sp_kernel(const AttnParam
         const int g = (db * 4 + 2 * (li >> 4) + ((t16 & 3) >> 1)) ^ swz_v<D>(v_key_in);
         v_ptr[db] = (LDS_PTR(const unsigned char))smem + (V_BASE + v_key_in * (D * 2) + g * 16 + (t16 & 1) * 8);
     }
+    // 16 keys of the 32 columns of block db, from byte offset off of the V tile on
+    auto v_frag = [&](int db, int off) __attribute__((always_inline)) {
+        const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LDS_PTR(s16x4))(v_ptr[db] + off));
+        const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LDS_PTR(s16x4))(v_ptr[db] + off + 8 * (D * 2)));
+        return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+    };
 
     // The item after this one, claimed by one lane, and whether its Q and K are on their way.
     int next = p.n_items;
@@ -465,17 +471,11 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_fwd_sp_kernel(const AttnParam
                 } else if constexpr (i < N_PV) {
                     constexpr int kb = i / (2 * NDB), u = (i / NDB) % 2, db = i % NDB;
                     constexpr int off0 = VP * TILE + (kb * 32 + u * 16) * (D * 2);
-                    s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LDS_PTR(s16x4))(v_ptr[db] + off0));
-                    s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LDS_PTR(s16x4))(v_ptr[db] + off0 + 8 * (D * 2)));
-                    typedef short s16x8 __attribute__((ext_vector_type(8)));
-                    const s16x8 av = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-                    frag[i % RING] = __builtin_bit_cast(bf16x8, av);
+                    frag[i % RING] = v_frag(db, off0);
                 } else if constexpr (i < N_FR && LAST) {
                     constexpr int n = i - N_PV, kb = n / (2 * NDB), u = (n / NDB) % 2, db = n % NDB;
                     constexpr int off0 = (kb * 32 + u * 16) * (D * 2);
-                    const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LDS_PTR(s16x4))(v_ptr[db] + off0));
-                    const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LDS_PTR(s16x4))(v_ptr[db] + off0 + 8 * (D * 2)));
-                    frag[i % RING] = __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+                    frag[i % RING] = v_frag(db, off0);
                 } else if constexpr (i < N_FR) {
                     constexpr int j = i - N_PV, kk = j / 2, kb = j % 2;
                     frag[i % RING] = *(LDS_PTR(const bf16x8))(k_ptr[kk] + (KN * TILE + kb * 32 * (D * 2)));
@@ -696,10 +696,7 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_fwd_sp_kernel(const AttnParam
 #pragma unroll
             for (int i = 0; i < NKB * 2 * NDB; ++i) {
                 const int kb = i / (2 * NDB), u = (i / NDB) % 2, db = i % NDB;
-                LDS_PTR(const unsigned char) a = v_ptr[db] + (kb * 32 + u * 16) * (D * 2);
-                const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LDS_PTR(s16x4))a);
-                const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LDS_PTR(s16x4))(a + 8 * (D * 2)));
-                const bf16x8 av = __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+                const bf16x8 av = v_frag(db, (kb * 32 + u * 16) * (D * 2));
                 const u32x4 pv = {p_io[kb][u][0], p_io[kb][u][1], p_io[kb][u][2], p_io[kb][u][3]};
                 o_acc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av, __builtin_bit_cast(bf16x8, pv), o_acc[db], 0, 0, 0);
             }
