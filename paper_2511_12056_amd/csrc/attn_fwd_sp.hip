@@ -38,8 +38,8 @@
 // tile has no further scores to compute and carries its own PV.  With one form of iteration for all of it
 // (branches in every copy, scores of a tile beyond the end, PV of the last tile by itself) the last three
 // iterations of a sweep took 0.3, 0.5 and 1.8 us longer than the others (d = 128, two workgroups per CU), and
-// every copy of the loop body was 780 instructions instead of 550: 24 x 16 384 on 570 keys 166 -> 161 us,
-// 24 x 9 600 -1.7 %, 3 x 67 576 -1.1 %, d = 64, 6 x 67 576 -2.7 %.  At the top of iteration t a
+// every copy of the loop body was 452 instructions, branches included, instead of 247: 24 x 16 384 on 570
+// keys 166 -> 161 us, 24 x 9 600 -1.7 %, 3 x 67 576 -1.1 %, d = 64, 6 x 67 576 -2.7 %.  At the top of iteration t a
 // wavefront issues its share of K tile t+NBUF (over K tile t) and V tile t+NBUF-2 (over V tile t-2),
 // both last read in iteration t-1; before the barrier that closes the iteration it waits for K tile
 // t+2 and V tile t, which iteration t+1 reads: with four buffers all but its two newest batches.
