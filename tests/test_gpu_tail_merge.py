@@ -1,9 +1,8 @@
 """Merge of a cut tile's key ranges for every number of ranges (one query tile is cut in up to 16)."""
-import numpy as np
 import pytest
 
 from synth import gen_qkv
-from tests.util import LSE_REL, REL_L2, assert_close, tail_plan, to_dev_bf16
+from tests.util import assert_close, tail_plan, to_dev_bf16
 
 pytestmark = pytest.mark.gpu
 

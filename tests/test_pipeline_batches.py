@@ -6,7 +6,7 @@ import subprocess
 
 import pytest
 
-from tests.util import tail_plan, to_dev_bf16
+from tests.util import tail_plan
 
 CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2511_12056_amd", "csrc")
 CLANG = "/opt/rocm/llvm/bin/clang++"
