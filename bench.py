@@ -246,7 +246,7 @@ def next_rows(pda, torch, w, q, k, v, out, lse, sink, cs, ds, t_linear_ms):
                                        "achieved": fl / (ms * 1e-3) * 1e-12, "unit": "TFLOP/s",
                                        "frac_of_bf16_mfma_peak": fl / (ms * 1e-3) * 1e-12 / PEAK_BF16_TFLOPS,
                                        "kernel": "attn_fwd_sp_kernel<64, 8, false, false>",
-                                       "note": "half the MFMA work per score: matrix pipe 52 % and VALU issue 67 % busy, neither full"}
+                                       "note": "half the MFMA work per score: matrix pipe 56 % and VALU issue 71 % busy, neither full"}
     del q64, k64, v64, o64, l64
 
     # head-chunk pipeline with the post-processing folded into the hand-off (token-major, final order)
