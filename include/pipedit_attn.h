@@ -47,7 +47,7 @@ typedef enum {
     PDA_ERR_INVALID_ARG = 1, /* null pointer, negative size, kv_valid_len > Skv, n < 1, ... */
     PDA_ERR_UNSUPPORTED = 2, /* d not in {64,128}, n > PDA_MAX_PARTIALS, misaligned pointer, size overflow */
     PDA_ERR_HIP = 3,         /* a HIP runtime call failed; see pda_last_error() */
-    PDA_ERR_NOMEM = 4        /* the one-time device workspace of a stream could not be allocated */
+    PDA_ERR_NOMEM = 4        /* the one-time device workspace of a stream, or host memory, could not be allocated */
 } pda_status;
 
 #define PDA_MAX_PARTIALS 16

@@ -4,6 +4,7 @@
 #include <cstdarg>
 #include <atomic>
 #include <cstdio>
+#include <exception>
 #include <map>
 #include <mutex>
 #include <utility>
@@ -25,6 +26,16 @@ int fail(int code, const char* fmt, ...) {
 
 int hip_fail(hipError_t e, const char* what) {
     return fail(PDA_ERR_HIP, "%s: %s", what, hipGetErrorString(e));
+}
+
+// Runs f, which allocates host memory in containers: no exception leaves a C entry.
+template <class F>
+int no_throw(F&& f) {
+    try {
+        return f();
+    } catch (const std::exception& x) {
+        return fail(PDA_ERR_NOMEM, "no host memory (%s)", x.what());
+    }
 }
 
 bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
@@ -123,7 +134,10 @@ int cached_workspace(hipStream_t st, int64_t need_slots, CachedWs* out) {
     if (e == hipSuccess) e = pda::device_cu_count(&n_cu);
     if (e != hipSuccess) return hip_fail(e, "device query");
     std::lock_guard<std::mutex> lock(mu);
-    CachedWs& w = pool[{dev, st}];
+    CachedWs* entry = nullptr;
+    const int rc = no_throw([&] { entry = &pool[{dev, st}]; return (int)PDA_OK; });
+    if (rc != PDA_OK) return rc;
+    CachedWs& w = *entry;
     if (!w.ptr) {
         const int64_t slots = pda::max_tail_slots(n_cu, true);
         void* ptr = nullptr;
@@ -224,7 +238,8 @@ int launch_heads(const void* q, const void* k, const void* v, float* out, float*
                           B, hg, Sq, d, compact_strides(H, Sq, Skv, d), scale, n_v, st, variant, false, false, kind, n_groups);
 }
 
-// The head-chunk pipeline (Algorithm 1, steps 2-9) over the given groups; arguments already validated.
+// The head-chunk pipeline (Algorithm 1, steps 2-9) over the given groups; arguments already validated.  May
+// throw for want of host memory, before the first event is created.
 int run_pipeline(const void* q, const void* k, const void* v, float* out, float* lse,
                  int B, int H, int64_t Sq, int64_t Skv, int d, float scale, int64_t kv_valid_len,
                  const std::vector<int>& sizes, int sp_ranks, int sink_layout,
@@ -462,10 +477,12 @@ int pda_headchunk_run(const void* q, const void* k, const void* v, float* out, f
     int rc = check_attn_args(q, k, v, out, lse, B, H, Sq, Skv, d, scale, kv_valid_len);
     if (rc != PDA_OK) return rc;
     if (heads_per_group < 1) return fail(PDA_ERR_INVALID_ARG, "heads_per_group=%d (need >= 1)", heads_per_group);
-    std::vector<int> sizes;
-    for (int h0 = 0; h0 < H; h0 += heads_per_group) sizes.push_back(h0 + heads_per_group <= H ? heads_per_group : H - h0);
-    return run_pipeline(q, k, v, out, lse, B, H, Sq, Skv, d, scale, kv_valid_len, sizes, 1, PDA_SINK_HEAD_MAJOR,
-                        compute_stream, drain_stream, sink, group_ms, total_ms);
+    return no_throw([&] {
+        std::vector<int> sizes;
+        for (int h0 = 0; h0 < H; h0 += heads_per_group) sizes.push_back(h0 + heads_per_group <= H ? heads_per_group : H - h0);
+        return run_pipeline(q, k, v, out, lse, B, H, Sq, Skv, d, scale, kv_valid_len, sizes, 1, PDA_SINK_HEAD_MAJOR,
+                            compute_stream, drain_stream, sink, group_ms, total_ms);
+    });
 }
 
 int pda_headchunk_run_ex(const void* q, const void* k, const void* v, float* out, float* lse,
@@ -490,9 +507,11 @@ int pda_headchunk_run_ex(const void* q, const void* k, const void* v, float* out
         if (!sink) return fail(PDA_ERR_INVALID_ARG, "a token-major hand-off needs a sink");
         if (H % sp_ranks != 0) return fail(PDA_ERR_INVALID_ARG, "H=%d is not a multiple of sp_ranks=%d", H, sp_ranks);
     }
-    return run_pipeline(q, k, v, out, lse, B, H, Sq, Skv, d, scale, kv_valid_len,
-                        std::vector<int>(group_sizes, group_sizes + n_groups), sp_ranks, sink_layout,
-                        compute_stream, drain_stream, sink, group_ms, total_ms);
+    return no_throw([&] {
+        return run_pipeline(q, k, v, out, lse, B, H, Sq, Skv, d, scale, kv_valid_len,
+                            std::vector<int>(group_sizes, group_sizes + n_groups), sp_ranks, sink_layout,
+                            compute_stream, drain_stream, sink, group_ms, total_ms);
+    });
 }
 
 int pda_pipesp_postprocess(const float* const* chunks, int h, int n, int64_t chunk_row_stride,

@@ -860,7 +860,7 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_fwd_sp_kernel(const AttnParam
             arrange_q();
             sweep(std::true_type{});
             // Q is fetched anew from here.  The compiler does not know it and would keep the old fragments through the
-            // last iteration above, five registers more than there are.
+            // last iteration above, up to six registers more than there are.
 #pragma unroll
             for (int kk = 0; kk < NKK; ++kk) asm volatile("" : "=v"(qf[kk]));
             barrier();                               // as above, before the next item's tiles are fetched
