@@ -137,10 +137,13 @@ int pda_attn_fwd_noalloc(const void* q, const void* k, const void* v, float* out
  * to three rounds of whole tiles), or of decreasing size (after four or more rounds), whichever
  * balances the end of the launch better.  Hence two launches agree bit for bit on every row that
  * lies in an uncut tile of both, and to the rounding of the probabilities on the others.
+ * (Where every tile is cut and the launch has few rows, up to 3 072 to 6 144 keys, the keys of a
+ * row are shared among the wavefronts of one workgroup instead, which merges their partial results
+ * itself: such a launch writes no partials and no second kernel follows.)
  * n_cu: compute units of the device (0 = ask the current device).  Outputs (any may be NULL):
  * n_tiles; n_cut (0 = nothing is cut); split (1 = nothing is cut); part_offsets, a HOST array of
  * PDA_MAX_KEY_RANGES + 1 values (part_offsets[0] = 0, entries from index split on are
- * kv_valid_len); workspace_slots, the number of 132 096-byte partial slots the launch uses (fp32
+ * kv_valid_len); workspace_slots, the number of 132 096-byte partial slots the plan asks for (fp32
  * out; never more than 9/4 per compute unit; a d = 64 launch fills half of each slot).  Empty key
  * sets are never cut.
  */

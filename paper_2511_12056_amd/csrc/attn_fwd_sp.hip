@@ -67,23 +67,6 @@ constexpr int kWaitVm0 = 0x0f70;     // s_waitcnt vmcnt(0), the other counters n
 // share a CU's 160 KB.
 constexpr int sp_buffers(int d, int n_waves) { return d == 128 && n_waves < 8 ? 2 : 4; }
 
-// 16 bytes per lane from global memory (scalar base + per-lane byte offset) straight into LDS:
-// lane l's data lands at lds_addr + 16*l (lds_addr wave-uniform, passed in M0).  Inline assembly
-// on purpose: the compiler's wait-count insertion then does not see an LDS write that it cannot
-// tell apart from the operand reads that follow (it would drain the whole prefetch before every
-// LDS read); completion is tracked by hand with s_waitcnt vmcnt before the barrier.
-// M0 is not restored; it is declared clobbered.
-// The compiler does not see into the assembly, so the wait states it would insert are up to us: one
-// between the write of M0 and the load, and five between a VALU write of the base registers (the
-// v_readlane that restores a spilled pointer) and the load.  Copying the base through VCC is both: an
-// instruction in between, and a scalar write, which the hardware interlocks.
-__device__ __forceinline__ void lds_dma16(const void* sbase, unsigned voff, unsigned lds_addr) {
-    asm volatile("s_mov_b32 m0, %0\n\ts_mov_b64 vcc, %2\n\tglobal_load_lds_dwordx4 %1, vcc"
-                 :
-                 : "s"(lds_addr), "v"(voff), "s"(sbase)
-                 : "memory", "m0", "vcc");
-}
-
 // Same with the LDS address given as wave-uniform base + compile-time offset.
 template <int LDS_OFF>
 __device__ __forceinline__ void lds_dma16_at(const void* sbase, unsigned voff, unsigned lds_base) {
@@ -93,25 +76,9 @@ __device__ __forceinline__ void lds_dma16_at(const void* sbase, unsigned voff, u
                  : "memory", "scc", "m0", "vcc");
 }
 
-template <int N>
-__device__ __forceinline__ void wait_vmcnt() {
-    asm volatile("s_waitcnt vmcnt(%0)" :: "n"(N) : "memory");
-}
-
 // BASE2: the scores are already in units of log2 (the caller folded scale*log2(e) into Q), so the
 // weights are 2^(q.k) and the first sweep needs no arithmetic before the exponential at all: the
 // score accumulators start from minus the row's reference instead of from zero.
-// Row-dependent XOR applied to the index of a row's 16-byte granules in an LDS tile, chosen so that
-// the operand reads are free of bank conflicts (64 banks of 4 bytes).  With 256-byte rows (d = 128)
-// every row starts at bank 0: the K reads (16 rows, one granule each) need 16 different granules,
-// the transposing V reads (4 rows, 4 granules each) 4 different groups of 4.  With 128-byte rows
-// (d = 64) even and odd rows already lie in different halves of the banks, so the XOR is taken
-// from the row index without its lowest bit.
-template <int D>
-__device__ __forceinline__ constexpr int swz_k(int row) { return D == 128 ? (row & 15) : ((row >> 1) & 7); }
-template <int D>
-__device__ __forceinline__ constexpr int swz_v(int row) { return D == 128 ? ((row & 3) << 2) : (((row >> 1) & 1) << 2); }
-
 enum class Iter { MAIN, FIRST, TAIL, LAST };      // forms of an iteration of the sweep
 
 template <int D, int NW, bool BASE2, bool OUT16>
@@ -1000,6 +967,7 @@ static hipError_t launch_sp(AttnParams p, int BH, float* ws, int64_t ws_slots, h
         for (int j = 0; j < t.split; ++j)
             if (t.part_off[j + 1] <= t.part_off[j] || t.part_off[j] % 64 != 0) return hipErrorInvalidValue;
     }
+    if (rows_form(t, p.Sq, BH, p.n_v, D, n_cu) && !p.redo_always) return launch_attn_rows(p, BH, D, st);
     p.tiles_per_head = t.tiles_per_head;
     p.split = t.split;
     p.n_cut = (int)t.n_cut;

@@ -215,6 +215,30 @@ inline int sp_wavefronts(const TailPlan& t, int64_t n_v, int d, int n_cu) {
     const int64_t rem = t.n_tiles % n_cu;
     return key_tiles >= 8 && (six_rounds || (rem > 0 && 2 * rem <= n_cu)) ? 4 : 8;
 }
+// Does a launch with plan `t` (of one group, if several share it) take the kernel for few query rows (attn_rows.hip:
+// 32 rows a workgroup, its wavefronts share the keys) instead of cut tiles and their merge?  Only launches in which
+// every tile is cut: rows of whole tiles keep the bits of a sweep in one pass.  A round of its workgroups (256, at d = 64
+// two a CU) costs 3 us and 5.3 us per 1 024 keys at d = 128, 2.8 at d = 64, whatever the rows; the cut form hardly
+// grows with the keys as long as CUs are free, but starts at 12 to 16 us.  So the line lies at a number of keys that grows with the
+// blocks of 32 rows up to one round and falls beyond (us, cut -> rows; of 572 shapes of 1 to 960 blocks on 1 024 to
+// 12 288 keys the rule takes 282, 1.02x to 2.1x faster):
+//   d = 64:  2 x 1 024 rows on 1 024 keys (64 blocks) 13.6 -> 7.1, on 4 096 16.3 -> 16.0, on 5 120 17.6 -> 18.4;
+//            1 x 256 on 3 072 13.3 -> 12.2, on 4 096 13.8 -> 15.0; 8 x 1 024 on 6 144 27.4 -> 23.0, on 12 288 39.1 -> 42.7;
+//            16 x 1 024 on 4 096 30.8 -> 28.3, on 6 144 38.9 -> 40.5; 18 x 1 024 on 2 048 24.6 -> 21.9, on 3 072 29.1 -> 29.9
+//   d = 128: 1 x 1 024 on 1 024 15.9 -> 10.1, on 2 048 16.5 -> 13.9, on 3 072 17.3 -> 18.0; 4 x 1 024 on 5 120
+//            31.6 -> 26.5; 8 x 1 024 on 2 048 24.1 -> 15.8, on 8 192 48.4 -> 48.4; two rounds pay only if the second is
+//            mostly full (9 x 1 024 on 2 560 30.9 -> 32.0; 16 x 1 024 on 2 048 35.2 -> 29.4, on 4 096 50.2 -> 51.7)
+inline bool rows_form(const TailPlan& t, int64_t Sq, int BH, int64_t n_v, int d, int n_cu) {
+    if (t.split <= 1 || t.n_cut != t.n_tiles) return false;
+    const int64_t blocks = (Sq + 31) / 32 * BH, round = n_cu;
+    if (d == 64) {
+        if (blocks > 2 * round) return blocks <= 3 * round ? n_v <= 2048 : blocks <= 4 * round && n_v <= 1536;
+        if (n_v <= 3072) return true;
+        return 4 * blocks >= round && n_v <= (8 * blocks >= 3 * round && blocks <= round ? 6144 : 4096);
+    }
+    if (blocks > round) return 8 * blocks >= 11 * round && blocks <= 2 * round && n_v <= 2560;
+    return n_v <= (2 * blocks >= round ? 5120 : 4 * blocks >= round ? 3072 : 2048);
+}
 // Head groups of a pipeline that share a launch: `left` groups of BH (batch, head) pairs each remain.
 // A group of at most half an item per CU (the four-wavefront rule above: its half items are alone on a CU or leave
 // CUs without work) cannot fill the chip, and its launch, merge, event and hand-off cost the host more than the GPU.
@@ -274,6 +298,9 @@ hipError_t launch_attn_fwd(const AttnParams& p, int BH, int D, int variant, floa
 
 // Software-pipelined kernel for d = 128 and 64 (attn_fwd_sp.hip); p.n_v >= 1, p.scale_log2e > 0.
 hipError_t launch_attn_fwd_sp(const AttnParams& p, int BH, int D, float* ws, int64_t ws_slots, hipStream_t st);
+
+// Kernel for launches of few query rows (attn_rows.hip).
+hipError_t launch_attn_rows(const AttnParams& p, int BH, int D, hipStream_t st);
 
 // Does this (d, variant, valid key count) take the software-pipelined kernel (and so possibly a workspace)?
 inline bool uses_sp_kernel(int D, int variant, int64_t n_v) { return (D == 128 || D == 64) && n_v > 0 && (variant == 0 || variant == 3); }

@@ -1,0 +1,264 @@
+// Flash-attention forward for launches of few query rows, gfx950, d = 128 and 64 (which launches: attn_internal.h,
+// rows_form).
+//
+// The software-pipelined kernel needs the keys of such a launch cut into ranges to fill the chip, a partial result of
+// every range in memory and a second launch that merges them; at 2 x 1 024 rows, d = 64, that was 13.6 us, of which 3 us
+// for the merge and most of the rest one wavefront per SIMD walking eight key tiles.  Here a workgroup finishes 32 query
+// rows: its KS wavefronts share the keys among them, sweep their shares independently of each other (own LDS tiles, own
+// waits, no barrier until the end) and add up their partial results in LDS.  One launch, no workspace.
+//
+// MFMA formulation, operand order and LDS swizzle are those of attn_fwd_sp.hip; tiles of 32 keys, one of K and one of V per
+// wavefront: K tile t+1 travels under the softmax and PV of tile t, V tile t+1 under the next QK and softmax.  The
+// reference is a running max that moves when the max grew by more than 2^8.
+//
+// What bounds it: every workgroup streams all keys of its head into LDS, 4 d bytes per key for 32 rows, at 110 GB/s per
+// CU (53 of the 64 bytes a clock that the vector cache can deliver), against 2 us of MFMA time for 1 024 keys at
+// d = 128 where the stream takes 4.8.  So a round of workgroups costs 3 us (start, sum, stores) and 5.3 us per 1 024
+// keys at d = 128, half of that at d = 64.  Two row blocks per wavefront, each K and V fragment feeding two MFMAs, halve the
+// stream but were slower up to two rounds (d = 64, 2 x 1 024: 6.8 -> 9.7 us; d = 128 spills).
+// KS = 8: two wavefronts per SIMD; d = 64 needs 70 KB of LDS, so two workgroups share a CU (16 wavefronts of 32
+// rows, one workgroup per CU: 8 x 2 048 rows 16.3 -> 20.0 us).
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+#include "attn_internal.h"
+#include "attn_device.h"
+
+namespace pda {
+
+constexpr int kRows = 32;            // query rows of a workgroup
+constexpr int kKeys = 32;            // keys of a tile
+static_assert(kRows == kKeys, "a wavefront's partial result takes the place of its two tiles");
+
+// LDS of a workgroup: per wavefront a tile of K and one of V (later its partial O in fp32), the rows of Q, and the reference
+// and sum of every row and wavefront.
+constexpr int rows_smem(int d, int ks) { return ks * 2 * kKeys * d * 2 + kRows * d * 2 + 2 * ks * kRows * 4; }
+
+template <int D, int KS>
+__global__ __launch_bounds__(64 * KS, 2) void attn_rows_kernel(const AttnParams p) {
+    static_assert(D == 128 || D == 64, "head dimension");
+    constexpr int G = D / 8;              // 16-byte granules per bf16 row
+    constexpr int NKK = D / 16, NDB = D / 32;
+    constexpr int TILE = kKeys * D * 2;   // 8 KB or 4 KB
+    constexpr int CPT = TILE / 1024;      // DMA chunks of 1 KB per tile
+    constexpr int RPC = 1024 / (D * 2);   // rows per chunk
+    constexpr int Q_BASE = KS * 2 * TILE, ST_BASE = Q_BASE + TILE;
+    static_assert(CPT <= KS, "a wavefront fetches at most one chunk of Q");
+
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int li = lane & 31, lh = lane >> 5;
+    const unsigned lds0 = (unsigned)(uintptr_t)(LDS_PTR(const void))smem;
+
+    // Workgroups are dealt to the 8 XCDs round robin; each XCD gets a consecutive range of row blocks, so that few heads
+    // pass through its L2.
+    const int per = (int)gridDim.x >> 3, extra = (int)gridDim.x & 7, xcd = (int)blockIdx.x & 7;
+    const int block = xcd * per + (xcd < extra ? xcd : extra) + ((int)blockIdx.x >> 3);
+    const int blocks_per_head = (int)((p.Sq + kRows - 1) / kRows);
+    const int bh = block / blocks_per_head, heads = p.Hg * p.n_groups;
+    const int b = bh / heads, h = bh - b * heads;
+    const int64_t row0 = (int64_t)(block - bh * blocks_per_head) * kRows;
+    const int rows = (int)(p.Sq - row0 < kRows ? p.Sq - row0 : kRows);
+    const char* qp = reinterpret_cast<const char*>(p.q + (int64_t)b * p.q_bs + (int64_t)h * p.q_hs + row0 * D);
+    const char* kp = reinterpret_cast<const char*>(p.k + (int64_t)b * p.kv_bs + (int64_t)h * p.kv_hs);
+    const char* vp = reinterpret_cast<const char*>(p.v + (int64_t)b * p.kv_bs + (int64_t)h * p.kv_hs);
+
+    // this wavefront's key tiles: none if there are fewer tiles than wavefronts
+    const int nt = (int)((p.n_v + kKeys - 1) / kKeys);
+    const int t0 = (int)((int64_t)nt * wave / KS), t1 = (int)((int64_t)nt * (wave + 1) / KS);
+
+    // ---- loads into LDS: chunk j of a tile holds rows j RPC .. j RPC + RPC-1, lane -> row lane / G of them, granule position lane % G
+    const unsigned lds_k = lds0 + wave * (2 * TILE), lds_v = lds_k + TILE;
+    auto granule = [&](int row, bool is_v) __attribute__((always_inline)) {
+        return (unsigned)(((lane % G) ^ (is_v ? swz_v<D>(row) : swz_k<D>(row))) * 16);
+    };
+    unsigned ld_k[CPT], ld_v[CPT];
+#pragma unroll
+    for (int j = 0; j < CPT; ++j) {
+        const int row = j * RPC + lane / G;
+        ld_k[j] = row * (D * 2) + granule(row, false);
+        ld_v[j] = row * (D * 2) + granule(row, true);
+    }
+    auto issue = [&](const char* base, bool is_v, unsigned lds, int tile) __attribute__((always_inline)) {
+        const char* src = base + (int64_t)tile * TILE;
+        const int64_t left = p.n_v - (int64_t)tile * kKeys;
+        if (left >= kKeys) {
+#pragma unroll
+            for (int j = 0; j < CPT; ++j) lds_dma16(src, is_v ? ld_v[j] : ld_k[j], lds + j * 1024);
+        } else {                                      // rows clamped to the last valid key: hidden keys are never read
+#pragma unroll
+            for (int j = 0; j < CPT; ++j) {
+                const int row = j * RPC + lane / G;
+                lds_dma16(src, (unsigned)(row < (int)left ? row : (int)left - 1) * (D * 2) + granule(row, is_v), lds + j * 1024);
+            }
+        }
+    };
+    if (wave < CPT) {
+        const int row = wave * RPC + lane / G;
+        lds_dma16(qp, (unsigned)(row < rows ? row : rows - 1) * (D * 2) + granule(row, false), lds0 + Q_BASE + wave * 1024);
+    }
+    if (t0 < t1) {
+        issue(kp, false, lds_k, t0);
+        issue(vp, true, lds_v, t0);
+        wait_vmcnt<2 * CPT>();                        // the chunk of Q came first
+    } else {
+        wait_vmcnt<0>();
+    }
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+
+    // ---- operand reads
+    auto k_off = [&](int kk) __attribute__((always_inline)) { return li * (D * 2) + (((2 * kk + lh) ^ swz_k<D>(li)) * 16); };
+    bf16x8 qf[NKK];
+#pragma unroll
+    for (int kk = 0; kk < NKK; ++kk) qf[kk] = *(LDS_PTR(const bf16x8))((LDS_PTR(const unsigned char))smem + Q_BASE + k_off(kk));
+    LDS_PTR(const unsigned char) my_k = (LDS_PTR(const unsigned char))smem + wave * (2 * TILE);
+    LDS_PTR(const unsigned char) my_v = my_k + TILE;
+    const int t16 = lane & 15, v_key_in = 4 * lh + (t16 >> 2);
+    auto v_frag = [&](int db, int u) __attribute__((always_inline)) {
+        const int g = (db * 4 + 2 * (li >> 4) + ((t16 & 3) >> 1)) ^ swz_v<D>(v_key_in);
+        LDS_PTR(const unsigned char) at = my_v + (u * 16 + v_key_in) * (D * 2) + g * 16 + (t16 & 1) * 8;
+        const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LDS_PTR(s16x4))at);
+        const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LDS_PTR(s16x4))(at + 8 * (D * 2)));
+        return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+    };
+    auto reads_done = [&]() __attribute__((always_inline)) { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); };
+
+    // ---- sweep over the wavefront's keys
+    const float c = p.scale_log2e;
+    float mc = -INFINITY, l_run = 0.f;               // reference in exp2 units; the lane's share of the sum
+    f32x16 o_acc[NDB];
+#pragma unroll
+    for (int db = 0; db < NDB; ++db)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) o_acc[db][r] = 0.f;
+
+    for (int t = t0; t < t1; ++t) {
+        wait_vmcnt<CPT>();                            // K tile t is in; V tile t, issued after it, perhaps not
+        f32x16 s = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
+#pragma unroll
+        for (int kk = 0; kk < NKK; ++kk)
+            s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*(LDS_PTR(const bf16x8))(my_k + k_off(kk)), qf[kk], s, 0, 0, 0);
+        reads_done();
+        const bool more = t + 1 < t1;
+        if (more) issue(kp, false, lds_k, t + 1);
+        if ((int64_t)(t + 1) * kKeys > p.n_v) {
+            const int hidden = (int)(p.n_v - (int64_t)t * kKeys) - 4 * lh;      // key 4 lh + x is hidden if x >= this
+#pragma unroll
+            for (int r = 0; r < 16; ++r)
+                if ((r >> 2) * 8 + (r & 3) >= hidden) s[r] = -INFINITY;
+        }
+        float m0 = s[0], m1 = s[1];
+#pragma unroll
+        for (int r = 2; r < 16; r += 2) {
+            m0 = fmaxf(m0, s[r]);
+            m1 = fmaxf(m1, s[r + 1]);
+        }
+        const float mxc = pair_max(fmaxf(m0, m1)) * c;
+        const float mc_new = (mxc - mc > 8.0f) ? mxc : mc;
+        const float alpha = __builtin_amdgcn_exp2f(mc - mc_new);          // 1 if unmoved, 0 on the first tile
+        if (__builtin_amdgcn_ballot_w64(alpha != 1.0f) != 0) {
+#pragma unroll
+            for (int db = 0; db < NDB; ++db)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) o_acc[db][r] *= alpha;
+        }
+        mc = mc_new;
+        float sum0 = 0.f, sum1 = 0.f;
+        u32x4 pk[2];
+#pragma unroll
+        for (int r = 0; r < 16; r += 2) {
+            const float x = __builtin_amdgcn_exp2f(__builtin_fmaf(s[r], c, -mc));
+            const float y = __builtin_amdgcn_exp2f(__builtin_fmaf(s[r + 1], c, -mc));
+            sum0 += x;
+            sum1 += y;
+            pk[r / 8][(r % 8) / 2] = pack_bf16(x, y);
+        }
+        l_run = __builtin_fmaf(l_run, alpha, sum0 + sum1);
+        if (more) wait_vmcnt<CPT>();                  // V tile t is in; K tile t+1, issued after it, perhaps not
+        else wait_vmcnt<0>();
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+#pragma unroll
+            for (int db = 0; db < NDB; ++db)
+                o_acc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v_frag(db, u), __builtin_bit_cast(bf16x8, pk[u]), o_acc[db], 0, 0, 0);
+        reads_done();
+        if (more) issue(vp, true, lds_v, t + 1);
+    }
+
+    // ---- partial results into LDS: O where the wavefront's tiles were, 16-byte granules XORed with the row
+    constexpr int G4 = D / 4;             // 16-byte granules per fp32 row
+    LDS_PTR(unsigned char) part = (LDS_PTR(unsigned char))smem;
+    LDS_PTR(float) st_m = (LDS_PTR(float))((LDS_PTR(unsigned char))smem + ST_BASE);
+    LDS_PTR(float) st_l = st_m + KS * kRows;
+#pragma unroll
+    for (int db = 0; db < NDB; ++db)
+#pragma unroll
+        for (int a = 0; a < 4; ++a) {
+            const f32x4 x = {o_acc[db][4 * a], o_acc[db][4 * a + 1], o_acc[db][4 * a + 2], o_acc[db][4 * a + 3]};
+            const int g = (db * 8 + 2 * a + lh) ^ (li % G4);
+            *(LDS_PTR(f32x4))(part + wave * (2 * TILE) + li * (D * 4) + g * 16) = x;
+        }
+    const float l_tot = pair_sum(l_run);
+    if (lh == 0) {
+        st_m[wave * kRows + li] = mc;
+        st_l[wave * kRows + li] = l_tot;
+    }
+    __syncthreads();
+
+    // ---- their sum on a common reference goes out, 16 bytes (8 of bf16) per lane
+#pragma unroll
+    for (int i = tid; i < kRows * G4; i += 64 * KS) {
+        const int row = i / G4, g = i % G4;
+        float m[KS], big = -INFINITY;
+#pragma unroll
+        for (int w = 0; w < KS; ++w) {
+            m[w] = st_m[w * kRows + row];
+            big = fmaxf(big, m[w]);
+        }
+        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+        float tot = 0.f;
+#pragma unroll
+        for (int w = 0; w < KS; ++w) {
+            const float f = __builtin_amdgcn_exp2f(m[w] - big);           // 0 for a wavefront without keys
+            const f32x4 x = *(LDS_PTR(const f32x4))(part + w * (2 * TILE) + row * (D * 4) + ((g ^ (row % G4)) * 16));
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc[e] = __builtin_fmaf(f, x[e], acc[e]);
+            tot = __builtin_fmaf(f, st_l[w * kRows + row], tot);
+        }
+        if (row < rows) {
+            const float inv = 1.0f / tot;
+            const int64_t at = (int64_t)b * p.o_bs + (int64_t)h * p.o_hs + (row0 + row) * D + g * 4;
+            if (p.out_bf16)
+                *reinterpret_cast<u32x2*>(reinterpret_cast<__bf16*>(p.out) + at) =
+                    u32x2{pack_bf16(acc[0] * inv, acc[1] * inv), pack_bf16(acc[2] * inv, acc[3] * inv)};
+            else
+                *reinterpret_cast<f32x4*>(p.out + at) = f32x4{acc[0] * inv, acc[1] * inv, acc[2] * inv, acc[3] * inv};
+            if (g == 0) {                // ln of the mantissa only: the error of the logarithm grows with its value
+                int e;
+                const float f = frexpf(tot, &e);
+                p.lse[(int64_t)b * p.l_bs + (int64_t)h * p.l_hs + row0 + row] =
+                    __builtin_fmaf((float)e, 0.6931471805599453f, __builtin_fmaf(big, 0.6931471805599453f, __logf(f)));
+            }
+        }
+    }
+}
+
+template <int D>
+static hipError_t launch_rows(const AttnParams& p, int BH, hipStream_t st) {
+    constexpr int KS = 8, smem = rows_smem(D, KS);
+    auto kern = attn_rows_kernel<D, KS>;
+    static KernelSetup setup;
+    hipError_t e = setup.ensure(reinterpret_cast<const void*>(kern), smem, nullptr);
+    if (e != hipSuccess) return e;
+    const int64_t blocks = (p.Sq + kRows - 1) / kRows * BH * p.n_groups;
+    if (blocks > 0x7fffffff) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(64 * KS), smem, st, p);
+    return hipGetLastError();
+}
+
+hipError_t launch_attn_rows(const AttnParams& p, int BH, int D, hipStream_t st) {
+    return D == 128 ? launch_rows<128>(p, BH, st) : launch_rows<64>(p, BH, st);
+}
+
+}  // namespace pda
