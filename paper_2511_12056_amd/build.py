@@ -9,7 +9,7 @@ from concurrent.futures import ThreadPoolExecutor
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libpipedit_attn.so")
-SOURCES = ["attn_fwd.hip", "attn_fwd_sp.hip", "attn_fwd_sp_d64.hip", "attn_rows.hip", "merge.hip", "layout.hip", "probe.hip", "api.hip"]
+SOURCES = ["attn_fwd.hip", "attn_fwd_sp.hip", "attn_fwd_sp_d64.hip", "attn_fwd_wide.hip", "attn_fwd_wide_d64.hip", "attn_rows.hip", "merge.hip", "layout.hip", "probe.hip", "api.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",

@@ -2,7 +2,8 @@
 // A workgroup of NW wavefronts sweeps 32 NW query rows: eight wavefronts (256 rows, one workgroup per
 // CU) or four (128 rows, two per CU); either way two wavefronts share a SIMD.  A wavefront owns 32 rows
 // of them.  Two such sub-tiles in one wavefront per SIMD, each K/V fragment feeding two MFMAs,
-// were slower: a single wavefront leaves the latencies at the iteration boundary exposed.
+// were slower: a single wavefront leaves the latencies at the iteration boundary exposed.  (With two wavefronts per SIMD in
+// opposite phases they are faster where there are pairs of whole tiles: attn_fwd_wide.hip.)
 //
 // MFMA formulation and LDS tile layout are those of attn_fwd.hip (S^T = K Q^T, O^T = V^T P^T on
 // v_mfma_f32_32x32x16_bf16, one query per lane, XOR-swizzled 16-byte granules).  Schedule: on
@@ -79,10 +80,31 @@ __device__ __forceinline__ void lds_dma16_at(const void* sbase, unsigned voff, u
 // BASE2: the scores are already in units of log2 (the caller folded scale*log2(e) into Q), so the
 // weights are 2^(q.k) and the first sweep needs no arithmetic before the exponential at all: the
 // score accumulators start from minus the row's reference instead of from zero.
+// The last workgroup to leave puts both counters back to zero for the next launch that uses this
+// workspace (launches sharing a workspace are ordered on one stream).  Every workgroup has made
+// its last fetch before it counts itself out, so nobody fetches after the reset.
+template <class Args>
+__device__ __forceinline__ void reset_counter(const Args& p) {
+    __threadfence();
+    if (atomicAdd(p.counter + 1, 1) == (int)gridDim.x - 1) {
+        __hip_atomic_store(p.counter, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(p.counter + 1, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+}
+
+// The lane's index in its wavefront, in a register that the compiler cannot trace back to an earlier one.
+__device__ __forceinline__ int fresh_lane() {
+    int l;
+    asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(l));
+    return l;
+}
+
 enum class Iter { MAIN, FIRST, TAIL, LAST };      // forms of an iteration of the sweep
 
-template <int D, int NW, bool BASE2, bool OUT16>
-__global__ __launch_bounds__(64 * NW, 2) void attn_fwd_sp_kernel(const AttnParams p) {
+// Works off the units of a launch from `item` on (claiming the following ones unless `direct`) until one is not below
+// n_items.  AFTER_WIDE: behind the wide items of attn_fwd_wide.hip, which number and leave out units as described there.
+template <int D, int NW, bool BASE2, bool OUT16, bool AFTER_WIDE, class Args>
+__device__ __forceinline__ void sp_items(const Args& p, int item, const int n_items, const bool direct, const int wave_in) {
     static_assert(D == 128 || D == 64, "head dimension");
     static_assert(NW == 8 || NW == 4, "wavefronts per workgroup");
     constexpr int BN = 64;
@@ -105,9 +127,10 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_fwd_sp_kernel(const AttnParam
     __shared__ int next_item;
     __shared__ int redo_flag[NW];
 
-    const int tid = threadIdx.x;
+    // (after wide items from a fresh lane index: formed from the thread's, all that follows would be ahead of those items)
+    const int tid = AFTER_WIDE ? fresh_lane() : threadIdx.x;
     const int lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wave = AFTER_WIDE ? wave_in : __builtin_amdgcn_readfirstlane(tid >> 6);
     const int li = lane & 31, lh = lane >> 5;
     // Values formed from the lane index outside the sweep's main path (tail rows, masks, Q rows, store
     // addresses) start from a copy that the compiler cannot trace back: it would otherwise form them
@@ -125,8 +148,6 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_fwd_sp_kernel(const AttnParam
     // workgroups of a grid to them round robin, so a grid with one workgroup per item would end with
     // the slowest XCD while the others idle.  A launch with no more items than workgroups does not
     // touch the counter.
-    const bool direct = p.n_items <= (int)gridDim.x;
-    int item = (int)blockIdx.x;
 
     // ---- work item -> (query tile, head, key range), inside the group of heads blockIdx.y.  Items [0, n_full) are whole tiles; then the
     // cut tiles' key ranges, range-major, so that the items in flight at any time sweep the same keys.
@@ -136,7 +157,11 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_fwd_sp_kernel(const AttnParam
         it /= SUB;
         tile = it;
         part = 0;
-        if (it >= p.n_full) {
+        if (AFTER_WIDE && it >= p.n_items) {
+            tile = it - p.n_items;                    // a tile that a wide item has given back
+        } else if (AFTER_WIDE && it < 2 * p.n_wide + p.n_odd) {
+            tile = (it - 2 * p.n_wide + 1) * p.tiles_per_head - 1;      // the last tile of a head of wide items
+        } else if (it >= p.n_full) {
             const int idx = it - p.n_full;
             part = idx / p.n_cut;
             tile = p.n_full + (idx - part * p.n_cut);
@@ -271,14 +296,14 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_fwd_sp_kernel(const AttnParam
     };
 
     // The item after this one, claimed by one lane, and whether its Q and K are on their way.
-    int next = p.n_items;
+    int next = n_items;
     bool begun = false;
     auto claim = [&]() __attribute__((always_inline)) {
         int lane0 = 0;                   // a lane's own address: for a uniform one the compiler would broadcast the answer at once
         asm volatile("" : "+v"(lane0));
         return __hip_atomic_fetch_add((GLOBAL_PTR(int))p.counter + lane0, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     };
-    auto publish = [&](int claimed) __attribute__((always_inline)) { next_item = (int)gridDim.x + claimed; };
+    auto publish = [&](int claimed) __attribute__((always_inline)) { next_item = (int)gridDim.x + claimed + (AFTER_WIDE ? p.n_wide : 0); };
     float mc_run, l_run;     // reference max in exp2 units (max * scale * log2 e), lane's share of the running sum
     f32x16 o_acc[NDB];
     f32x16 nref;                         // BASE2, first sweep: minus the row's reference, as an accumulator seed
@@ -569,7 +594,7 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_fwd_sp_kernel(const AttnParam
                 if constexpr (LAST && i == N_PV) {
                     if constexpr (SAFE) rescale(alpha);
                     if constexpr (NBUF == 2) {      // V tile t was fetched in this iteration, then what the next item starts with
-                        if (begun && next < p.n_items) wait_vmcnt<NKK + CPW>();
+                        if (begun && next < n_items) wait_vmcnt<NKK + CPW>();
                         else wait_vmcnt<0>();
                         barrier();
                         static_for<0, PF>([&](auto j) { load_frag(std::integral_constant<int, N_PV + decltype(j)::value>{}); });
@@ -652,7 +677,7 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_fwd_sp_kernel(const AttnParam
             // No scores are left to compute: the registers of Q and the buffers of K are free for the next item.
             if (begun) {
                 next = __builtin_amdgcn_readfirstlane(next_item);
-                if (next < p.n_items) begin_item(next);
+                if (next < n_items) begin_item(next);
             } else if (!direct && leader()) {
                 publish(claim());
             }
@@ -782,12 +807,12 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_fwd_sp_kernel(const AttnParam
                                               ok ? (l & 31) * 4 : kOutside, 0, 0);
     };
 
-    if (item < p.n_items) {
+    if (item < n_items) {
         begin_item(item);
         issue_first_v();
     }
     __builtin_amdgcn_s_waitcnt(kWaitVm0);     // no stores follow the first item's loads
-    while (item < p.n_items) {
+    while (item < n_items) {
     // The next item is claimed as late as possible (the order of the items balances the end of the
     // launch): one iteration before the last, in which its Q and first K tiles travel; V follows with the stores.
     // Sweeps of one or two tiles claim it in the last one and begin it with the stores.
@@ -834,7 +859,7 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_fwd_sp_kernel(const AttnParam
         }
     }
     locate();
-    if (next < p.n_items) {
+    if (next < n_items) {
         if (!begun) begin_item(next);
         issue_first_v();
     }
@@ -842,18 +867,15 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_fwd_sp_kernel(const AttnParam
     item = next;
     }   // next work item
 
-    // The last workgroup to leave puts both counters back to zero for the next launch that uses this
-    // workspace (launches sharing a workspace are ordered on one stream).  Every workgroup has made
-    // its last fetch before it counts itself out, so nobody fetches after the reset.
-    if (!direct && leader()) {
-        __threadfence();
-        if (atomicAdd(p.counter + 1, 1) == (int)gridDim.x - 1) {
-            __hip_atomic_store(p.counter, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            __hip_atomic_store(p.counter + 1, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
-    }
+    if (!AFTER_WIDE && !direct && leader()) reset_counter(p);
 }
 
+template <int D, int NW, bool BASE2, bool OUT16>
+__global__ __launch_bounds__(64 * NW, 2) void attn_fwd_sp_kernel(const AttnParams p) {
+    sp_items<D, NW, BASE2, OUT16, false>(p, (int)blockIdx.x, p.n_items, p.n_items <= (int)gridDim.x, 0);
+}
+
+#ifndef PDA_SP_DEVICE_ONLY
 // Folds the key-range partials of the cut tiles into out/lse (in place): per row,
 // L = ln sum_p exp(lse_p), out = sum_p exp(lse_p - L) out_p.  One group of d/4 lanes (half or a
 // quarter of a wavefront) per row, so a row's lse is read by all its lanes before one of them
@@ -977,8 +999,18 @@ static hipError_t launch_sp(AttnParams p, int BH, float* ws, int64_t ws_slots, h
     p.part_lse = slots ? ws + slots * (kTileRows * D) : nullptr;
     p.counter = reinterpret_cast<int*>(ws + ws_slots * kSlotFloats);     // two ints behind the slots, zero between launches
     const int64_t items = p.n_full + t.n_cut * t.split;
-    const bool four = sp_wavefronts(t, p.n_v, D, n_cu) == 4;
-    hipError_t e = four ? launch_items<D, 4, BASE2, OUT16>(p, items, n_cu, st) : launch_items<D, 8, BASE2, OUT16>(p, items, n_cu, st);
+    hipError_t e;
+    const WidePlan wide = p.n_groups > 1 || p.redo_always ? WidePlan{0, 0} : wide_plan(t, p.n_v, n_cu);
+    if (wide.items > 0) {
+        p.n_wide = wide.items;
+        p.n_odd = wide.odd_heads;
+        p.n_items = (int)items;
+        e = launch_attn_wide(p, D, n_cu, st);
+    } else if (sp_wavefronts(t, p.n_v, D, n_cu) == 4) {
+        e = launch_items<D, 4, BASE2, OUT16>(p, items, n_cu, st);
+    } else {
+        e = launch_items<D, 8, BASE2, OUT16>(p, items, n_cu, st);
+    }
     if (e != hipSuccess || t.split <= 1) return e;
     return launch_tail_merge<D>(p, st);
 }
@@ -1002,5 +1034,6 @@ hipError_t launch_attn_fwd_sp_d64(const AttnParams& p, int BH, float* ws, int64_
     return launch_sp_form<64>(p, BH, ws, ws_slots, st);
 }
 #endif
+#endif   // PDA_SP_DEVICE_ONLY
 
 }  // namespace pda

@@ -66,6 +66,8 @@ struct AttnParams {
     float* part_lse;        // [(tile - n_full) * (split - 1) + part - 1][256]
     int n_cut;              // number of cut tiles (the last n_cut of a group)
     int n_items;            // n_full + n_cut * split per group, twice that with four wavefronts (set by the launch)
+    int n_wide;             // leading items that are pairs of whole tiles (attn_fwd_wide.hip); 0: none
+    int n_odd;              // heads whose last, single tile is left out of those pairs
     int* counter;           // two ints, zero between launches: items taken beyond each workgroup's first, workgroups that have finished
     int out_bf16;           // software-pipelined kernel: `out` points to bf16 elements (same element strides)
     int base2;              // scores are already in log2 units: weights 2^(q.k), scale_log2e == 1
@@ -187,7 +189,8 @@ inline TailPlan plan_tail(int64_t Sq, int BH, int64_t n_v, int n_cu) {
     }
     return t;
 }
-// Wavefronts per workgroup of a launch with plan `t`: eight (256 rows, one workgroup per CU) or four
+// Wavefronts per workgroup of a launch with plan `t` and no pairs of tiles (wide_plan below; those leave the second case of
+// four to sweeps of under 224 keys and to variant 3): eight (256 rows, one workgroup per CU) or four
 // (128 rows, half a tile; two per CU).  The results are the same bits; only the time differs (us,
 // eight -> four).  Eight is the rule: a K/V tile in LDS serves twice the rows, half the global -> LDS
 // traffic (3 heads x 67 576, d = 128: 5 530 -> 6 120; 10 x 9 600: 419 -> 471).  Four
@@ -214,6 +217,29 @@ inline int sp_wavefronts(const TailPlan& t, int64_t n_v, int d, int n_cu) {
     if (d == 128) return six_rounds || key_tiles >= 4 ? 4 : 8;
     const int64_t rem = t.n_tiles % n_cu;
     return key_tiles >= 8 && (six_rounds || (rem > 0 && 2 * rem <= n_cu)) ? 4 : 8;
+}
+// Leading items of a launch with plan `t` that are pairs of whole tiles of one head, 512 rows a workgroup (attn_fwd_wide.hip),
+// and the heads among those with an odd number of tiles that they cover but for the last tile.  A CU works off a pair in 1.83
+// times (d = 128; 1.9 at d = 64) what it needs for a tile, so pairs are taken wherever each CU has two whole tiles to
+// do: of `full` whole tiles, n_cu - rem CUs have full / n_cu and rem have one more.  That is worth most where the last round is
+// partly full and uncut: those CUs have one pair instead of two tiles (us, eight or four wavefronts a tile -> pairs first,
+// d = 128 / d = 64):
+//   long sweeps:  3 x 119 056 16 430 -> 15 140 (five rounds, four of them in pairs); 24 x 9 600 927 -> 879 / 574 -> 558;
+//                 24 x 5 000 289 -> 247 / 180 -> 158 (1.88 rounds, uncut)
+//   short ones:   24 x 16 384 on 1 536 keys 292 -> 271 / 177 -> 162, on 570 154 -> 150 / 100 -> 86, on 224 110 -> 102 / 67 -> 55;
+//                 48 x 4 800 on 400 92 -> 76 / 61 -> 52; 400 x 301 on 700 99 -> 86 / 68 -> 60
+// Of 96 shapes (1 to 12 rounds, 224 to 119 056 keys, fp32, bf16 and base-2 results) one is slower, by 0.4 % (24 x 9 600, d = 64,
+// base 2).  Below 224 keys the first steps of a sweep would not find the whole tiles they fetch.
+constexpr int64_t kWideKeys = 224;
+struct WidePlan { int items, odd_heads; };
+inline WidePlan wide_plan(const TailPlan& t, int64_t n_v, int n_cu) {
+    const int64_t full = t.n_tiles - t.n_cut, pairs = t.tiles_per_head / 2;
+    if (n_v < kWideKeys || full < n_cu || pairs == 0) return {0, 0};
+    const int64_t rounds = full / n_cu, rem = full % n_cu;
+    const int64_t have = full / t.tiles_per_head * pairs + full % t.tiles_per_head / 2;
+    int64_t n = (n_cu - rem) * (rounds / 2) + rem * ((rounds + 1) / 2);
+    if (n > have) n = have;
+    return {(int)n, t.tiles_per_head % 2 ? (int)(n / pairs) : 0};
 }
 // Does a launch with plan `t` (of one group, if several share it) take the kernel for few query rows (attn_rows.hip:
 // 32 rows a workgroup, its wavefronts share the keys) instead of cut tiles and their merge?  Only launches in which
@@ -298,6 +324,9 @@ hipError_t launch_attn_fwd(const AttnParams& p, int BH, int D, int variant, floa
 
 // Software-pipelined kernel for d = 128 and 64 (attn_fwd_sp.hip); p.n_v >= 1, p.scale_log2e > 0.
 hipError_t launch_attn_fwd_sp(const AttnParams& p, int BH, int D, float* ws, int64_t ws_slots, hipStream_t st);
+
+// Software-pipelined kernel with p.n_wide > 0 wide items in front (attn_fwd_wide.hip); all of p but the grid is set.
+hipError_t launch_attn_wide(const AttnParams& p, int D, int n_cu, hipStream_t st);
 
 // Kernel for launches of few query rows (attn_rows.hip).
 hipError_t launch_attn_rows(const AttnParams& p, int BH, int D, hipStream_t st);
