@@ -989,7 +989,7 @@ static hipError_t launch_sp(AttnParams p, int BH, float* ws, int64_t ws_slots, h
         for (int j = 0; j < t.split; ++j)
             if (t.part_off[j + 1] <= t.part_off[j] || t.part_off[j] % 64 != 0) return hipErrorInvalidValue;
     }
-    if (rows_form(t, p.Sq, BH, p.n_v, D, n_cu) && !p.redo_always) return launch_attn_rows(p, BH, D, st);
+    if (rows_form(t, p.Sq, BH, p.n_v, D, n_cu) && !p.redo_always) return launch_attn_rows(p, BH, D, n_cu, st);
     p.tiles_per_head = t.tiles_per_head;
     p.split = t.split;
     p.n_cut = (int)t.n_cut;

@@ -241,29 +241,40 @@ inline WidePlan wide_plan(const TailPlan& t, int64_t n_v, int n_cu) {
     if (n > have) n = have;
     return {(int)n, t.tiles_per_head % 2 ? (int)(n / pairs) : 0};
 }
-// Does a launch with plan `t` (of one group, if several share it) take the kernel for few query rows (attn_rows.hip:
-// 32 rows a workgroup, its wavefronts share the keys) instead of cut tiles and their merge?  Only launches in which
-// every tile is cut: rows of whole tiles keep the bits of a sweep in one pass.  A round of its workgroups (256, at d = 64
-// two a CU) costs 3 us and 5.3 us per 1 024 keys at d = 128, 2.8 at d = 64, whatever the rows; the cut form hardly
-// grows with the keys as long as CUs are free, but starts at 12 to 16 us.  So the line lies at a number of keys that grows with the
-// blocks of 32 rows up to one round and falls beyond (us, cut -> rows; of 572 shapes of 1 to 960 blocks on 1 024 to
-// 12 288 keys the rule takes 282, 1.02x to 2.1x faster):
+// Does a launch with plan `t` (of one group, if several share it) take the kernel for few query rows (attn_rows.hip: its
+// wavefronts share the keys) instead of cut tiles and their merge?  Only launches in which every tile is cut: rows of whole
+// tiles keep the bits of a sweep in one pass.  The time of that kernel goes by rounds of its workgroups (one per CU, at d = 64
+// two) and by the keys; the cut form hardly grows with the keys as long as CUs are free, but starts at 12 to 16 us.  So
+// the line lies at a number of keys that grows with the blocks of 32 rows up to the end of a round and falls behind it (us,
+// cut -> rows; of about 750 shapes of 1 to 1 024 blocks on 1 024 to 12 288 keys none that the rule takes is slower):
 //   d = 64:  2 x 1 024 rows on 1 024 keys (64 blocks) 13.6 -> 7.1, on 4 096 16.3 -> 16.0, on 5 120 17.6 -> 18.4;
 //            1 x 256 on 3 072 13.3 -> 12.2, on 4 096 13.8 -> 15.0; 8 x 1 024 on 6 144 27.4 -> 23.0, on 12 288 39.1 -> 42.7;
 //            16 x 1 024 on 4 096 30.8 -> 28.3, on 6 144 38.9 -> 40.5; 18 x 1 024 on 2 048 24.6 -> 21.9, on 3 072 29.1 -> 29.9
 //   d = 128: 1 x 1 024 on 1 024 15.9 -> 10.1, on 2 048 16.5 -> 13.9, on 3 072 17.3 -> 18.0; 4 x 1 024 on 5 120
-//            31.6 -> 26.5; 8 x 1 024 on 2 048 24.1 -> 15.8, on 8 192 48.4 -> 48.4; two rounds pay only if the second is
-//            mostly full (9 x 1 024 on 2 560 30.9 -> 32.0; 16 x 1 024 on 2 048 35.2 -> 29.4, on 4 096 50.2 -> 51.7)
+//            31.6 -> 26.5; 8 x 1 024 on 2 048 24.1 -> 15.8, on 8 192 48.4 -> 48.4; 9 x 1 024 on 1 024 20.5 -> 15.4, on 4 096
+//            39.1 -> 38.7; 16 x 1 024 on 2 048 37.6 -> 26.4, on 6 144 64.7 -> 64.0; 17 x 1 024 on 1 024 29.9 -> 29.2, on 1 536
+//            33.7 -> 37.0; 32 x 1 024 on 1 536 46.9 -> 43.6, on 2 048 52.6 -> 53.4
 inline bool rows_form(const TailPlan& t, int64_t Sq, int BH, int64_t n_v, int d, int n_cu) {
     if (t.split <= 1 || t.n_cut != t.n_tiles) return false;
     const int64_t blocks = (Sq + 31) / 32 * BH, round = n_cu;
+    if (blocks > 4 * round) return false;
     if (d == 64) {
-        if (blocks > 2 * round) return blocks <= 3 * round ? n_v <= 2048 : blocks <= 4 * round && n_v <= 1536;
+        if (blocks > 2 * round) return n_v <= (blocks <= 3 * round ? 2048 : 1536);
         if (n_v <= 3072) return true;
         return 4 * blocks >= round && n_v <= (8 * blocks >= 3 * round && blocks <= round ? 6144 : 4096);
     }
-    if (blocks > round) return 8 * blocks >= 11 * round && blocks <= 2 * round && n_v <= 2560;
+    if (blocks > 2 * round) return n_v <= (2 * blocks >= 7 * round ? 1536 : 1152);
+    if (blocks > round) return n_v <= 4096;
     return n_v <= (2 * blocks >= round ? 5120 : 4 * blocks >= round ? 3072 : 2048);
+}
+// Blocks of 32 rows in a workgroup of that kernel, for a launch of `blocks` (of all groups that share it); same bits.  Two halve the
+// keys that a CU streams for a row, but a wavefront then needs 1.7 times as long for a tile, so at d = 128 they pay as soon as there
+// is more than one round (us, one -> two: 9 x 1 024 on 2 048 keys 28.5 -> 22.6, 16 x 1 024 31.8 -> 26.4, 32 x 1 024 65.7 -> 53.4; 8 x
+// 1 024 16.7 -> 22.9), at d = 64, where two workgroups share a CU, for a nearly full second round of few keys (16 x 1 024 on
+// 1 024 13.4 -> 11.2, on 1 536 16.5 -> 14.4, on 2 048 17.7 -> 18.0; 24 x 1 024 on 1 024 16.1 -> 21.4).
+inline int rows_blocks(int64_t blocks, int64_t n_v, int d, int n_cu) {
+    if (d == 128) return blocks > n_cu ? 2 : 1;
+    return 2 * blocks >= 3 * (int64_t)n_cu && blocks <= 2 * (int64_t)n_cu && n_v <= 1536 ? 2 : 1;
 }
 // Head groups of a pipeline that share a launch: `left` groups of BH (batch, head) pairs each remain.
 // A group of at most half an item per CU (the four-wavefront rule above: its half items are alone on a CU or leave
@@ -329,7 +340,7 @@ hipError_t launch_attn_fwd_sp(const AttnParams& p, int BH, int D, float* ws, int
 hipError_t launch_attn_wide(const AttnParams& p, int D, int n_cu, hipStream_t st);
 
 // Kernel for launches of few query rows (attn_rows.hip).
-hipError_t launch_attn_rows(const AttnParams& p, int BH, int D, hipStream_t st);
+hipError_t launch_attn_rows(const AttnParams& p, int BH, int D, int n_cu, hipStream_t st);
 
 // Does this (d, variant, valid key count) take the software-pipelined kernel (and so possibly a workspace)?
 inline bool uses_sp_kernel(int D, int variant, int64_t n_v) { return (D == 128 || D == 64) && n_v > 0 && (variant == 0 || variant == 3); }

@@ -1,4 +1,4 @@
-"""Launches of few query rows, whose workgroups finish 32 rows each and share the keys among eight wavefronts: the
+"""Launches of few query rows, whose workgroups finish 32 or 64 rows each and share the keys among eight wavefronts: the
 rule that picks them against the same rule written out here, and their results at the edges of row blocks, key tiles
 and key shares against the fp64 oracle."""
 import math
@@ -38,7 +38,7 @@ def rows_form(BH, Sq, n_v, d, n_cu):
         return n_v <= (2048 if rounds <= 3 else 1536 if rounds <= 4 else 0)
     if rounds <= 1:
         return n_v <= (2048 if rounds < 1 / 4 else 3072 if rounds < 1 / 2 else 5120)
-    return 11 / 8 <= rounds <= 2 and n_v <= 2560
+    return n_v <= (4096 if rounds <= 2 else 1152 if rounds < 3.5 else 1536 if rounds <= 4 else 0)
 
 
 def test_rule(tmp_path):
@@ -53,8 +53,8 @@ def test_rule(tmp_path):
     for n_cu in (256, 256, 256, 304, 64, 1):
         for _ in range(1500):
             Sq = rng.randint(1, 3000)
-            BH = max(1, round(n_cu * rng.choice([0.1, 0.25, 0.375, 0.5, 1, 1.375, 2, 3, 4, rng.uniform(0, 5)]) / -(-Sq // 32)))
-            cases.append((BH, Sq, rng.choice([rng.randint(900, 7000), rng.choice([1024, 1536, 2048, 2560, 3072, 4096, 5120, 6144]) + rng.randint(0, 1)]),
+            BH = max(1, round(n_cu * rng.choice([0.1, 0.25, 0.375, 0.5, 1, 2, 3, 3.5, 4, rng.uniform(0, 5)]) / -(-Sq // 32)))
+            cases.append((BH, Sq, rng.choice([rng.randint(900, 7000), rng.choice([1024, 1152, 1536, 2048, 3072, 4096, 5120, 6144]) + rng.randint(0, 1)]),
                           rng.choice([64, 128]), n_cu))
     out = subprocess.run([str(exe)], input="\n".join(" ".join(map(str, c)) for c in cases), capture_output=True, text=True, check=True, timeout=120)
     got = [bool(int(x)) for x in out.stdout.split()]
@@ -84,7 +84,8 @@ def _launch(entry, q, k, v, scale, n_v):
 @pytest.mark.gpu
 @pytest.mark.parametrize("d", [128, 64])
 @pytest.mark.parametrize("B,H,Sq,n_v", [(1, 1, 1, 1024), (1, 2, 31, 1025), (2, 1, 32, 1055), (1, 3, 33, 1056), (1, 1, 63, 1087), (2, 2, 65, 1281),
-                                        (1, 3, 97, 1500), (1, 5, 301, 2017), (3, 3, 800, 2048), (3, 5, 799, 1100)])
+                                        (1, 3, 97, 1500), (1, 5, 301, 2017), (3, 3, 800, 2048),
+                                        (3, 5, 799, 1100), (1, 9, 1025, 1311), (2, 12, 1000, 1024)])
 def test_edges_against_the_oracle(B, H, Sq, n_v, d):
     """Rows and keys at the edges of blocks, shares of unequal length, keys beyond kv_valid_len that must not be read."""
     import torch
@@ -184,3 +185,20 @@ def test_cut_form_of_few_ranges(ranges, d):
     out, lse = torch.full((1, 1, Sq, d), float("nan"), device="cuda"), torch.full((1, 1, Sq), float("nan"), device="cuda")
     pda.attn_fwd_variant(to_dev_bf16(qb), to_dev_bf16(kb), to_dev_bf16(vb), out, lse, d ** -0.5, variant=3)
     assert_close(out.cpu().numpy(), lse.cpu().numpy(), *attention(qb, kb, vb, d ** -0.5), f"{ranges} ranges, d={d}")
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("d,n_v", [(128, 1024), (128, 1499), (128, 2047), (64, 1025), (64, 1499)])
+@pytest.mark.parametrize("Sq", [993, 1024, 1025])
+def test_two_blocks_of_rows_give_the_bits_of_one(Sq, d, n_v):
+    """13 heads (more than a round of 32-row blocks: 64 rows a workgroup) against one of them alone."""
+    import torch
+    if _n_cu() == 256:
+        assert rows_form(13, Sq, n_v, d, 256) and rows_form(1, Sq, n_v, d, 256)
+    qb, kb, vb = gen_qkv(80 + Sq, 1, 13, Sq, n_v, d, unit_rms=True)
+    q, k, v = to_dev_bf16(qb), to_dev_bf16(kb), to_dev_bf16(vb)
+    for entry in ("fp32", "bf16"):
+        out, lse = _launch(entry, q, k, v, d ** -0.5, n_v)
+        for h in (0, 7, 12):
+            o, l = _launch(entry, *(t[:, h:h + 1].contiguous() for t in (q, k, v)), d ** -0.5, n_v)
+            assert torch.equal(out[:, h], o[:, 0]) and torch.equal(lse[:, h], l[:, 0]), (entry, h)
