@@ -220,7 +220,9 @@ int pda_attn_merge(const float* const* partials, const float* const* lses, int n
  * small groups share a launch: consecutive equal groups whose work items number at most half the
  * compute units go out floor(compute units / items) at a time (items = n_tiles + n_cut * (split - 1)
  * of pda_attn_tail_plan for one group; one head of 2 048 tokens is 32 items, eight such groups share
- * a launch with 256 compute units).  The hand-off of groups that share a launch is one, after that
+ * a launch with 256 compute units); groups whose keys the wavefronts of a workgroup share (see
+ * pda_attn_tail_plan) up to three times as many, with up to 2 048 keys at d = 128 and 4 096 at
+ * d = 64.  The hand-off of groups that share a launch is one, after that
  * launch, and overlaps the launch that follows.  Every group keeps the results it has in a launch of
  * its own: out/lse of group g are what one pda_attn_fwd call over the group's heads writes (a call
  * over all heads agrees up to the rounding of probabilities: which query tiles

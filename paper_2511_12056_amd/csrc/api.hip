@@ -200,7 +200,9 @@ int launch_checked(const void* q, const void* k, const void* v, float* out, floa
         hipError_t e = pda::device_cu_count(&n_cu);
         if (e != hipSuccess) return hip_fail(e, "device query");
         // every launch of this kernel uses a workspace: its work counters, and the partial slots of cut tiles
-        const int64_t need = n_groups * pda::tail_slots(pda::plan_tail(Sq, B * hg, n_v, n_cu), out_bf16);
+        const pda::TailPlan plan = pda::plan_tail(Sq, B * hg, n_v, n_cu);
+        // (groups in one launch of the kernel for few rows, however many, use no slots)
+        const int64_t need = n_groups > 1 && pda::rows_form(plan, Sq, B * hg, n_v, d, n_cu) ? 0 : n_groups * pda::tail_slots(plan, out_bf16);
         if (kind == WS_STATIC) {
             if (need > kStaticSlots)
                 return fail(PDA_ERR_UNSUPPORTED, "this launch needs %lld partial slots (%lld bytes) of scratch; the static buffer holds %lld (%lld bytes)",
@@ -264,7 +266,8 @@ int run_pipeline(const void* q, const void* k, const void* v, float* out, float*
     hipError_t e = hipSuccess;
     int n_cu = 0;
     if ((e = pda::device_cu_count(&n_cu)) != hipSuccess) return hip_fail(e, "device query");
-    const std::vector<pda::PipelineStep> steps = pda::pipeline_steps(sizes, B, Sq, kv_valid_len, n_cu, group_ms != nullptr);
+    const std::vector<pda::PipelineStep> steps =
+        pda::join_steps(pda::pipeline_steps(sizes, B, Sq, kv_valid_len, n_cu, group_ms != nullptr), B, Sq, kv_valid_len, d, n_cu, group_ms != nullptr);
     const int n_steps = (int)steps.size();
 
     // Events: done[i] orders the hand-off of step i after its attention (Algorithm 1, steps 5-6);

@@ -980,6 +980,7 @@ static hipError_t launch_sp(AttnParams p, int BH, float* ws, int64_t ws_slots, h
         if (e != hipSuccess) return e;
     }
     const TailPlan t = plan_tail(p.Sq, BH, p.n_v, n_cu);
+    if (rows_form(t, p.Sq, BH, p.n_v, D, n_cu) && !p.redo_always) return launch_attn_rows(p, BH, D, n_cu, st);
     p.group_slots = (int)tail_slots(t, p.out_bf16 != 0);
     const int64_t slots = (int64_t)p.group_slots * p.n_groups;
     if (ws == nullptr || slots > ws_slots) return hipErrorInvalidValue;
@@ -989,7 +990,6 @@ static hipError_t launch_sp(AttnParams p, int BH, float* ws, int64_t ws_slots, h
         for (int j = 0; j < t.split; ++j)
             if (t.part_off[j + 1] <= t.part_off[j] || t.part_off[j] % 64 != 0) return hipErrorInvalidValue;
     }
-    if (rows_form(t, p.Sq, BH, p.n_v, D, n_cu) && !p.redo_always) return launch_attn_rows(p, BH, D, n_cu, st);
     p.tiles_per_head = t.tiles_per_head;
     p.split = t.split;
     p.n_cut = (int)t.n_cut;

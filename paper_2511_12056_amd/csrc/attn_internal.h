@@ -311,6 +311,27 @@ std::vector<PipelineStep> pipeline_steps(const Sizes& sizes, int B, int64_t Sq, 
     }
     return steps;
 }
+// Steps whose launches take the kernel for few query rows need neither workgroups all at once nor workspace, and where a round of
+// that kernel is over before the host has issued the next step (launch, event, wait and hand-off: 20 us, of which the wait on the
+// drain stream takes 8), consecutive ones go out as one launch of up to three rounds (six blocks of 32 rows per
+// CU).  24 x 2 048, d = 128, head by head: three launches of eight heads 130 us, one launch 112.  With longer rounds (over 2 048 keys
+// at d = 128, 4 096 at d = 64) the GPU is the slower side, and the hand-off of a step overlaps the next one.
+inline std::vector<PipelineStep> join_steps(const std::vector<PipelineStep>& steps, int B, int64_t Sq, int64_t n_v, int d, int n_cu, bool alone) {
+    std::vector<PipelineStep> out;
+    for (const PipelineStep& s : steps) {
+        if (!alone && !out.empty() && out.back().hg == s.hg && n_v * d <= 2048 * 128) {
+            PipelineStep& last = out.back();
+            const int BH = B * s.hg;
+            const int64_t blocks = (Sq + 31) / 32 * BH;
+            if ((last.groups + s.groups) * blocks <= 6 * (int64_t)n_cu && rows_form(plan_tail(Sq, BH, n_v, n_cu), Sq, BH, n_v, d, n_cu)) {
+                last.groups += s.groups;
+                continue;
+            }
+        }
+        out.push_back(s);
+    }
+    return out;
+}
 // One workspace slot holds one key-range partial of a cut tile: 256 x 128 values + 256 lse.
 // A workspace of n slots is n * kSlotFloats floats followed by kCounterFloats floats that hold the
 // kernel's two work counters (zero whenever no launch is running on it).

@@ -202,3 +202,78 @@ def test_two_blocks_of_rows_give_the_bits_of_one(Sq, d, n_v):
         for h in (0, 7, 12):
             o, l = _launch(entry, *(t[:, h:h + 1].contiguous() for t in (q, k, v)), d ** -0.5, n_v)
             assert torch.equal(out[:, h], o[:, 0]) and torch.equal(lse[:, h], l[:, 0]), (entry, h)
+
+
+JOIN = r"""
+#include "attn_internal.h"
+#include <stdio.h>
+int main() {
+    long long Sq, n_v;
+    int B, d, n_cu, alone, hg, n;
+    while (scanf("%d %lld %lld %d %d %d %d %d", &B, &Sq, &n_v, &d, &n_cu, &alone, &hg, &n) == 8) {
+        const std::vector<int> sizes(n, hg);
+        const auto steps = pda::pipeline_steps(sizes, B, Sq, n_v, n_cu, alone != 0);
+        for (const auto& s : pda::join_steps(steps, B, Sq, n_v, d, n_cu, alone != 0)) printf("%d:%d:%d ", s.h0, s.hg, s.groups);
+        printf("\n");
+    }
+}
+"""
+
+
+def test_joined_steps(tmp_path):
+    """Steps of a pipeline in one launch: every head once and in order, none beyond six blocks of 32 rows per compute unit
+    unless one step is, none joined outside the rule."""
+    if not os.path.exists(CLANG):
+        pytest.skip("no ROCm clang++ here")
+    src, exe = tmp_path / "join.cpp", tmp_path / "join"
+    src.write_text(JOIN)
+    subprocess.run([CLANG, "-std=c++17", "-O1", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include", "-I", CSRC, str(src), "-o", str(exe)],
+                   check=True, timeout=120)
+    rng = random.Random(24)
+    cases = [(1, 2048, 2048, 128, 256, 0, 1, 24), (1, 2048, 2048, 128, 256, 1, 1, 24), (1, 2048, 2049, 128, 256, 0, 1, 24), (1, 2048, 2049, 64, 256, 0, 1, 49),
+             (1, 2048, 1000, 64, 256, 0, 1, 24)]
+    for _ in range(1500):
+        cases.append((rng.randint(1, 2), rng.randint(1, 5000), rng.randint(900, 5000), rng.choice([64, 128]), rng.choice([256, 256, 304, 64]),
+                      rng.randint(0, 4) // 4, rng.randint(1, 3), rng.randint(0, 60)))
+    out = subprocess.run([str(exe)], input="\n".join(" ".join(map(str, c)) for c in cases), capture_output=True, text=True, check=True, timeout=120)
+    rows = [[tuple(map(int, x.split(":"))) for x in l.split()] for l in out.stdout.split("\n")][:len(cases)]
+    assert [len(r) for r in rows[:5]] == [1, 24, 3, 3, 1]
+    for (B, Sq, n_v, d, n_cu, alone, hg, n), steps in zip(cases, rows):
+        assert sum(g for _, _, g in steps) == n and all(h == hg for _, h, _ in steps)
+        assert [h0 for h0, _, _ in steps] == [sum(g * hg for _, _, g in steps[:i]) for i in range(len(steps))]
+        plan = tail_plan(B * hg, Sq, n_v, d, n_cu)
+        items = plan["n_tiles"] + plan["n_cut"] * (plan["split"] - 1)
+        alone_fit = n_cu // items if 2 * items <= n_cu else 1               # groups of a launch without joining
+        for _, _, g in steps:
+            if alone:
+                assert g == 1
+            elif g > alone_fit:
+                assert rows_form(B * hg, Sq, n_v, d, n_cu) and n_v * d <= 2048 * 128 and g * B * hg * -(-Sq // 32) <= 6 * n_cu
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("S,n_v,d,groups", [(1100, 1100, 128, [1] * 50), (2000, 2000, 64, [1] * 20 + [2] * 9), (1030, 1025, 128, [3] * 8 + [1])])
+def test_joined_launches_of_a_pipeline(S, n_v, d, groups):
+    """Each group the bits of its own launch, the hand-off complete; more groups than one launch takes."""
+    import torch
+    import paper_2511_12056_amd as pda
+    H = sum(groups)
+    gen = torch.Generator(device="cuda").manual_seed(S)
+    q, k, v = (torch.randn(1, H, S, d, generator=gen, device="cuda").to(torch.bfloat16) for _ in range(3))
+    ref, rlse = torch.empty(1, H, S, d, device="cuda"), torch.empty(1, H, S, device="cuda")
+    h0 = 0
+    for g in groups:
+        if _n_cu() == 256:
+            assert rows_form(g, S, n_v, d, 256)
+        sl = slice(h0, h0 + g)
+        pda.attn_fwd_strided(q[:, sl], k[:, sl], v[:, sl], ref[:, sl], rlse[:, sl], 0.1, n_v)
+        h0 += g
+    cs, ds = torch.cuda.Stream(), torch.cuda.Stream()
+    for layout in (pda.PDA_SINK_HEAD_MAJOR, pda.PDA_SINK_TOKEN_FINAL):
+        out, lse = torch.full_like(ref, float("nan")), torch.full_like(rlse, float("nan"))
+        sink = torch.full((1, H, S, d) if layout == pda.PDA_SINK_HEAD_MAJOR else (1, S, H, d), float("nan"), device="cuda")
+        torch.cuda.synchronize()
+        pda.headchunk_run_ex(q, k, v, out, lse, 0.1, groups, cs, ds, sink_layout=layout, kv_valid_len=n_v, sink=sink)
+        cs.synchronize(); ds.synchronize()
+        assert torch.equal(out, ref) and torch.equal(lse, rlse)
+        assert torch.equal(sink, ref if layout == pda.PDA_SINK_HEAD_MAJOR else ref.transpose(1, 2))
