@@ -231,7 +231,7 @@ def next_rows(pda, torch, w, q, k, v, out, lse, sink, cs, ds, t_linear_ms):
     res["attn_base2_scale_folded_into_q_pack"] = {"bound": "mfma", "launch_ms": ms, "flops_per_launch": fl,
                                                   "achieved": fl / (ms * 1e-3) * 1e-12, "peak": PEAK_BF16_TFLOPS,
                                                   "unit": "TFLOP/s", "frac": fl / (ms * 1e-3) * 1e-12 / PEAK_BF16_TFLOPS,
-                                                  "kernel": "attn_fwd_sp_kernel<128, 8, true, false> (one 3-head group)"}
+                                                  "kernel": "attn_fwd_wide_kernel<128, true, false> (one 3-head group)"}
     del xq, q2
 
     # the d = 64 instance of the attention kernel on a long sequence (the workloads have d = 64 only in
@@ -245,8 +245,8 @@ def next_rows(pda, torch, w, q, k, v, out, lse, sink, cs, ds, t_linear_ms):
     res["attn_d64_6_heads_x_67576"] = {"bound": "latency", "launch_ms": ms, "flops_per_launch": fl,
                                        "achieved": fl / (ms * 1e-3) * 1e-12, "unit": "TFLOP/s",
                                        "frac_of_bf16_mfma_peak": fl / (ms * 1e-3) * 1e-12 / PEAK_BF16_TFLOPS,
-                                       "kernel": "attn_fwd_sp_kernel<64, 8, false, false>",
-                                       "note": "half the MFMA work per score: matrix pipe 56 % and VALU issue 71 % busy, neither full"}
+                                       "kernel": "attn_fwd_wide_kernel<64, false, false>",
+                                       "note": "half the MFMA work per score: matrix pipe 55 % and VALU issue 72 % busy, neither full"}
     del q64, k64, v64, o64, l64
 
     # head-chunk pipeline with the post-processing folded into the hand-off (token-major, final order)
@@ -386,10 +386,10 @@ def main():
                                "c5_720p_split_merge (6 heads: 3 query ranges, 4 key chunks + merge)",
                    "B": w.B, "H": w.H, "d": w.d, "S": w.Sq, "heads_per_group": w.heads_per_group,
                    "seed": w.seed, "flops_per_step": flops_step},
-        "roofline": {"kernel": "attn_fwd_sp_kernel<128, 8, false, false> (one 3-head group)", "bound": "mfma", "achieved": achieved,
+        "roofline": {"kernel": "attn_fwd_wide_kernel<128, false, false> (one 3-head group)", "bound": "mfma", "achieved": achieved,
                      "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s", "frac": achieved / PEAK_BF16_TFLOPS,
                      "launch_ms": launch_ms, "flops_per_launch": flops_launch,
-                     "traffic": measured_traffic("attn_fwd_sp_kernel_3head_group")},
+                     "traffic": measured_traffic("attn_fwd_kernel_3head_group")},
         "roofline_merge": {"kernel": "merge_kernel<4>", "bound": "hbm", "achieved": merge_bytes / (merge_ms * 1e-3) * 1e-9,
                            "peak": PEAK_HBM_GBS, "unit": "GB/s",
                            "frac": merge_bytes / (merge_ms * 1e-3) * 1e-9 / PEAK_HBM_GBS,
