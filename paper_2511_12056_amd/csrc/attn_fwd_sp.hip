@@ -1000,7 +1000,7 @@ static hipError_t launch_sp(AttnParams p, int BH, float* ws, int64_t ws_slots, h
     p.counter = reinterpret_cast<int*>(ws + ws_slots * kSlotFloats);     // two ints behind the slots, zero between launches
     const int64_t items = p.n_full + t.n_cut * t.split;
     hipError_t e;
-    const WidePlan wide = p.n_groups > 1 || p.redo_always ? WidePlan{0, 0} : wide_plan(t, p.n_v, n_cu);
+    const WidePlan wide = p.n_groups > 1 || p.redo_always || !wide_pays(t, p.n_v, D, BASE2, n_cu) ? WidePlan{0, 0} : wide_plan(t, p.n_v, n_cu);
     if (wide.items > 0) {
         p.n_wide = wide.items;
         p.n_odd = wide.odd_heads;

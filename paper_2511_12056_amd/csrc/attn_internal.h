@@ -228,8 +228,8 @@ inline int sp_wavefronts(const TailPlan& t, int64_t n_v, int d, int n_cu) {
 //                 24 x 5 000 289 -> 247 / 180 -> 158 (1.88 rounds, uncut)
 //   short ones:   24 x 16 384 on 1 536 keys 292 -> 271 / 177 -> 162, on 570 154 -> 150 / 100 -> 86, on 224 110 -> 102 / 67 -> 55;
 //                 48 x 4 800 on 400 92 -> 76 / 61 -> 52; 400 x 301 on 700 99 -> 86 / 68 -> 60
-// Of 96 shapes (1 to 12 rounds, 224 to 119 056 keys, fp32, bf16 and base-2 results) one is slower, by 0.4 % (24 x 9 600, d = 64,
-// base 2).  Below 224 keys the first steps of a sweep would not find the whole tiles they fetch.
+// Of 64 shapes (1 to 12 rounds, 224 to 119 056 keys, fp32 and bf16 results, and base 2 at d = 128) none is slower; base 2 at
+// d = 64: wide_pays.  Below 224 keys the first steps of a sweep would not find the whole tiles they fetch.
 constexpr int64_t kWideKeys = 224;
 struct WidePlan { int items, odd_heads; };
 inline WidePlan wide_plan(const TailPlan& t, int64_t n_v, int n_cu) {
@@ -240,6 +240,16 @@ inline WidePlan wide_plan(const TailPlan& t, int64_t n_v, int n_cu) {
     int64_t n = (n_cu - rem) * (rounds / 2) + rem * ((rounds + 1) / 2);
     if (n > have) n = have;
     return {(int)n, t.tiles_per_head % 2 ? (int)(n / pairs) : 0};
+}
+// Do the pairs pay?  At d = 64 with scores in base 2 (no scale left to apply, so the single tiles of attn_fwd_sp.hip have the least
+// to do beside the products) only for short sweeps: the phases of a pair, seeded scores among them, take 1 to 4 % longer, what
+// pairs save is between items and in the last round (us, without -> with pairs: 24 x 9 600 on 3 000 keys 192 -> 188, on 9 600
+// 517 -> 524, 24 x 6 400 on 65 536 2 200 -> 2 293; 24 x 5 000, under two rounds, on 9 600 287 -> 286, on 32 768 894 -> 900; 19 x
+// 24 087, seven rounds, on 512 99 -> 96, 24 x 26 708 on 768 163 -> 160, 19 x 24 087 on 1 024 149 -> 152, on 65 536 6 456 -> 6 696).
+inline bool wide_pays(const TailPlan& t, int64_t n_v, int d, bool base2, int n_cu) {
+    if (d != 64 || !base2) return true;
+    if (t.n_tiles < 2 * (int64_t)n_cu) return n_v <= 9600;
+    return n_v <= (t.n_tiles <= 4 * (int64_t)n_cu ? 3072 : 768);
 }
 // Does a launch with plan `t` (of one group, if several share it) take the kernel for few query rows (attn_rows.hip: its
 // wavefronts share the keys) instead of cut tiles and their merge?  Only launches in which every tile is cut: rows of whole
