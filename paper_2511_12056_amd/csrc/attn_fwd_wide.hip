@@ -261,11 +261,12 @@ __global__ __launch_bounds__(512, 2) void attn_fwd_wide_kernel(const AttnParams)
             };
             // Base 2: the scores start from minus the reference, not from zero.  There are registers for that only as P dies:
             // the first block's are set in the second half of PV, the second block's during the first two products
-            // of the first block.
+            // of the first block.  Ordinary moves, each anchored by an empty statement: a VALU write needs two wait states before
+            // an MFMA that reads the register, and the compiler inserts none behind a move written in assembly.
             auto seed = [&](auto b_c, auto lo, auto hi) __attribute__((always_inline)) {
                 static_for<decltype(lo)::value, decltype(hi)::value>([&](auto r) {
-                    float x;
-                    asm volatile("v_mov_b32 %0, %1" : "=v"(x) : "v"(neg_mc[decltype(b_c)::value]));
+                    float x = neg_mc[decltype(b_c)::value];
+                    asm volatile("" : "+v"(x));
                     s[decltype(b_c)::value][decltype(r)::value] = x;
                 });
             };
