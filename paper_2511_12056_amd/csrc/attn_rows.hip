@@ -9,7 +9,8 @@
 //
 // MFMA formulation, operand order and LDS swizzle are those of attn_fwd_sp.hip; tiles of 32 keys, one of K and one of V per
 // wavefront: K tile t+1 travels under the softmax and PV of tile t, V tile t+1 under the next QK and softmax.  The
-// reference is a running max that moves when the max grew by more than 2^8.
+// reference is a running max that moves when the max grew by more than 2^8.  It starts from the lowest finite value, not from
+// -inf: keys that score -inf then weigh 0 also where they are the first of a share (-inf - -inf would make the row NaN).
 //
 // What bounds it: every workgroup streams all keys of its head into LDS, 4 d bytes per key, at 110 GB/s per CU (53 of
 // the 64 bytes a clock that the vector cache can deliver), against 2 us of MFMA time for 32 rows and 1 024 keys at
@@ -19,6 +20,7 @@
 // attn_internal.h, rows_blocks.  KS = 8: two wavefronts per SIMD; d = 64 needs 70 KB of LDS, so two workgroups share a CU (16
 // wavefronts of 32 rows, one workgroup per CU: 8 x 2 048 rows 16.3 -> 20.0 us).
 #include <hip/hip_runtime.h>
+#include <float.h>
 #include <stdint.h>
 #include "attn_internal.h"
 #include "attn_device.h"
@@ -132,7 +134,7 @@ __global__ __launch_bounds__(64 * KS, 2) void attn_rows_kernel(const AttnParams 
     f32x16 o_acc[NR][NDB];
 #pragma unroll
     for (int i = 0; i < NR; ++i) {
-        mc[i] = -INFINITY;
+        mc[i] = -FLT_MAX;
         l_run[i] = 0.f;
 #pragma unroll
         for (int db = 0; db < NDB; ++db)
@@ -229,7 +231,7 @@ __global__ __launch_bounds__(64 * KS, 2) void attn_rows_kernel(const AttnParams 
             }
         const float l_tot = pair_sum(l_run[i]);
         if (lh == 0) {
-            st_m[wave * kRows + li] = mc[i];
+            st_m[wave * kRows + li] = l_tot == 0.f ? -INFINITY : mc[i];        // -inf: no keys, or none above -inf
             st_l[wave * kRows + li] = l_tot;
         }
         __syncthreads();
