@@ -238,30 +238,32 @@ __global__ __launch_bounds__(64 * KS, 2) void attn_rows_kernel(const AttnParams 
 #pragma unroll
         for (int n = tid; n < kRows * G4; n += 64 * KS) {
             const int r = n / G4, g = n % G4, row = i * kRows + r;
-            float m[KS], big = -INFINITY;
+            float f[KS], big = -INFINITY, tot = 0.f;
 #pragma unroll
             for (int w = 0; w < KS; ++w) {
-                m[w] = st_m[w * kRows + r];
-                big = fmaxf(big, m[w]);
+                f[w] = st_m[w * kRows + r];
+                big = fmaxf(big, f[w]);
             }
-            f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-            float tot = 0.f;
 #pragma unroll
             for (int w = 0; w < KS; ++w) {
-                const float f = __builtin_amdgcn_exp2f(m[w] - big);           // 0 for a wavefront without keys
+                f[w] = __builtin_amdgcn_exp2f(f[w] - big);                    // 0 for a wavefront without keys
+                tot = __builtin_fmaf(f[w], st_l[w * kRows + r], tot);
+            }
+            const float inv = 1.0f / tot;
+            f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int w = 0; w < KS; ++w) {       // normalised one by one: their plain sum may leave fp32 where the result does not
                 const f32x4 x = *(LDS_PTR(const f32x4))(part + w * (2 * TILE) + r * (D * 4) + ((g ^ (r % G4)) * 16));
 #pragma unroll
-                for (int e = 0; e < 4; ++e) acc[e] = __builtin_fmaf(f, x[e], acc[e]);
-                tot = __builtin_fmaf(f, st_l[w * kRows + r], tot);
+                for (int e = 0; e < 4; ++e) acc[e] = __builtin_fmaf(f[w] * inv, x[e], acc[e]);
             }
             if (row < rows) {
-                const float inv = 1.0f / tot;
                 const int64_t at = (int64_t)b * p.o_bs + (int64_t)h * p.o_hs + (row0 + row) * D + g * 4;
                 if (p.out_bf16)
                     *reinterpret_cast<u32x2*>(reinterpret_cast<__bf16*>(p.out) + at) =
-                        u32x2{pack_bf16(acc[0] * inv, acc[1] * inv), pack_bf16(acc[2] * inv, acc[3] * inv)};
+                        u32x2{pack_bf16(acc[0], acc[1]), pack_bf16(acc[2], acc[3])};
                 else
-                    *reinterpret_cast<f32x4*>(p.out + at) = f32x4{acc[0] * inv, acc[1] * inv, acc[2] * inv, acc[3] * inv};
+                    *reinterpret_cast<f32x4*>(p.out + at) = acc;
                 if (g == 0) {                // ln of the mantissa only: the error of the logarithm grows with its value
                     int e;
                     const float f = frexpf(tot, &e);

@@ -49,3 +49,21 @@ def test_keys_that_score_minus_infinity(H, Sq, n_v, hidden, d, entry, low):
     ro, rl = _reference(qb, f32_to_bf16_bits(kb64), vb, scale)
     o, l = _launch(entry, to_dev_bf16(qb), to_dev_bf16(kb), to_dev_bf16(vb), scale, n_v)
     _check(o, l, ro, rl)
+
+
+@pytest.mark.parametrize("entry", ["fp32", "bf16", "base2"])
+@pytest.mark.parametrize("d", [128, 64])
+@pytest.mark.parametrize("H,Sq,n_v", [(1, 70, 1024), (13, 1000, 1100)])
+def test_values_near_the_largest_float(H, Sq, n_v, d, entry):
+    """Values of 5e35: 512 of them, the keys of a range of the cut form, add up inside fp32, 1 024 of them do not."""
+    if _n_cu() == 256:
+        assert rows_form(H, Sq, n_v, d, 256)
+    rng = np.random.default_rng(n_v - d)
+    q, k, v = (rng.standard_normal((1, H, s, d)).astype(np.float32) for s in (Sq, n_v, n_v))
+    q *= np.float32(2.0 ** -6)                                      # nearly equal weights
+    v = np.float32(5e35) * (1 + v * np.float32(0.01))
+    qb, kb, vb = (f32_to_bf16_bits(x) for x in (q, k, v))
+    scale = np.log(2.0) if entry == "base2" else 1.0
+    ro, rl = _reference(qb, kb, vb, scale)
+    o, l = _launch(entry, to_dev_bf16(qb), to_dev_bf16(kb), to_dev_bf16(vb), scale, n_v)
+    _check(o, l, ro, rl)
