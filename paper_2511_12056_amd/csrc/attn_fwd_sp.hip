@@ -102,9 +102,11 @@ __device__ __forceinline__ int fresh_lane() {
 enum class Iter { MAIN, FIRST, TAIL, LAST };      // forms of an iteration of the sweep
 
 // Works off the units of a launch from `item` on (claiming the following ones unless `direct`) until one is not below
-// n_items.  AFTER_WIDE: behind the wide items of attn_fwd_wide.hip, which number and leave out units as described there.
+// n_items.  AFTER_WIDE: behind the wide items of attn_fwd_wide.hip, which number and leave out units as described there; if
+// `swept`, `item` is a single unit that has had its first sweep, of which this wavefront's rows `again` need the second one.
 template <int D, int NW, bool BASE2, bool OUT16, bool AFTER_WIDE, class Args>
-__device__ __forceinline__ void sp_items(const Args& p, int item, const int n_items, const bool direct, const int wave_in) {
+__device__ __forceinline__ void sp_items(const Args& p, int item, const int n_items, const bool direct, const int wave_in, const bool swept,
+                                         const unsigned again) {
     static_assert(D == 128 || D == 64, "head dimension");
     static_assert(NW == 8 || NW == 4, "wavefronts per workgroup");
     constexpr int BN = 64;
@@ -816,9 +818,10 @@ __device__ __forceinline__ void sp_items(const Args& p, int item, const int n_it
     // The next item is claimed as late as possible (the order of the items balances the end of the
     // launch): one iteration before the last, in which its Q and first K tiles travel; V follows with the stores.
     // Sweeps of one or two tiles claim it in the last one and begin it with the stores.
-    sweep(std::false_type{});
     uint64_t store_mask = ~0ull;                      // lanes whose results are still to be stored
-    {
+    int any = 1;
+    if (!AFTER_WIDE || !swept) {
+        sweep(std::false_type{});
         // A row whose sum left the safe range (a later score exceeded the first tile's max by more
         // than ~2^64, or non-finite input) or whose accumulators are not finite takes its result from a
         // second sweep with the running max (weights <= 2^8 there).  The workgroup sweeps together, but
@@ -838,25 +841,30 @@ __device__ __forceinline__ void sp_items(const Args& p, int item, const int n_it
         redo |= redo << 32 | redo >> 32;             // lanes l and l + 32 hold one row
         if (lane == 0) redo_flag[wave] = redo != 0 ? 1 : 0;
         barrier();                                   // flags are written, and every wavefront is done with the LDS tiles
-        int any = 0;
+        any = 0;
 #pragma unroll
         for (int w = 0; w < NW; ++w) any |= redo_flag[w];
+        any = __builtin_amdgcn_readfirstlane(any);
         if (!begun && !direct) next = __builtin_amdgcn_readfirstlane(next_item);
-        if (__builtin_expect(__builtin_amdgcn_readfirstlane(any), 0)) {
+        if (__builtin_expect(any, 0)) {
             locate();
             store_results(~redo);
             store_mask = redo;
             begin_item(item);                        // again: the next one may have taken its place
             issue_first_v();
-            __builtin_amdgcn_s_waitcnt(kWaitVm0);
-            arrange_q();
-            sweep(std::true_type{});
-            // Q is fetched anew from here.  The compiler does not know it and would keep the old fragments through the
-            // last iteration above, up to six registers more than there are.
-#pragma unroll
-            for (int kk = 0; kk < NKK; ++kk) asm volatile("" : "=v"(qf[kk]));
-            barrier();                               // as above, before the next item's tiles are fetched
         }
+    } else {
+        store_mask = (uint64_t)again << 32 | again;
+    }
+    if (__builtin_expect(any, 0)) {
+        __builtin_amdgcn_s_waitcnt(kWaitVm0);
+        arrange_q();
+        sweep(std::true_type{});
+        // Q is fetched anew from here.  The compiler does not know it and would keep the old fragments through the
+        // last iteration above, up to six registers more than there are.
+#pragma unroll
+        for (int kk = 0; kk < NKK; ++kk) asm volatile("" : "=v"(qf[kk]));
+        barrier();                                   // as above, before the next item's tiles are fetched
     }
     locate();
     if (next < n_items) {
@@ -872,7 +880,7 @@ __device__ __forceinline__ void sp_items(const Args& p, int item, const int n_it
 
 template <int D, int NW, bool BASE2, bool OUT16>
 __global__ __launch_bounds__(64 * NW, 2) void attn_fwd_sp_kernel(const AttnParams p) {
-    sp_items<D, NW, BASE2, OUT16, false>(p, (int)blockIdx.x, p.n_items, p.n_items <= (int)gridDim.x, 0);
+    sp_items<D, NW, BASE2, OUT16, false>(p, (int)blockIdx.x, p.n_items, p.n_items <= (int)gridDim.x, 0, false, 0);
 }
 
 #ifndef PDA_SP_DEVICE_ONLY

@@ -19,8 +19,11 @@
 // others follow in the same workgroups (sp_items): the last tile of each head of an odd number of tiles that wide items cover,
 // then whatever lies behind the wide items.  How many are wide: attn_internal.h, wide_plan.  A row gets the bits it has in a
 // single tile: same reference, same order of sums.  Rows that need the second sweep get it there, too: a wide item
-// hands back a tile with such a row, and the workgroup sweeps it as a single tile later; if it has collected sixteen, it
-// takes no more wide items than it has claimed and sweeps those as single tiles.
+// hands back a tile with such a row, and the workgroup makes the running-max sweep of that tile later, for the rows that the wide
+// item has found; if it has collected sixteen, it takes no more wide items than it has claimed and sweeps those as single tiles.
+// With every row swept twice 24 x 9 600 take 1 820 us, 3 x 67 576 10 170 (2 290 and 13 530 with the first sweep of a tile given
+// back repeated as well; without pairs 1 870 and 10 620).  Where few rows need it in short sweeps, pairs cost: 24 x 16 384 on 570
+// keys with one such row in 500 takes 200 us (267 with that sweep repeated), without pairs, in items of 128 rows, 179.
 #ifndef PDA_SP_DEVICE_ONLY
 #define PDA_SP_DEVICE_ONLY
 #endif
@@ -60,6 +63,7 @@ __global__ __launch_bounds__(512, 2) void attn_fwd_wide_kernel(const AttnParams)
     __shared__ int w_next;
     __shared__ int w_flag[8];
     __shared__ int w_redo[kRedoMax];
+    __shared__ unsigned w_rows[kRedoMax][8];           // of a tile given back: the rows that need the second sweep, 32 each
 
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     const bool second = wave >= 4;                     // the group of wavefronts that runs a phase behind
@@ -433,19 +437,19 @@ __global__ __launch_bounds__(512, 2) void attn_fwd_wide_kernel(const AttnParams)
                 if (!second) barrier();
 
                 // ---- rows whose sum or accumulators left the safe range: their tiles are swept again by the other items' code
-                bool bad = false;
-                float x = 0.f;
+                unsigned bad_rows[2];                      // of this wavefront's two blocks
 #pragma unroll
                 for (int i = 0; i < 2; ++i) {
-                    bad |= !(pair_sum(l_run[i]) < 1.8446744e19f);
+                    float x = 0.f;
 #pragma unroll
                     for (int db = 0; db < NDB; ++db)
 #pragma unroll
                         for (int r = 0; r < 16; ++r) x = __builtin_fmaf(o[i][db][r], 0.0f, x);
+                    const bool bad = !(pair_sum(l_run[i]) < 1.8446744e19f) || !(x == 0.f);
+                    const uint64_t lanes = __builtin_amdgcn_ballot_w64(bad);      // lanes l and l + 32 hold one row
+                    bad_rows[i] = (unsigned)lanes | (unsigned)(lanes >> 32);
                 }
-                bad |= !(x == 0.f);
-                const int any = __builtin_amdgcn_ballot_w64(bad) != 0;
-                if (fresh_lane() == 0) w_flag[wave] = any;
+                if (fresh_lane() == 0) w_flag[wave] = (bad_rows[0] | bad_rows[1]) != 0;
                 lds_done();
                 barrier();                                 // and every wavefront is done with V
                 int bad_tile[2] = {0, 0};
@@ -459,6 +463,10 @@ __global__ __launch_bounds__(512, 2) void attn_fwd_wide_kernel(const AttnParams)
                 for (int i = 0; i < 2; ++i)
                     if (__builtin_amdgcn_readfirstlane(bad_tile[i])) {
                         if (wave == 0 && fresh_lane() == 0) w_redo[n_redo] = (b * p.Hg + h) * p.tiles_per_head + (int)((row0 - wave * 64) / kTileRows) + i;
+                        if (wave / 4 == i && fresh_lane() == 0) {
+                            w_rows[n_redo][wave % 4 * 2] = bad_rows[0];
+                            w_rows[n_redo][wave % 4 * 2 + 1] = bad_rows[1];
+                        }
                         ++n_redo;
                     }
                 if (item < n_wide) begin_rest(item);
@@ -525,12 +533,15 @@ __global__ __launch_bounds__(512, 2) void attn_fwd_wide_kernel(const AttnParams)
     // ---- the other units of the launch; first the tiles given back, and the wide items of a workgroup whose list was full
     __builtin_amdgcn_s_waitcnt(kWaitVm0);                      // no load into LDS and no store of a tile given back is under way
     lds_done();
-    barrier();                                                 // w_redo is written, LDS is free
+    barrier();                                                 // w_redo and w_rows are written, LDS is free
     KernelArgs& p = args_here();
+    bool swept = true;                                         // the tiles of the list lack the running-max sweep only
     for (bool more = true; more;) {
         int unit, end = 0x7fffffff;
+        unsigned again = 0;
         if (n_redo > 0) {
             unit = p.n_items + __builtin_amdgcn_readfirstlane(w_redo[--n_redo]);
+            again = __builtin_amdgcn_readfirstlane(w_rows[n_redo][wave]);
         } else if (item < n_wide) {
             if (wave == 0 && fresh_lane() == 0) {
                 const int pairs_per_head = p.tiles_per_head >> 1, bh = item / pairs_per_head;
@@ -541,14 +552,15 @@ __global__ __launch_bounds__(512, 2) void attn_fwd_wide_kernel(const AttnParams)
             lds_done();
             barrier();
             n_redo = 2;
+            swept = false;
             item = __builtin_amdgcn_readfirstlane(w_next);
             continue;
         } else {
-            more = false;
+            more = swept = false;
             unit = item < 0x7fffffff - n_wide ? item + n_wide : item;
             end = p.n_items;
         }
-        sp_items<D, 8, BASE2, OUT16, true>(p, unit, end, direct || more, wave);
+        sp_items<D, 8, BASE2, OUT16, true>(p, unit, end, direct || more, wave, swept, again);
         __builtin_amdgcn_s_waitcnt(kWaitVm0);
         lds_done();
         barrier();
