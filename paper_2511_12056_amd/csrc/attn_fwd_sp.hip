@@ -77,9 +77,6 @@ __device__ __forceinline__ void lds_dma16_at(const void* sbase, unsigned voff, u
                  : "memory", "scc", "m0", "vcc");
 }
 
-// BASE2: the scores are already in units of log2 (the caller folded scale*log2(e) into Q), so the
-// weights are 2^(q.k) and the first sweep needs no arithmetic before the exponential at all: the
-// score accumulators start from minus the row's reference instead of from zero.
 // The last workgroup to leave puts both counters back to zero for the next launch that uses this
 // workspace (launches sharing a workspace are ordered on one stream).  Every workgroup has made
 // its last fetch before it counts itself out, so nobody fetches after the reset.
@@ -101,6 +98,10 @@ __device__ __forceinline__ int fresh_lane() {
 
 enum class Iter { MAIN, FIRST, TAIL, LAST };      // forms of an iteration of the sweep
 
+// BASE2: the scores are already in units of log2 (the caller folded scale*log2(e) into Q), so the
+// weights are 2^(q.k) and the first sweep needs no arithmetic before the exponential at all: the
+// score accumulators start from minus the row's reference instead of from zero.
+//
 // Works off the units of a launch from `item` on (claiming the following ones unless `direct`) until one is not below
 // n_items.  AFTER_WIDE: behind the wide items of attn_fwd_wide.hip, which number and leave out units as described there; if
 // `swept`, `item` is a single unit that has had its first sweep, of which this wavefront's rows `again` need the second one.
@@ -819,7 +820,17 @@ __device__ __forceinline__ void sp_items(const Args& p, int item, const int n_it
     // launch): one iteration before the last, in which its Q and first K tiles travel; V follows with the stores.
     // Sweeps of one or two tiles claim it in the last one and begin it with the stores.
     uint64_t store_mask = ~0ull;                      // lanes whose results are still to be stored
-    int any = 1;
+    auto second_sweep = [&]() __attribute__((always_inline)) {
+        __builtin_amdgcn_s_waitcnt(kWaitVm0);
+        arrange_q();
+        sweep(std::true_type{});
+        // Q is fetched anew from here.  The compiler does not know it and would keep the old fragments through the
+        // last iteration above, up to six registers more than there are.
+#pragma unroll
+        for (int kk = 0; kk < NKK; ++kk) asm volatile("" : "=v"(qf[kk]));
+        barrier();                                   // as above, before the next item's tiles are fetched
+    };
+    int any = 0;
     if (!AFTER_WIDE || !swept) {
         sweep(std::false_type{});
         // A row whose sum left the safe range (a later score exceeded the first tile's max by more
@@ -841,31 +852,23 @@ __device__ __forceinline__ void sp_items(const Args& p, int item, const int n_it
         redo |= redo << 32 | redo >> 32;             // lanes l and l + 32 hold one row
         if (lane == 0) redo_flag[wave] = redo != 0 ? 1 : 0;
         barrier();                                   // flags are written, and every wavefront is done with the LDS tiles
-        any = 0;
 #pragma unroll
         for (int w = 0; w < NW; ++w) any |= redo_flag[w];
-        any = __builtin_amdgcn_readfirstlane(any);
         if (!begun && !direct) next = __builtin_amdgcn_readfirstlane(next_item);
-        if (__builtin_expect(any, 0)) {
+        if (__builtin_expect(__builtin_amdgcn_readfirstlane(any), 0)) {
             locate();
             store_results(~redo);
             store_mask = redo;
             begin_item(item);                        // again: the next one may have taken its place
             issue_first_v();
+            if constexpr (!AFTER_WIDE) second_sweep();
         }
     } else {
         store_mask = (uint64_t)again << 32 | again;
+        any = 1;
     }
-    if (__builtin_expect(any, 0)) {
-        __builtin_amdgcn_s_waitcnt(kWaitVm0);
-        arrange_q();
-        sweep(std::true_type{});
-        // Q is fetched anew from here.  The compiler does not know it and would keep the old fragments through the
-        // last iteration above, up to six registers more than there are.
-#pragma unroll
-        for (int kk = 0; kk < NKK; ++kk) asm volatile("" : "=v"(qf[kk]));
-        barrier();                                   // as above, before the next item's tiles are fetched
-    }
+    if constexpr (AFTER_WIDE)
+        if (__builtin_expect(__builtin_amdgcn_readfirstlane(any), 0)) second_sweep();      // one copy of it for both ways
     locate();
     if (next < n_items) {
         if (!begun) begin_item(next);
