@@ -176,7 +176,8 @@ def measure_config(pda, torch, idx, cs, tensors=None, oracle_rows=192):
            "frac_of_bf16_peak": flops / (med * 1e-3) * 1e-12 / PEAK_BF16_TFLOPS,
            "plan": pda.attn_tail_plan(w.B, H, w.Sq, n_v, w.d)}
     if idx == 1:
-        res["note"] = "cache resident and launch bound: 0.54 GFLOP per launch"
+        res["note"] = ("cache resident and launch bound: 0.54 GFLOP per launch; takes the kernel for few query rows, which cuts and "
+                       "merges nothing in memory: the plan is that of the cut form")
     o, l = out.cpu().numpy(), lse.cpu().numpy()
     errs = {}
     for h in sorted({0, H - 1}):

@@ -199,9 +199,10 @@ int launch_checked(const void* q, const void* k, const void* v, float* out, floa
         int n_cu = 0;
         hipError_t e = pda::device_cu_count(&n_cu);
         if (e != hipSuccess) return hip_fail(e, "device query");
-        // every launch of this kernel uses a workspace: its work counters, and the partial slots of cut tiles
+        // the work counters and the partial slots of cut tiles.  The kernel for few rows uses neither, but what a launch is refused for
+        // and that the first launch on a stream of whatever size allocates (a later one may be under capture) do not depend on it.
         const pda::TailPlan plan = pda::plan_tail(Sq, B * hg, n_v, n_cu);
-        // (groups in one launch of the kernel for few rows, however many, use no slots)
+        // (groups in one launch of that kernel may be more than the slots allow)
         const int64_t need = n_groups > 1 && pda::rows_form(plan, Sq, B * hg, n_v, d, n_cu) ? 0 : n_groups * pda::tail_slots(plan, out_bf16);
         if (kind == WS_STATIC) {
             if (need > kStaticSlots)

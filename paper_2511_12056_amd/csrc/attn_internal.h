@@ -189,26 +189,25 @@ inline TailPlan plan_tail(int64_t Sq, int BH, int64_t n_v, int n_cu) {
     }
     return t;
 }
-// Wavefronts per workgroup of a launch with plan `t` and no pairs of tiles (wide_plan below; those leave the second case of
-// four to sweeps of under 224 keys and to variant 3): eight (256 rows, one workgroup per CU) or four
-// (128 rows, half a tile; two per CU).  The results are the same bits; only the time differs (us,
+// Wavefronts per workgroup of a launch with plan `t` and no pairs of tiles (wide_plan, wide_pays below): eight (256 rows, one
+// workgroup per CU) or four (128 rows, half a tile; two per CU).  The results are the same bits; only the time differs (us,
 // eight -> four).  Eight is the rule: a K/V tile in LDS serves twice the rows, half the global -> LDS
 // traffic (3 heads x 67 576, d = 128: 5 530 -> 6 120; 10 x 9 600: 419 -> 471).  Four
 //  * where even the halves of the items do not fill every CU: twice the CUs work on the launch, one
 //    wavefront per SIMD (112 shapes of 1 to 128 tiles, 64 to 119 056 keys: none slower beyond the noise;
-//    1 head x 2 048 on 2 048, d = 128: 26.2 -> 19.7, d = 64: 19.2 -> 15.9; 1 x 1 024 on 119 056,
-//    d = 128: 149 -> 107);
+//    1 head x 1 024 on 119 056, d = 128: 149 -> 107);
 //  * for short sweeps (up to 24 key tiles) in more than four rounds of tiles: two workgroups share a CU
-//    and one computes while the other loads or stores, and the last round is spread more evenly (24 x
-//    16 384, d = 128, on 640 keys: 186 -> 177, on 1 536: 318 -> 310; 26 x 10 100 on 866: 167 -> 153,
-//    d = 64: 112 -> 102).  From 28 key tiles on both are the same within 1 %.  Not
-//      - in exactly four rounds (16 x 16 384, d = 128, on 1 536 keys: 210 -> 216), at d = 64 not in four
-//        to six rounds whose last is more than half full (80 x 4 096 on 512 keys: 89 -> 91);
+//    and one computes while the other loads or stores, and the last round is spread more evenly.  Pairs have taken over most of
+//    these launches.  What is left is fewer keys than pairs need (24 x 40 000, d = 128, on 128 keys 197 -> 186, on 200
+//    231 -> 219; 26 x 10 100 on 200 80.2 -> 77.4; 24 x 16 384 on 220 the same, but on 192, six full rounds, 91.8 -> 98.9), base 2 at
+//    d = 64 where pairs do not pay (193 x 1 900 on 1 000 145 -> 132; 26 x 10 100 on 866 93.0 -> 89.4, on 1 400 122 -> 122;
+//    24 x 16 384 on 800 to 1 536 within 1 %), and variant 3, which has no pairs.  Not
+//      - in exactly four rounds, at d = 64 not in four to six rounds whose last is more than half full;
 //      - with too few key tiles to hide the second workgroup's start behind: at d = 64, where a tile
-//        takes half the time, under eight (24 x 16 384 on 128 keys: 65 -> 73), at d = 128 under four
-//        unless there are six rounds (88 x 4 096 on 64 keys: 97 -> 100; 24 x 40 000 on 128: 243 -> 217);
+//        takes half the time, under eight (24 x 16 384 on 192 keys: 56.9 -> 63.7), at d = 128 under four
+//        unless there are six rounds (88 x 4 096 on 64 keys: 86 -> 87);
 //      - under eight tiles per head (four with up to four key tiles), where K and V of a head are fetched
-//        for few rows (400 x 700, d = 128, on 1 536 keys: 270 -> 289; 1 126 x 256 on 1 529: 286 -> 315).
+//        for few rows (1 126 x 256, d = 128, on 1 529 keys: 286 -> 315).
 inline int sp_wavefronts(const TailPlan& t, int64_t n_v, int d, int n_cu) {
     const int64_t items = t.n_tiles - t.n_cut + t.n_cut * t.split, key_tiles = (n_v + 63) / 64;
     if (2 * items <= n_cu) return 4;
@@ -230,6 +229,7 @@ inline int sp_wavefronts(const TailPlan& t, int64_t n_v, int d, int n_cu) {
 //                 48 x 4 800 on 400 92 -> 76 / 61 -> 52; 400 x 301 on 700 99 -> 86 / 68 -> 60
 // Of 64 shapes (1 to 12 rounds, 224 to 119 056 keys, fp32 and bf16 results, and base 2 at d = 128) none is slower; base 2 at
 // d = 64: wide_pays.  Below 224 keys the first steps of a sweep would not find the whole tiles they fetch.
+// (With rows that need the second sweep: attn_fwd_wide.hip.)
 constexpr int64_t kWideKeys = 224;
 struct WidePlan { int items, odd_heads; };
 inline WidePlan wide_plan(const TailPlan& t, int64_t n_v, int n_cu) {
@@ -256,9 +256,11 @@ inline bool wide_pays(const TailPlan& t, int64_t n_v, int d, bool base2, int n_c
 // tiles keep the bits of a sweep in one pass.  The time of that kernel goes by rounds of its workgroups (one per CU, at d = 64
 // two) and by the keys; the cut form hardly grows with the keys as long as CUs are free, but starts at 12 to 16 us.  So
 // the line lies at a number of keys that grows with the blocks of 32 rows up to the end of a round and falls behind it (us,
-// cut -> rows; of about 750 shapes of 1 to 1 024 blocks on 1 024 to 12 288 keys none that the rule takes is slower):
-//   d = 64:  2 x 1 024 rows on 1 024 keys (64 blocks) 13.6 -> 7.1, on 4 096 16.3 -> 16.0, on 5 120 17.6 -> 18.4;
-//            1 x 256 on 3 072 13.3 -> 12.2, on 4 096 13.8 -> 15.0; 8 x 1 024 on 6 144 27.4 -> 23.0, on 12 288 39.1 -> 42.7;
+// cut -> rows; of about 750 shapes of 1 to 1 024 blocks on 1 024 to 12 288 keys those that the rule takes are not slower, but for a few
+// blocks more than two rounds on 1 025 to 1 152 keys at d = 128: 17 x 1 024 on 1 152 29.1 -> 31.7, 22 x 1 024 on 1 100 33.9 -> 31.0.  The
+// reference of shares of twelve tiles and more has since cost up to 3 %, no line moved):
+//   d = 64:  2 x 1 024 rows on 1 024 keys (64 blocks) 14.0 -> 7.0, on 4 096 16.1 -> 15.8, on 5 120 17.6 -> 18.4;
+//            1 x 256 on 3 072 14.1 -> 12.6, on 4 096 13.8 -> 15.0; 8 x 1 024 on 6 144 27.4 -> 23.0, on 12 288 39.1 -> 42.7;
 //            16 x 1 024 on 4 096 30.8 -> 28.3, on 6 144 38.9 -> 40.5; 18 x 1 024 on 2 048 24.6 -> 21.9, on 3 072 29.1 -> 29.9
 //   d = 128: 1 x 1 024 on 1 024 15.9 -> 10.1, on 2 048 16.5 -> 13.9, on 3 072 17.3 -> 18.0; 4 x 1 024 on 5 120
 //            31.6 -> 26.5; 8 x 1 024 on 2 048 24.1 -> 15.8, on 8 192 48.4 -> 48.4; 9 x 1 024 on 1 024 20.5 -> 15.4, on 4 096
@@ -321,11 +323,15 @@ std::vector<PipelineStep> pipeline_steps(const Sizes& sizes, int B, int64_t Sq, 
     }
     return steps;
 }
-// Steps whose launches take the kernel for few query rows need neither workgroups all at once nor workspace, and where a round of
-// that kernel is over before the host has issued the next step (launch, event, wait and hand-off: 20 us, of which the wait on the
-// drain stream takes 8), consecutive ones go out as one launch of up to three rounds (six blocks of 32 rows per
-// CU).  24 x 2 048, d = 128, head by head: three launches of eight heads 130 us, one launch 112.  With longer rounds (over 2 048 keys
-// at d = 128, 4 096 at d = 64) the GPU is the slower side, and the hand-off of a step overlaps the next one.
+// Steps whose launches take the kernel for few query rows need neither workgroups all at once nor workspace, so consecutive ones can go
+// out as one launch of up to three rounds (six blocks of 32 rows per CU).  That saves the host's part of a step (launch,
+// event, wait and hand-off: 20 us, of which the wait on the drain stream takes 8), and it fills the CUs: a step is as many groups as the
+// cut form fills them with (batch_of_groups), with this kernel often half of that (us, head by head, apart -> joined: d = 128,
+// 24 x 1 536 116 -> 92, 24 x 2 048 140 -> 109, 48 x 1 024 on 2 048 122 -> 107; d = 64, 24 x 3 072 238 -> 139, 24 x 4 096 328 -> 198; where
+// one step holds all groups, 24 x 1 024, no difference).
+// The line, 2 048 keys at d = 128 and 4 096 at d = 64, is not where joining stops paying: 24 x 2 304 164 -> 133, 24 x 3 072
+// 294 -> 199, 24 x 5 120 811 -> 439, d = 64 24 x 4 608 590 -> 259, 24 x 6 144 657 -> 388, no shape of 12, 24 and 48 heads slower.  It
+// bounds how long the hand-offs of a joined launch, which all wait for its end, are held back (three rounds of 25 us).
 inline std::vector<PipelineStep> join_steps(const std::vector<PipelineStep>& steps, int B, int64_t Sq, int64_t n_v, int d, int n_cu, bool alone) {
     std::vector<PipelineStep> out;
     for (const PipelineStep& s : steps) {

@@ -5,7 +5,7 @@
 // every range in memory and a second launch that merges them; at 2 x 1 024 rows, d = 64, that was 13.6 us, of which 3 us
 // for the merge and most of the rest one wavefront per SIMD walking eight key tiles.  Here a workgroup finishes 32 query
 // rows: its KS wavefronts share the keys among them, sweep their shares independently of each other (own LDS tiles, own
-// waits, no barrier until the end) and add up their partial results in LDS.  One launch, no workspace.
+// waits, no barrier until the end) and add up their partial results in LDS.  One launch, and nothing in the workspace.
 //
 // MFMA formulation, operand order and LDS swizzle are those of attn_fwd_sp.hip; tiles of 32 keys, one of K and one of V per
 // wavefront: K tile t+1 travels under the softmax and PV of tile t, V tile t+1 under the next QK and softmax.  The
@@ -15,13 +15,15 @@
 // d = 128, cut in ranges 1.625e-3, reference from 32 keys 1.638e-3, now 1.606e-3; 4 x 1 024: 1.615, 1.635, 1.605).  It starts from the lowest finite value, not from
 // -inf: keys that score -inf then weigh 0 also where they are the first of a share (-inf - -inf would make the row NaN).
 //
-// What bounds it: every workgroup streams all keys of its head into LDS, 4 d bytes per key, at 110 GB/s per CU (53 of
-// the 64 bytes a clock that the vector cache can deliver), against 2 us of MFMA time for 32 rows and 1 024 keys at
-// d = 128 where the stream takes 4.8.  So a round of workgroups costs 3 us (start, sum, stores) and 5.3 us per 1 024
-// keys at d = 128, half of that at d = 64.  With two blocks of 32 rows (NR = 2) each K and V fragment feeds two MFMAs; Q is
-// then read from LDS beside K at d = 128 (in registers, 23 of them spilled and a tile took 2.4 us instead of 1.2).  When that pays:
-// attn_internal.h, rows_blocks.  KS = 8: two wavefronts per SIMD; d = 64 needs 70 KB of LDS, so two workgroups share a CU (16
-// wavefronts of 32 rows, one workgroup per CU: 8 x 2 048 rows 16.3 -> 20.0 us).
+// What bounds it: nothing is saturated.  Every workgroup streams all keys of its head into LDS, 4 d bytes per key.  One block of rows:
+// up to 110 GB/s per CU, of the 64 bytes a clock that the vector cache can deliver (a round of workgroups costs 3 us (start, sum,
+// stores) and 5.3 us per 1 024 keys at d = 128, half of that at d = 64), against 2 us of MFMA time for 32 rows and 1 024 keys at d = 128.
+// Two blocks of 32 rows (NR = 2), each K and V fragment feeding two MFMAs: a round on 2 048 keys takes 25 us, 42 GB/s per CU; in
+// three such rounds (24 x 2 048, d = 128, 78 us at 2.2 GHz) the matrix pipe is busy 29 % of the time, the VALU port 40 %, LDS
+// 22 %, and wavefronts wait 38 % of theirs: each of them does the products, the softmax and the products of a tile one after the
+// other, and there are two per SIMD.  Q is read from LDS beside K there at d = 128 (in registers, 23 of them spilled and a tile
+// took 2.4 us instead of 1.2).  When two blocks pay: attn_internal.h, rows_blocks.  KS = 8: two wavefronts per SIMD; d = 64 needs 70 KB of
+// LDS, so two workgroups share a CU (16 wavefronts of 32 rows, one workgroup per CU: 8 x 2 048 rows 16.3 -> 20.0 us).
 #include <hip/hip_runtime.h>
 #include <float.h>
 #include <stdint.h>
