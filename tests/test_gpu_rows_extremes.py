@@ -33,6 +33,7 @@ def _check(o, l, ro, rl):
 @pytest.mark.parametrize("H,Sq,n_v,hidden", [(1, 70, 1024, (128, 160)),      # the first tile of a wavefront's share
                                              (1, 70, 1024, (128, 256)),      # a whole share
                                              (1, 33, 1500, (160, 1100)),     # several, and parts of two
+                                             (2, 1024, 3072, (384, 420)),    # a long share, whose reference follows the max at first
                                              (13, 1000, 1100, (256, 300))])  # two row blocks a workgroup
 def test_keys_that_score_minus_infinity(H, Sq, n_v, hidden, d, entry, low):
     """K entries of -inf, or products beyond fp32, in keys that are the first of a wavefront's share."""
@@ -67,3 +68,16 @@ def test_values_near_the_largest_float(H, Sq, n_v, d, entry):
     ro, rl = _reference(qb, kb, vb, scale)
     o, l = _launch(entry, to_dev_bf16(qb), to_dev_bf16(kb), to_dev_bf16(vb), scale, n_v)
     _check(o, l, ro, rl)
+
+
+@pytest.mark.parametrize("d", [128, 64])
+@pytest.mark.parametrize("H,Sq,n_v", [(1, 70, 1024), (2, 1024, 3072), (13, 1000, 1100)])
+def test_scale_zero(H, Sq, n_v, d):
+    """All weights are equal: the mean of V, whatever the scores, and ln n_v."""
+    if _n_cu() == 256:
+        assert rows_form(H, Sq, n_v, d, 256)
+    rng = np.random.default_rng(n_v + 2 * d)
+    qb, kb, vb = (f32_to_bf16_bits(rng.standard_normal((1, H, s, d)).astype(np.float32)) for s in (Sq, n_v, n_v))
+    o, l = _launch("fp32", to_dev_bf16(qb), to_dev_bf16(kb), to_dev_bf16(vb), 0.0, n_v)
+    mean = bf16_bits_to_f32(vb).astype(np.float64).mean(2, keepdims=True)
+    _check(o, l, np.broadcast_to(mean, (1, H, Sq, d)), np.full((1, H, Sq), np.log(n_v)))
