@@ -21,9 +21,11 @@
 // single tile: same reference, same order of sums.  Rows that need the second sweep get it there, too: a wide item
 // hands back a tile with such a row, and the workgroup makes the running-max sweep of that tile later, for the rows that the wide
 // item has found; if it has collected sixteen, it takes no more wide items than it has claimed and sweeps those as single tiles.
-// With every row swept twice 24 x 9 600 take 1 820 us, 3 x 67 576 10 170 (2 290 and 13 530 with the first sweep of a tile given
-// back repeated as well; without pairs 1 870 and 10 620).  Where few rows need it in short sweeps, pairs cost: 24 x 16 384 on 570
-// keys with one such row in 500 takes 200 us (267 with that sweep repeated), without pairs, in items of 128 rows, 179.
+// Wavefronts without such a row only fetch for that sweep (fetch_for_sweep).  us, without pairs -> with pairs: 24 x 9 600 with every row
+// swept twice 1 774 -> 1 729, with one row in 160 1 882 -> 1 571 (2 293 and 2 381 with the first sweep of a tile given back repeated as
+// well; 1 867 for the latter with all wavefronts computing in the second; another box, 1 866 and 1 939 without pairs).  24 x 16 384
+// on 570 keys with one row in 500 174 -> 184: in short sweeps items of 128 rows, which such launches have without pairs, are swept again
+// less often than tiles of 256.
 #ifndef PDA_SP_DEVICE_ONLY
 #define PDA_SP_DEVICE_ONLY
 #endif
@@ -47,6 +49,49 @@ __device__ __forceinline__ KernelArgs& args_here() {
     auto x = (KernelArgs*)__builtin_amdgcn_kernarg_segment_ptr();
     asm volatile("" : "+s"(x));
     return *x;
+}
+
+// The part of a wavefront in sp_items' second sweep of a tile given back of which none of its rows needs it: its chunks of every
+// tile of K and V, and the barriers of that sweep, in the same order.  A sweep in which half of the wavefronts compute nothing is shorter.
+template <int D>
+__device__ __forceinline__ void fetch_for_sweep(KernelArgs& p, int tile, int wave) {
+    constexpr int BN = 64, G = D / 8, NBUF = sp_buffers(D, 8), TILE = BN * D * 2, CPW = TILE / 1024 / 8, RPC = 1024 / (D * 2);
+    static_assert(NBUF == 4, "the ring of sp_items with eight wavefronts");
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    const unsigned dma_base = (unsigned)(uintptr_t)(LDS_PTR(const void))smem + wave * 1024;
+    const int bh = tile / p.tiles_per_head, b = bh / p.Hg, h = bh - b * p.Hg, n_v = (int)p.n_v, nt = (n_v + BN - 1) / BN, l = fresh_lane();
+    const __bf16* kp = p.k + (int64_t)b * p.kv_bs + (int64_t)h * p.kv_hs;
+    const __bf16* vp = p.v + (int64_t)b * p.kv_bs + (int64_t)h * p.kv_hs;
+    auto issue = [&](bool is_k, int buf, int t) __attribute__((always_inline)) {
+        const __bf16* src = (is_k ? kp : vp) + (int64_t)t * BN * D;
+        const int last = n_v - t * BN - 1;                     // hidden keys are never read
+#pragma unroll
+        for (int j = 0; j < CPW; ++j) {
+            const int row = wave * RPC + l / G + j * (8 * RPC);
+            const unsigned at = (((l % G) ^ (is_k ? swz_k<D>(row) : swz_v<D>(row))) * 16);
+            lds_dma16(src, (unsigned)(row < last ? row : last) * (D * 2) + at, dma_base + ((is_k ? 0 : NBUF) + buf) * TILE + j * 8192);
+        }
+    };
+    auto barrier = [&]() __attribute__((always_inline)) {
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+    };
+    for (int t = 0; t < NBUF && t < nt; ++t) issue(true, t, t);
+    for (int t = 0; t < NBUF - 2 && t < nt; ++t) issue(false, t, t);
+    wait_vmcnt<0>();
+    barrier();                                                 // Q and the first tiles are there
+    barrier();                                                 // the first scores are
+    for (int t = 0; t < nt - 1; ++t) {
+        if (t + NBUF < nt) issue(true, t % NBUF, t + NBUF);
+        if (t + NBUF - 2 < nt) issue(false, (t + NBUF - 2) % NBUF, t + NBUF - 2);
+        if (nt - t > 4) wait_vmcnt<4 * CPW>();                 // K tile t + 2 and V tile t, as there
+        else if (nt - t == 4) wait_vmcnt<3 * CPW>();
+        else if (nt - t == 3) wait_vmcnt<2 * CPW>();
+        else wait_vmcnt<0>();
+        barrier();
+    }
+    barrier();                                                 // the sweep is over
 }
 
 template <int D, bool BASE2, bool OUT16>
@@ -534,14 +579,16 @@ __global__ __launch_bounds__(512, 2) void attn_fwd_wide_kernel(const AttnParams)
     __builtin_amdgcn_s_waitcnt(kWaitVm0);                      // no load into LDS and no store of a tile given back is under way
     lds_done();
     barrier();                                                 // w_redo and w_rows are written, LDS is free
-    KernelArgs& p = args_here();
     bool swept = true;                                         // the tiles of the list lack the running-max sweep only
     for (bool more = true; more;) {
+        KernelArgs& p = args_here();
+        int wave_here = wave;                                  // opaque: scalar registers would be taken up from here on by what is formed from it
+        asm volatile("" : "+s"(wave_here));
         int unit, end = 0x7fffffff;
         unsigned again = 0;
         if (n_redo > 0) {
             unit = p.n_items + __builtin_amdgcn_readfirstlane(w_redo[--n_redo]);
-            again = __builtin_amdgcn_readfirstlane(w_rows[n_redo][wave]);
+            again = __builtin_amdgcn_readfirstlane(w_rows[n_redo][wave_here]);
         } else if (item < n_wide) {
             if (wave == 0 && fresh_lane() == 0) {
                 const int pairs_per_head = p.tiles_per_head >> 1, bh = item / pairs_per_head;
@@ -560,7 +607,8 @@ __global__ __launch_bounds__(512, 2) void attn_fwd_wide_kernel(const AttnParams)
             unit = item < 0x7fffffff - n_wide ? item + n_wide : item;
             end = p.n_items;
         }
-        sp_items<D, 8, BASE2, OUT16, true>(p, unit, end, direct || more, wave, swept, again);
+        if (swept && again == 0) fetch_for_sweep<D>(p, unit - p.n_items, wave_here);
+        else sp_items<D, 8, BASE2, OUT16, true>(p, unit, end, direct || more, wave_here, swept, again);
         __builtin_amdgcn_s_waitcnt(kWaitVm0);
         lds_done();
         barrier();
